@@ -139,6 +139,9 @@ struct volpot_plan_s {
   double *d_mp = nullptr, *d_loc = nullptr, *d_lb = nullptr, *d_ab = nullptr, *d_usum = nullptr, *d_leaf_s2 = nullptr;
   double *d_far = nullptr, *d_afar = nullptr;  // far-field parts before the downward chains
   double *d_nw = nullptr, *d_nwa = nullptr;    // low-rank near field: per pair V_r f~, U_r^T ubar
+  // compressed near field: outgoing and received values, and their cotangents
+  double *d_e = nullptr, *d_hs = nullptr, *d_hc = nullptr, *d_ea = nullptr, *d_hsa = nullptr, *d_hca = nullptr;
+  int32_t* d_loc_box = nullptr;  // box of each leaf at level >= 2, else -1
   double* d_fs = nullptr;  // prescaled input s^2 f
   double* d_part[2] = {nullptr, nullptr};  // partial sums of split tiles: helper-stream, caller-stream stages
   int split_min = 0;
@@ -197,6 +200,16 @@ int schedule_all(volpot_plan_s* p, int nominal) {
   try {
     for (auto* v : {&p->host.fwd, &p->host.adj})
       for (Stage& s : *v) {
+        if (s.custom == C_LIN || s.custom == C_LOUT) {
+          // whole tiles, each block an equal run of them: a tile counts its chunks and as much again
+          // for its fixed cost, as below
+          const bool out = s.custom == C_LOUT, adj = v == &p->host.adj;
+          const int res = nominal > 0 ? nominal : leaf_resident_blocks(out, adj);
+          if (res <= 0) return VOLPOT_ERR_HIP;
+          const int64_t ch = s.K / s.KC, mu = p->split_min > 0 ? p->split_min : ch;
+          s.n_blocks = p->split_min < 0 ? s.n_tiles : int(std::min<int64_t>(res, (2 * ch * s.n_tiles + mu - 1) / mu));
+          continue;
+        }
         if (s.custom != C_NONE) continue;  // own kernels, one block per target
         auto key = std::array<int, 4>{s.M, s.NT, s.KC, s.cx_rel >= 0};
         auto it = resident.find(key);
@@ -234,8 +247,8 @@ int upload(volpot_plan_s* p) {
   std::vector<std::vector<SegDesc>> segd;   // segment descriptors (table pointers of this device)
   auto plan_stage = [&](const Stage& s) {
     Off o;
-    segd.emplace_back(s.seg_rel.size());
-    for (size_t i = 0; i < s.seg_rel.size(); ++i) {
+    segd.emplace_back(s.seg_fam.size());  // none for the leaf kernels
+    for (size_t i = 0; i < s.seg_fam.size(); ++i) {
       const RelDesc& rd = p->tables->rels[size_t(s.seg_rel[i])];
       const RelDesc& ra = s.cx_rel >= 0 ? p->tables->rels[size_t(s.cx_rel)] : rd;  // factored: the core
       segd.back()[i] = {ra.A, ra.K, int32_t(s.seg_fam[i]), rd.w_in, rd.w_out, rd.koff};
@@ -252,33 +265,43 @@ int upload(volpot_plan_s* p) {
   std::vector<Off> ofw, oad;
   for (auto& s : P.fwd) ofw.push_back(plan_stage(s));
   for (auto& s : P.adj) oad.push_back(plan_stage(s));
-  const bool vol = !P.layer;  // the adjoint's and the prescaled input's arrays are for volume plans only
-  size_t o_mp = (total + 255) & ~size_t(255); total = o_mp + nb;
-  size_t o_loc = (total + 255) & ~size_t(255); total = o_loc + nb;
-  size_t o_lb = (total + 255) & ~size_t(255); total = o_lb + (vol ? nb : 0);
-  size_t o_ab = (total + 255) & ~size_t(255); total = o_ab + (vol ? nb : 0);
-  size_t o_far = (total + 255) & ~size_t(255); total = o_far + nb;
-  size_t o_afar = (total + 255) & ~size_t(255); total = o_afar + (vol ? nb : 0);
-  const size_t nlr = size_t(P.pairs_lr) * kNearRank * sizeof(double);
-  size_t o_nw = (total + 255) & ~size_t(255); total = o_nw + nlr;
-  size_t o_nwa = (total + 255) & ~size_t(255); total = o_nwa + (vol ? nlr : 0);
-  size_t o_us = (total + 255) & ~size_t(255); total = o_us + (vol ? size_t(P.n_leaves) * sizeof(double) : 0);
-  size_t o_fs = (total + 255) & ~size_t(255); total = o_fs + (vol ? size_t(P.n_leaves) * kNP * sizeof(double) : 0);
+  const bool vol = !P.layer, lf = P.leaf_form;
   std::vector<double> s2(P.leaf_s2);
   size_t o_s2 = add_bytes(total, s2);
-  std::vector<int32_t> leaf_box(P.layer ? P.leaf_box : std::vector<int32_t>());
+  std::vector<int32_t> leaf_box(P.layer || lf ? P.leaf_box : std::vector<int32_t>()), loc_box;
+  if (lf) {
+    loc_box = leaf_box;
+    for (int32_t& b : loc_box)
+      if (P.box_level[size_t(b)] < 2) b = -1;
+  }
   size_t o_order = add_bytes(total, P.src_order), o_sxy = add_bytes(total, P.src_xy), o_sw = add_bytes(total, P.src_w);
   size_t o_sn = add_bytes(total, P.src_n), o_bptr = add_bytes(total, P.box_src_ptr), o_geo = add_bytes(total, P.box_geo);
-  size_t o_lbox = add_bytes(total, leaf_box);
+  size_t o_lbox = add_bytes(total, leaf_box), o_cbox = add_bytes(total, loc_box);
   size_t o_pxy = add_bytes(total, P.pt_xy), o_ploc = add_bytes(total, P.pt_loc), o_pnp = add_bytes(total, P.pt_near_ptr);
   const size_t n_pairs = P.pt_xi.size() / 3;
   size_t o_pnl = add_bytes(total, P.pt_near_leaf), o_pwp = add_bytes(total, P.pt_w_ptr);
-  size_t o_pmom = (total + 255) & ~size_t(255); total = o_pmom + n_pairs * 3 * kNP * sizeof(double);
   size_t o_pxi = add_bytes(total, P.pt_xi);
   size_t o_pwb = add_bytes(total, P.pt_w_box);
-  size_t o_sq = (total + 255) & ~size_t(255); total = o_sq + std::max<size_t>(size_t(P.n_src), 1) * sizeof(double);
-  size_t o_smu = (total + 255) & ~size_t(255); total = o_smu + std::max<size_t>(size_t(P.n_src), 1) * 2 * sizeof(double);
-  std::vector<char> host(total, 0);
+  // what follows is workspace: zeroed on the device, not copied from the host. The adjoint's and
+  // the prescaled input's arrays are for volume plans only.
+  const size_t o_work = (total + 255) & ~size_t(255);
+  total = o_work;
+  auto work = [&](size_t bytes) {
+    const size_t o = total;
+    total = (o + bytes + 255) & ~size_t(255);
+    return o;
+  };
+  const size_t nlr = lf ? 0 : size_t(P.pairs_lr) * kNearRank * sizeof(double);
+  const size_t per_leaf = size_t(P.n_leaves) * sizeof(double), nlf = lf ? per_leaf : 0;
+  const size_t o_mp = work(nb), o_loc = work(nb), o_lb = work(vol ? nb : 0), o_ab = work(vol ? nb : 0), o_far = work(nb);
+  const size_t o_afar = work(vol ? nb : 0), o_nw = work(nlr), o_nwa = work(vol ? nlr : 0);
+  const size_t o_e = work(nlf * kOutAll), o_ea = work(nlf * kOutAll), o_hs = work(nlf * 4 * kEdge), o_hsa = work(nlf * 4 * kEdge);
+  const size_t o_hc = work(nlf * 4 * kCorner), o_hca = work(nlf * 4 * kCorner);
+  const size_t o_us = work(vol ? per_leaf : 0), o_fs = work(vol && !lf ? per_leaf * kNP : 0);
+  const size_t o_pmom = work(n_pairs * 3 * kNP * sizeof(double));
+  const size_t o_sq = work(std::max<size_t>(size_t(P.n_src), 1) * sizeof(double));
+  const size_t o_smu = work(std::max<size_t>(size_t(P.n_src), 1) * 2 * sizeof(double));
+  std::vector<char> host(o_work, 0);
   auto put = [&](size_t o, const auto& v) {
     if (!v.empty()) std::memcpy(host.data() + o, v.data(), v.size() * sizeof(v[0]));
   };
@@ -294,12 +317,15 @@ int upload(volpot_plan_s* p) {
   static_assert(sizeof(Piece) == sizeof(PieceDesc), "piece layouts differ");
   put(o_s2, s2);
   put(o_order, P.src_order); put(o_sxy, P.src_xy); put(o_sw, P.src_w); put(o_sn, P.src_n);
-  put(o_bptr, P.box_src_ptr); put(o_geo, P.box_geo); put(o_lbox, leaf_box);
+  put(o_bptr, P.box_src_ptr); put(o_geo, P.box_geo); put(o_lbox, leaf_box); put(o_cbox, loc_box);
   put(o_pxy, P.pt_xy); put(o_ploc, P.pt_loc); put(o_pnp, P.pt_near_ptr); put(o_pnl, P.pt_near_leaf);
   put(o_pxi, P.pt_xi); put(o_pwp, P.pt_w_ptr); put(o_pwb, P.pt_w_box);
   if (hipMalloc(&p->d_block, total) != hipSuccess) return VOLPOT_ERR_OOM;
   p->device_bytes = int64_t(total);
-  if (hipMemcpy(p->d_block, host.data(), total, hipMemcpyHostToDevice) != hipSuccess) return VOLPOT_ERR_HIP;
+  if (hipMemcpy(p->d_block, host.data(), o_work, hipMemcpyHostToDevice) != hipSuccess ||
+      (total > o_work && hipMemset(p->d_block + o_work, 0, total - o_work) != hipSuccess) ||
+      hipStreamSynchronize(nullptr) != hipSuccess)
+    return VOLPOT_ERR_HIP;
   char* b = p->d_block;
   auto mk = [&](const Stage& s, const Off& o) {
     DevStage d;
@@ -325,6 +351,13 @@ int upload(volpot_plan_s* p) {
   p->d_afar = reinterpret_cast<double*>(b + o_afar);
   p->d_nw = reinterpret_cast<double*>(b + o_nw);
   p->d_nwa = reinterpret_cast<double*>(b + o_nwa);
+  p->d_e = reinterpret_cast<double*>(b + o_e);
+  p->d_ea = reinterpret_cast<double*>(b + o_ea);
+  p->d_hs = reinterpret_cast<double*>(b + o_hs);
+  p->d_hsa = reinterpret_cast<double*>(b + o_hsa);
+  p->d_hc = reinterpret_cast<double*>(b + o_hc);
+  p->d_hca = reinterpret_cast<double*>(b + o_hca);
+  p->d_loc_box = reinterpret_cast<int32_t*>(b + o_cbox);
   p->d_usum = reinterpret_cast<double*>(b + o_us);
   p->d_fs = reinterpret_cast<double*>(b + o_fs);
   p->d_leaf_s2 = reinterpret_cast<double*>(b + o_s2);
@@ -401,8 +434,41 @@ const double* arr_ptr(volpot_plan_s* p, int8_t a, const double* in, double* out)
     case A_AFAR: return p->d_afar;
     case A_NW: return p->d_nw;
     case A_NWA: return p->d_nwa;
+    case A_E: return p->d_e;
+    case A_HS: return p->d_hs;
+    case A_HC: return p->d_hc;
+    case A_EA: return p->d_ea;
+    case A_HSA: return p->d_hsa;
+    case A_HCA: return p->d_hca;
     default: return nullptr;
   }
+}
+
+// A leaf kernel's launch: leaf values in (the apply's input), tables and work arrays of the plan.
+hipError_t launch_leaf(volpot_plan_s* p, const DevStage& d, bool adjoint, const double* in, double* out, hipStream_t st) {
+  const Stage& s = *d.st;
+  const bool lout = s.custom == C_LOUT;
+  LeafParams g;
+  std::memset(&g, 0, sizeof(g));
+  g.x = in;
+  g.table = p->tables->rels[size_t(s.leaf_rel)].A;
+  g.leaf_s2 = p->d_leaf_s2;
+  g.leaf_box = p->d_leaf_box;
+  // forward locals and their cotangents belong to leaves at level >= 2, multipoles to every leaf
+  g.loc_box = lout == adjoint ? p->d_leaf_box : p->d_loc_box;
+  g.n_leaves = int32_t(p->host.n_leaves);
+  g.n_tiles = s.n_tiles;
+  g.n_chunks = s.K / s.KC;
+  g.n_groups = s.M / 64;
+  g.ne = p->host.ne;
+  g.s2_in = !adjoint;
+  g.in_e = p->d_ea; g.in_edge = p->d_hs; g.in_corner = p->d_hc;
+  g.in_exp = adjoint ? p->d_ab : p->d_loc;
+  g.out_e = p->d_e; g.out_edge = p->d_hsa; g.out_corner = p->d_hca;
+  g.out_exp = adjoint ? p->d_lb : p->d_mp;
+  g.out = out;
+  g.r1_ptr = d.r1_ptr; g.r1_idx = d.r1_idx; g.r1_coef = d.r1_coef; g.r1_base = p->d_mp;
+  return lout ? launch_leaf_out(g, adjoint, s.n_blocks, st) : launch_leaf_in(g, adjoint, s.n_blocks, st);
 }
 
 hipEvent_t take_event(volpot_plan_s* p) {
@@ -460,11 +526,11 @@ int run(volpot_plan_s* p, bool adjoint, const double* in, const double* in2, dou
       if (launch_layer_prep(p->host.n_src, p->d_order, p->d_sw, p->d_sn, in, in2, p->d_sq, p->d_smu, main) != hipSuccess)
         return VOLPOT_ERR_HIP;
       timed_end(p, K_UP, main, ea, eb);
-    } else if (!adjoint) {  // every forward source read uses s^2 f: scale once
+    } else if (!adjoint && !p->host.leaf_form) {  // every forward source read uses s^2 f: scale once
       timed_begin(p, timing, K_UP, main, &ea, &eb);
       if (launch_prescale(in, p->d_leaf_s2, p->d_fs, p->host.n_leaves, main) != hipSuccess) return VOLPOT_ERR_HIP;
       timed_end(p, K_UP, main, ea, eb);
-    } else if (p->host.adj_leaf_sums) {  // leaf sums of the cotangent, for log terms of leaves above level 2
+    } else if (adjoint && p->host.adj_leaf_sums) {  // leaf sums of the cotangent, for log terms of leaves above level 2
       timed_begin(p, timing, K_ASUM, main, &ea, &eb);
       if (launch_rowsum(in, p->d_usum, p->host.n_leaves, main) != hipSuccess) return VOLPOT_ERR_HIP;
       timed_end(p, K_ASUM, main, ea, eb);
@@ -483,6 +549,8 @@ int run(volpot_plan_s* p, bool adjoint, const double* in, const double* in2, dou
       hipError_t e = hipSuccess;
       if (s.custom == C_P2M)
         e = launch_p2m(s.n_tiles, d.c_tgt, p->d_bptr, p->d_geo, p->d_sxy, p->d_sq, p->d_smu, p->d_mp, st);
+      else if (s.custom == C_LIN || s.custom == C_LOUT)
+        e = launch_leaf(p, d, adjoint, in, out, st);
       else if (s.custom == C_P2L)
         e = launch_p2l(s.n_tiles, d.c_tgt, d.c_ptr, d.c_idx, p->d_bptr, p->d_geo, p->d_sxy, p->d_sq, p->d_smu, p->d_far, st);
       else

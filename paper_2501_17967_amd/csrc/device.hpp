@@ -75,6 +75,29 @@ hipError_t launch_prescale(const double* x, const double* s2, double* out, int64
 // usum[a] = sum of the 256 values of leaf a
 hipError_t launch_rowsum(const double* x, double* usum, int64_t n_leaves, hipStream_t stream);
 
+// ---------------------------------------------------------------- leaf kernels (leaf.hip)
+// One launch of leaf_in or leaf_out over all leaves, in the caller's order. Passed by value.
+struct LeafParams {
+  const double* x;            // leaf values, [n_leaves][256]
+  const double* table;        // fragment-major kRelLI / kRelLO or their adjoints
+  const double* leaf_s2;
+  const int32_t* leaf_box;    // box of each leaf
+  const int32_t* loc_box;     // box whose expansion a leaf reads or writes, -1: none
+  int32_t n_leaves, n_tiles;  // tiles of kLeafTile leaves
+  int32_t n_chunks;           // leaf_out: chunks of 16 columns per part
+  int32_t n_groups;           // adjoint leaf_in: groups of 16 rows per part
+  int32_t ne;                 // reals per expansion
+  int32_t s2_in;              // 1: multiply the values by s^2 of their leaf
+  const double *in_e, *in_edge, *in_corner, *in_exp;          // leaf_out
+  double *out_e, *out_edge, *out_corner, *out_exp, *out;      // leaf_in; leaf_out's output
+  const int32_t *r1_ptr, *r1_idx;  // forward leaf_out: log terms of each leaf, n_leaves + 1
+  const double *r1_coef, *r1_base;
+};
+// Blocks of leaf_in / leaf_out that fit on the current device at once (0 on error).
+int leaf_resident_blocks(bool out, bool adjoint);
+hipError_t launch_leaf_in(const LeafParams& p, bool adjoint, int n_blocks, hipStream_t stream);
+hipError_t launch_leaf_out(const LeafParams& p, bool adjoint, int n_blocks, hipStream_t stream);
+
 // ---------------------------------------------------------------- layer potentials (layer.hip)
 // Nodes of a leaf on [-1,1] (first-kind Chebyshev, ascending); passed by value.
 struct LeafNodes {

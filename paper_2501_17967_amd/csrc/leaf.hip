@@ -1,0 +1,460 @@
+// Leaf kernels of the compressed near field, FP64 on MFMA.
+//
+// A leaf's 256 values split into four parts, even or odd in x and in y, of 64 values each (sums
+// and differences of the four mirrored nodes). Every map between a leaf's values and what the
+// other stages exchange commutes with both reflections, so it is four 64-column blocks instead of
+// one 256-column table, a quarter of the work:
+//   leaf_in   values -> outgoing values e (28 per part) and multipoles          (forward)
+//             cotangents -> cotangents of the received values and of the locals (adjoint)
+//   leaf_out  the leaf's own values, the values received across its edges and corners, and its
+//             local expansion -> its potential                                   (forward)
+//             cotangents, cotangents of e and of the multipole -> the gradient   (adjoint)
+// Both work on leaves in the caller's order: they stream the leaf arrays.
+//
+// Part p = px + 2 py. Sums are left without the factor 1/2 of the orthonormal transform; the
+// tables carry it. MFMA layout as in kernels.hip.
+#include <hip/hip_runtime.h>
+
+#include "device.hpp"
+#include "plan.hpp"
+
+namespace vp {
+
+typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
+#define GLOBAL __attribute__((address_space(1)))
+typedef const GLOBAL double* gdp;
+typedef const GLOBAL d2* gd2p;
+
+// Blocks are dispatched round-robin over the 8 XCDs; each XCD gets a contiguous range of tiles.
+__device__ __forceinline__ int leaf_block(int b, int G) {
+  const int q = G >> 3, r = G & 7, x = b & 7;
+  return x * q + min(x, r) + (b >> 3);
+}
+__device__ __forceinline__ d4 mfma(double a, double b, d4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// The real of part p's term i in an expansion of interleaved (Re, Im): Re z^n is even in y, Im z^n
+// odd; in x they have the parity of n and of n - 1.
+__device__ __forceinline__ int part_real(int p, int i) { return 4 * i + (p == 0 ? 0 : (p == 1 ? 2 : (p == 2 ? 3 : 1))); }
+
+// Four raw pairs of one leaf: the mirrored nodes of rows j, 15 - j and columns i, i + 1, 15 - i, 14 - i
+struct Raw {
+  d2 v[4];
+  __device__ __forceinline__ void leaf(gdp x, int j, int i) {
+    v[0] = *(gd2p)(x + 16 * j + i);
+    v[1] = *(gd2p)(x + 16 * j + 14 - i);
+    v[2] = *(gd2p)(x + 16 * (15 - j) + i);
+    v[3] = *(gd2p)(x + 16 * (15 - j) + 14 - i);
+  }
+  __device__ __forceinline__ void unmirror() {
+    v[1] = d2{v[1].y, v[1].x};
+    v[3] = d2{v[3].y, v[3].x};
+  }
+  __device__ __forceinline__ void sum_x() {  // v[0] +- v[1], v[2] +- v[3]
+    const d2 a = v[0], b = v[1], c = v[2], d = v[3];
+    v[0] = a + b; v[1] = a - b; v[2] = c + d; v[3] = c - d;
+  }
+  __device__ __forceinline__ void sum_y() {  // v[0] +- v[2], v[1] +- v[3]
+    const d2 a = v[0], b = v[1], c = v[2], d = v[3];
+    v[0] = a + c; v[1] = b + d; v[2] = a - c; v[3] = b - d;
+  }
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = d2{0.0, 0.0};
+  }
+};
+
+constexpr int kSlots = 32;    // leaves per tile
+constexpr int kThreads = 256;
+
+// ---------------------------------------------------------------- leaf_in
+// A tile's 256 x 32 parity sums sit in LDS (row stride 65: conflict-free operand reads). The
+// forward form has 48 rows per part: wave p keeps part p's 48 x 64 table in registers for the
+// whole launch and the next tile's values are loaded while this one is multiplied; it is bound by
+// the 2 KB read and 1.4 KB written per leaf. The adjoint form has 160 or 176 rows per part: the
+// waves share out the groups of 16 rows, each group with all four parts (whose sums its results
+// need), and stream the table's fragments from the L2.
+constexpr int kLdIn = 65;
+
+__device__ __forceinline__ void in_load(const LeafParams& p, int tile, int tid, Raw (&r)[4], double (&sc)[4]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int idx = tid + q * kThreads, leaf = tile * kSlots + (idx >> 5);
+    const bool ok = leaf < p.n_leaves;
+    const int l = ok ? leaf : 0;
+    sc[q] = ok ? (p.s2_in ? p.leaf_s2[l] : 1.0) : 0.0;
+    r[q].leaf((gdp)p.x + (size_t)l * 256, (idx & 31) >> 2, 2 * (idx & 3));
+    if (!ok) r[q].zero();
+  }
+}
+__device__ __forceinline__ void in_store(int tid, Raw (&r)[4], const double (&sc)[4], double* Bs) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int idx = tid + q * kThreads, slot = idx >> 5, k = 8 * ((idx & 31) >> 2) + 2 * (idx & 3);
+    r[q].unmirror();
+    r[q].sum_x();
+    r[q].sum_y();
+#pragma unroll
+    for (int pt = 0; pt < 4; ++pt) {
+      double* b = Bs + (pt * kSlots + slot) * kLdIn + k;
+      b[0] = r[q].v[pt].x * sc[q];
+      b[1] = r[q].v[pt].y * sc[q];
+    }
+  }
+}
+
+__global__ void __launch_bounds__(kThreads, 2) leaf_in_kernel(const LeafParams p) {
+  __shared__ double Bs[4 * kSlots * kLdIn];
+  const int tid = threadIdx.x, lane = tid & 63, part = tid >> 6;
+  const int blk = leaf_block(blockIdx.x, gridDim.x);
+  const int t0 = (int)((int64_t)blk * p.n_tiles / gridDim.x), t1 = (int)((int64_t)(blk + 1) * p.n_tiles / gridDim.x);
+  double a[16][3];
+#pragma unroll
+  for (int kk = 0; kk < 16; ++kk)
+#pragma unroll
+    for (int t = 0; t < 3; ++t) a[kk][t] = ((gdp)p.table)[(kk * 12 + part * 3 + t) * 64 + lane];
+  Raw r[4];
+  double sc[4];
+  if (t0 < t1) in_load(p, t0, tid, r, sc);
+  for (int tile = t0; tile < t1; ++tile) {
+    __syncthreads();  // the previous tile's values are read
+    in_store(tid, r, sc, Bs);
+    __syncthreads();
+    if (tile + 1 < t1) in_load(p, tile + 1, tid, r, sc);
+    d4 acc[3][2];
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[t][j] = d4{0.0, 0.0, 0.0, 0.0};
+    const double* B0 = Bs + (part * kSlots + (lane & 15)) * kLdIn + (lane >> 4);
+#pragma unroll
+    for (int kk = 0; kk < 16; ++kk) {
+      const double b0 = B0[4 * kk], b1 = B0[16 * kLdIn + 4 * kk];
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        acc[t][0] = mfma(a[kk][t], b0, acc[t][0]);
+        acc[t][1] = mfma(a[kk][t], b1, acc[t][1]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int leaf = tile * kSlots + 16 * j + (lane & 15);
+      if (leaf >= p.n_leaves) continue;
+      double* __restrict__ e = p.out_e + (size_t)leaf * kOutAll + kOut * part;
+      double* __restrict__ m = p.out_exp + (size_t)p.leaf_box[leaf] * p.ne;
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int row = 16 * t + 4 * q + (lane >> 4);
+          if (row < kOut) e[row] = acc[t][j][q];
+          else if (row - kOut < p.ne / 4) m[part_real(part, row - kOut)] = acc[t][j][q];
+        }
+    }
+  }
+}
+
+__global__ void __launch_bounds__(kThreads, 2) leaf_in_adj_kernel(const LeafParams p) {
+  __shared__ double Bs[4 * kSlots * kLdIn];
+  const int tid = threadIdx.x, lane = tid & 63;
+  // waves take the groups in turn; every other block starts two waves on, so that the SIMDs
+  // share the groups left over
+  const int wave = ((tid >> 6) + 2 * (blockIdx.x >> 3)) & 3;
+  const int blk = leaf_block(blockIdx.x, gridDim.x);
+  const int t0 = (int)((int64_t)blk * p.n_tiles / gridDim.x), t1 = (int)((int64_t)(blk + 1) * p.n_tiles / gridDim.x);
+  Raw r[4];
+  double sc[4];
+  if (t0 < t1) in_load(p, t0, tid, r, sc);
+  for (int tile = t0; tile < t1; ++tile) {
+    __syncthreads();
+    in_store(tid, r, sc, Bs);
+    __syncthreads();
+    if (tile + 1 < t1) in_load(p, tile + 1, tid, r, sc);
+    const double* B0 = Bs + (lane & 15) * kLdIn + (lane >> 4);
+    for (int g = wave; g < p.n_groups; g += 4) {
+      gdp A = (gdp)p.table + (size_t)g * 4 * 64 + lane;
+      const size_t step = (size_t)p.n_groups * 4 * 64;
+      d4 acc[4][2];
+#pragma unroll
+      for (int pt = 0; pt < 4; ++pt)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[pt][j] = d4{0.0, 0.0, 0.0, 0.0};
+      double a[2][4][4];  // four k-steps of fragments, and the next four in flight
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int pt = 0; pt < 4; ++pt) a[0][k][pt] = A[k * step + pt * 64];
+#pragma unroll
+      for (int kq = 0; kq < 4; ++kq) {
+        if (kq < 3)
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int pt = 0; pt < 4; ++pt) a[(kq + 1) & 1][k][pt] = A[(4 * (kq + 1) + k) * step + pt * 64];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+          for (int pt = 0; pt < 4; ++pt) {
+            const double* b = B0 + pt * kSlots * kLdIn + 4 * (4 * kq + k);
+            acc[pt][0] = mfma(a[kq & 1][k][pt], b[0], acc[pt][0]);
+            acc[pt][1] = mfma(a[kq & 1][k][pt], b[16 * kLdIn], acc[pt][1]);
+          }
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int leaf = tile * kSlots + 16 * j + (lane & 15);
+        if (leaf >= p.n_leaves) continue;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int row = 4 * q + (lane >> 4);
+          const double x0 = acc[0][j][q], x1 = acc[1][j][q], x2 = acc[2][j][q], x3 = acc[3][j][q];
+          if (g < 3) {  // right and left edge: even and odd in y
+            double* o = p.out_edge + (size_t)leaf * (4 * kEdge) + 16 * g + row;
+            o[0] = x0 + x1;
+            o[kEdge] = x0 - x1;
+            o[kEdge / 2] = x2 + x3;
+            o[kEdge + kEdge / 2] = x2 - x3;
+          } else if (g < 6) {  // upper and lower edge: even and odd in x
+            double* o = p.out_edge + (size_t)leaf * (4 * kEdge) + 2 * kEdge + 16 * (g - 3) + row;
+            o[0] = x0 + x2;
+            o[kEdge] = x0 - x2;
+            o[kEdge / 2] = x1 + x3;
+            o[kEdge + kEdge / 2] = x1 - x3;
+          } else if (g < kLinGroups) {  // corners
+            double* o = p.out_corner + (size_t)leaf * (4 * kCorner) + 16 * (g - 6) + row;
+            const double s0 = x0 + x1, d0 = x0 - x1, s1 = x2 + x3, d1 = x2 - x3;
+            o[0] = s0 + s1;
+            o[kCorner] = d0 + d1;
+            o[2 * kCorner] = s0 - s1;
+            o[3 * kCorner] = d0 - d1;
+          } else {
+            const int i = 16 * (g - kLinGroups) + row;
+            const int box = p.loc_box[leaf];
+            if (i < p.ne / 4 && box >= 0) {  // reals 4i .. 4i + 3 are parts 0, 3, 1, 2
+              double* o = p.out_exp + (size_t)box * p.ne + 4 * i;
+              *reinterpret_cast<d2*>(o) = d2{x0, x3};
+              *reinterpret_cast<d2*>(o + 2) = d2{x1, x2};
+            }
+          }
+        }
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------- leaf_out
+// The product of a tile's 256 rows (64 of each part) with its columns in chunks of 16 per part:
+// wave w holds rows 16 w .. 16 w + 15 of all four parts, so the sums that give the mirrored nodes
+// are between its own accumulators. A chunk (256 x 16 of the table, 4 x 16 values of 32 leaves)
+// goes through LDS while the next one's loads are in flight, as in grg_kernel. Every kind of
+// column is four raw pairs per thread and sums of them: mirrored nodes, the two edges or four
+// corners that the parts add or subtract, or an expansion's reals.
+constexpr int kLdOut = 17;
+constexpr int kCorner0 = (64 + kEdge) / 16;  // first chunk of the corners' columns
+
+template <bool ADJ>
+struct OutLoader {
+  Raw r;
+  d2 a[8];
+  // the raw pairs of chunk c for leaf `leaf`, term pair starting at 2 m
+  __device__ __forceinline__ void load(const LeafParams& p, int c, int leaf, int box, int tid) {
+    gd2p A2 = (gd2p)p.table + (size_t)c * (256 * 16 / 2);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) a[q] = A2[tid + q * kThreads];
+    const int m = tid & 7, o = 2 * m;
+    if (c < 4) {
+      r.leaf((gdp)p.x + (size_t)leaf * 256, 2 * c + (m >> 2), 2 * (m & 3));
+      return;
+    }
+    if (ADJ) {
+      if (c < 6) {
+        const int k = 16 * (c - 4) + o;
+        gdp e = (gdp)p.in_e + (size_t)leaf * kOutAll + (k < kOut ? k : 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r.v[q] = *(gd2p)(e + q * kOut);
+        if (k >= kOut) r.zero();
+        return;
+      }
+    } else {
+      if (c < 7) {
+        gdp h = (gdp)p.in_edge + (size_t)leaf * (4 * kEdge) + 16 * (c - 4) + o;
+        r.v[0] = *(gd2p)(h);
+        r.v[1] = *(gd2p)(h + kEdge);
+        r.v[2] = *(gd2p)(h + kEdge / 2);
+        r.v[3] = *(gd2p)(h + kEdge + kEdge / 2);
+        return;
+      }
+      if (c < 10) {
+        gdp h = (gdp)p.in_edge + (size_t)leaf * (4 * kEdge) + 2 * kEdge + 16 * (c - 7) + o;
+        r.v[0] = *(gd2p)(h);
+        r.v[1] = *(gd2p)(h + kEdge / 2);
+        r.v[2] = *(gd2p)(h + kEdge);
+        r.v[3] = *(gd2p)(h + kEdge + kEdge / 2);
+        return;
+      }
+      if (c < kCorner0 + kCorner / 16) {
+        gdp h = (gdp)p.in_corner + (size_t)leaf * (4 * kCorner) + 16 * (c - kCorner0) + o;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r.v[q] = *(gd2p)(h + q * kCorner);
+        return;
+      }
+    }
+    const int i = 16 * (c - (ADJ ? 6 : kCorner0 + kCorner / 16)) + o;  // terms i, i + 1 of each part: reals 4i .. 4i + 7
+    const bool ok = box >= 0 && i < p.ne / 4;
+    gdp x = (gdp)p.in_exp + (ok ? (size_t)box * p.ne + 4 * i : 0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) r.v[q] = *(gd2p)(x + 2 * q);
+    if (!ok) r.zero();
+  }
+  __device__ __forceinline__ void store(int c, double scale, int tid, double* As, double* Bs) {
+    d2* As2 = reinterpret_cast<d2*>(As);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) As2[tid + q * kThreads] = a[q];
+    if (c < 4) {
+      r.unmirror();
+      r.sum_x();
+      r.sum_y();
+#pragma unroll
+      for (int q = 0; q < 4; ++q) r.v[q] *= scale;
+    } else if (!ADJ && c < 7) {
+      r.sum_x();
+    } else if (!ADJ && c < 10) {
+      r.sum_y();
+    } else if (!ADJ && c < kCorner0 + kCorner / 16) {
+      r.sum_x();
+      r.sum_y();
+    } else if (!ADJ || c >= 6) {  // reals (4i: parts 0, 3, 1, 2)
+      const d2 u = r.v[0], v = r.v[1], w = r.v[2], z = r.v[3];
+      r.v[0] = d2{u.x, w.x};
+      r.v[1] = d2{v.x, z.x};
+      r.v[2] = d2{v.y, z.y};
+      r.v[3] = d2{u.y, w.y};
+    }
+    const int slot = tid >> 3, k = 2 * (tid & 7);
+#pragma unroll
+    for (int pt = 0; pt < 4; ++pt) {
+      double* b = Bs + (pt * kSlots + slot) * kLdOut + k;
+      b[0] = r.v[pt].x;
+      b[1] = r.v[pt].y;
+    }
+  }
+};
+
+template <bool ADJ>
+__global__ void __launch_bounds__(kThreads, 2) leaf_out_kernel(const LeafParams p) {
+  __shared__ double As[256 * 16];
+  __shared__ double Bs[4 * kSlots * kLdOut];
+  __shared__ double r1s[kSlots];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int blk = leaf_block(blockIdx.x, gridDim.x);
+  const int t0 = (int)((int64_t)blk * p.n_tiles / gridDim.x), t1 = (int)((int64_t)(blk + 1) * p.n_tiles / gridDim.x);
+  const int n_chunks = p.n_chunks;
+  const double* __restrict__ Aw = As + wave * 64 + lane;
+  const double* __restrict__ Bw = Bs + (lane & 15) * kLdOut + (lane >> 4);
+  for (int tile = t0; tile < t1; ++tile) {
+    const int sl = tile * kSlots + (tid >> 3);  // the leaf whose values this thread stages
+    const bool ok = sl < p.n_leaves;
+    const int leaf = ok ? sl : 0;
+    const int box = ok ? p.loc_box[leaf] : -1;
+    const double scale = ok ? (p.s2_in ? p.leaf_s2[leaf] : 1.0) : 0.0;
+    OutLoader<ADJ> L;
+    L.load(p, 0, leaf, box, tid);
+    if (!ADJ) {  // the leaf's log terms, summed by its eight threads in a fixed order
+      double c = 0.0;
+      if (ok)
+        for (int e = p.r1_ptr[leaf] + (tid & 7); e < p.r1_ptr[leaf + 1]; e += 8)
+          c += p.r1_coef[e] * ((gdp)p.r1_base)[(size_t)p.r1_idx[e] * p.ne];
+      c += __shfl_xor(c, 1, 64);
+      c += __shfl_xor(c, 2, 64);
+      c += __shfl_xor(c, 4, 64);
+      if ((tid & 7) == 0) r1s[tid >> 3] = c;
+    }
+    d4 acc[4][2];
+#pragma unroll
+    for (int pt = 0; pt < 4; ++pt)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[pt][j] = d4{0.0, 0.0, 0.0, 0.0};
+    L.store(0, scale, tid, As, Bs);
+    __syncthreads();
+    for (int c = 0;;) {
+      const bool more = c + 1 < n_chunks;
+      if (more) L.load(p, c + 1, leaf, box, tid);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        double a[4], b[4][2];
+#pragma unroll
+        for (int pt = 0; pt < 4; ++pt) {
+          a[pt] = Aw[(kk * 16 + pt * 4) * 64];
+          b[pt][0] = Bw[pt * kSlots * kLdOut + 4 * kk];
+          b[pt][1] = Bw[(pt * kSlots + 16) * kLdOut + 4 * kk];
+        }
+#pragma unroll
+        for (int pt = 0; pt < 4; ++pt) {
+          acc[pt][0] = mfma(a[pt], b[pt][0], acc[pt][0]);
+          acc[pt][1] = mfma(a[pt], b[pt][1], acc[pt][1]);
+        }
+      }
+      if (!more) break;
+      ++c;
+      __syncthreads();  // every wave is done reading the chunk
+      L.store(c, scale, tid, As, Bs);
+      __syncthreads();  // the next chunk is visible
+    }
+    // rows 16 w + 4 q + lane / 16 of each part: node row j = 2 w + q / 2, column i = 4 (q % 2) + lane / 16
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int s = 16 * h + (lane & 15), lf = tile * kSlots + s;
+      if (lf < p.n_leaves) {
+        const double r1 = ADJ ? 0.0 : r1s[s];
+        const double so = ADJ ? p.leaf_s2[lf] : 1.0;
+        double* __restrict__ o = p.out + (size_t)lf * 256;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int j = 2 * wave + (q >> 1), i = 4 * (q & 1) + (lane >> 4);
+          const double x0 = acc[0][h][q], x1 = acc[1][h][q], x2 = acc[2][h][q], x3 = acc[3][h][q];
+          const double s0 = x0 + x1, d0 = x0 - x1, s1 = x2 + x3, d1 = x2 - x3;
+          o[16 * j + i] = (s0 + s1 + r1) * so;
+          o[16 * j + 15 - i] = (d0 + d1 + r1) * so;
+          o[16 * (15 - j) + i] = (s0 - s1 + r1) * so;
+          o[16 * (15 - j) + 15 - i] = (d0 - d1 + r1) * so;
+        }
+      }
+    }
+    __syncthreads();  // LDS is free for the next tile
+  }
+}
+
+static const void* leaf_kernel(bool out, bool adjoint) {
+  if (out)
+    return adjoint ? reinterpret_cast<const void*>(&leaf_out_kernel<true>) : reinterpret_cast<const void*>(&leaf_out_kernel<false>);
+  return adjoint ? reinterpret_cast<const void*>(&leaf_in_adj_kernel) : reinterpret_cast<const void*>(&leaf_in_kernel);
+}
+
+int leaf_resident_blocks(bool out, bool adjoint) {
+  int dev = 0, cus = 0, per_cu = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, leaf_kernel(out, adjoint), kThreads, 0) != hipSuccess)
+    return 0;
+  return per_cu * cus;
+}
+
+hipError_t launch_leaf_in(const LeafParams& p, bool adjoint, int n_blocks, hipStream_t stream) {
+  if (p.n_tiles <= 0) return hipSuccess;
+  const dim3 grid(unsigned(n_blocks < p.n_tiles ? n_blocks : p.n_tiles));
+  if (adjoint) hipLaunchKernelGGL(leaf_in_adj_kernel, grid, dim3(kThreads), 0, stream, p);
+  else hipLaunchKernelGGL(leaf_in_kernel, grid, dim3(kThreads), 0, stream, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_leaf_out(const LeafParams& p, bool adjoint, int n_blocks, hipStream_t stream) {
+  if (p.n_tiles <= 0) return hipSuccess;
+  const dim3 grid(unsigned(n_blocks < p.n_tiles ? n_blocks : p.n_tiles));
+  if (adjoint) hipLaunchKernelGGL(leaf_out_kernel<true>, grid, dim3(kThreads), 0, stream, p);
+  else hipLaunchKernelGGL(leaf_out_kernel<false>, grid, dim3(kThreads), 0, stream, p);
+  return hipGetLastError();
+}
+
+}  // namespace vp

@@ -867,6 +867,10 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   const int NTL = (tile_leaf == 32 || tile_leaf == 64) ? tile_leaf : 32;
   // k-chunk of the near-field stages; the low-rank form's segments (K = 48 or 64) take 16
   const bool lr = !layer && !dense_near;
+  // compressed form of the low-rank near field (leaf.hip): the pair rows give way to what a leaf
+  // sends (A_E) and what it receives across each edge and corner
+  const bool lf = lr && P.n_leaves >= kLeafFormMin;
+  P.leaf_form = lf;
   const int KCL = (lr || kchunk_leaf == 16) ? 16 : 32;
   const int NTB = (tile_box == 16 || tile_box == 32 || tile_box == 64) ? tile_box : 32;
   // the expansion-row stages that read or write leaf data (K or M = 256: S2M, S2L and their
@@ -910,6 +914,20 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
     st.K = st.KC = mats.K[size_t(st.cx_rel)];
     if (st.KC == 32 && st.NT == 32) st.NT = 64;
   };
+  // one launch of a leaf kernel over all leaves: reported as n_tiles segments of the kernel's table
+  auto leaf_stage = [&](int kind, const char* name, int8_t custom, int rel, int K, int KC) {
+    Stage st;
+    init_stage(st, kind, name, -1, mats.M[size_t(rel)], K, kLeafTile, A_NONE, 0);
+    st.KC = KC;
+    st.custom = custom;
+    st.leaf_rel = rel;
+    st.n_tiles = int((P.n_leaves + kLeafTile - 1) / kLeafTile);
+    st.seg_rel.assign(size_t(st.n_tiles), rel);
+    st.seg_k.assign(size_t(st.n_tiles), K);
+    st.flops = 2.0 * mats.nnz[size_t(rel)] * double(P.n_leaves);
+    st.flops_issued = 2.0 * st.M * K * kLeafTile * double(st.n_tiles);
+    return st;
+  };
   // boxes at levels >= 2 ordered by (level, quadrant, tree, morton): targets of one tile then
   // share their V-list offset pattern
   std::vector<int32_t> deep_by_quadrant;
@@ -943,7 +961,11 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
     st.n_tiles = int(st.c_tgt.size());
     defer(std::move(st), {}, {}, {}, false);
   }
-  if (!layer) {  // S2M: every leaf's multipole
+  if (lf) {  // S2M: every leaf's multipole and outgoing values
+    P.n_s2m = P.n_leaves;
+    defer(leaf_stage(K_UP, "S2M", C_LIN, kRelLI, 64, 64), {}, {}, {}, false);
+  }
+  if (!layer && !lf) {  // S2M: every leaf's multipole
     std::vector<int32_t> tg;
     for (int32_t b = 0; b < NB; ++b) if (P.box_leaf[b] >= 0) tg.push_back(b);
     Stage st; init_stage(st, K_UP, "S2M", -1, kNE, kNP, kLeafDataTile, A_MP, kNE);
@@ -1101,13 +1123,13 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
     std::vector<int32_t> tg;
     for (int32_t b : deep_by_quadrant) if (!Xlist[b].empty()) tg.push_back(b);
     if (!tg.empty()) {
-      Stage st; init_stage(st, K_DOWN, "FARX", -1, kNE, kNP, kLeafDataTile, A_FAR, kNE);
-        st.accumulate = 1;
-      st.fam[0] = {A_INS, kNP, 0};
+      Stage st; init_stage(st, K_DOWN, "FARX", -1, kNE, lf ? kOutAll : kNP, kLeafDataTile, A_FAR, kNE);
+      st.accumulate = 1;
+      st.fam[0] = {int8_t(lf ? A_E : A_INS), lf ? kOutAll : kNP, 0};
       std::vector<std::vector<Entry>> E(tg.size());
       std::vector<std::vector<R1>> R(tg.size());
       par_for(int64_t(tg.size()), [&](int64_t i) {
-        for (auto& e : Xlist[tg[size_t(i)]]) E[size_t(i)].push_back({kRelS2L + e.first, 0, e.second});
+        for (auto& e : Xlist[tg[size_t(i)]]) E[size_t(i)].push_back({(lf ? kRelXE : kRelS2L) + e.first, 0, e.second});
       });
       defer(std::move(st), tg, std::move(E), std::move(R), false);
     }
@@ -1214,7 +1236,49 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
     std::vector<std::vector<R1>> R(tg.size());
     defer(std::move(st), tg, std::move(E), std::move(R), adj);
   };
-  if (lr) {
+  // Compressed form. Directions (edge 0..3, corner 4..7) of the near and W relations.
+  auto dir_near = [&](int r) { return near_dir(NO[size_t(r)].dx, NO[size_t(r)].dy, NO[size_t(r)].rho); };
+  auto dir_w = [&](int r) { return near_dir(WO[size_t(r)].dx, WO[size_t(r)].dy, WO[size_t(r)].rho); };
+  if (lf) {
+    P.pairs_lr = int64_t(Ulist.e.size()) - P.n_leaves;
+    if (P.n_leaves >= (int64_t(1) << 29)) throw std::runtime_error("too many leaves");  // 4 n fits 32 bits
+    // NEARC, NEARC48: the values each leaf receives across its edges (corners) from the outgoing
+    // values of the adjacent leaves and the multipoles of the W-list boxes there. A direction with
+    // nothing across it is no target: its row is zero from the plan's creation on.
+    for (int c = 0; c < 2; ++c) {
+      std::vector<int64_t> at(size_t(P.n_leaves) + 1, 0);
+      auto dirs = [&](int32_t a) {  // the leaf's directions (of this stage) that receive something
+        unsigned m = 0;
+        for (auto& e : Ulist[size_t(a)]) if (e.first != 0) m |= 1u << dir_near(e.first);
+        for (auto& e : Wlist[size_t(a)]) m |= 1u << dir_w(e.first);
+        return (c ? m >> 4 : m) & 15u;
+      };
+      par_for(P.n_leaves, [&](int64_t i) { at[size_t(i) + 1] = __builtin_popcount(dirs(leaf_order[size_t(i)])); });
+      for (int64_t i = 0; i < P.n_leaves; ++i) at[size_t(i) + 1] += at[size_t(i)];
+      std::vector<int32_t> tg(static_cast<size_t>(at[size_t(P.n_leaves)]));
+      if (tg.empty()) continue;
+      std::vector<std::vector<Entry>> E(tg.size());
+      std::vector<std::vector<R1>> R(tg.size());
+      par_for(P.n_leaves, [&](int64_t i) {
+        const int32_t a = leaf_order[size_t(i)];
+        const unsigned m = dirs(a);
+        auto slot = [&](int d) { return size_t(at[size_t(i)]) + size_t(__builtin_popcount(m & ((1u << d) - 1u))); };
+        for (int d = 0; d < 4; ++d)
+          if (m >> d & 1) tg[slot(d)] = 4 * a + d;
+        for (auto& e : Ulist[size_t(a)])
+          if (e.first != 0 && dir_near(e.first) / 4 == c) E[slot(dir_near(e.first) & 3)].push_back({kRelC + e.first - 1, 0, e.second});
+        for (auto& e : Wlist[size_t(a)])
+          if (dir_w(e.first) / 4 == c) E[slot(dir_w(e.first) & 3)].push_back({kRelCW + e.first, 1, e.second});
+      });
+      Stage st; init_stage(st, K_NEARC, c ? "NEARC48" : "NEARC", -1, c ? kCorner : kEdge, kOutAll, kLeafDataTile,
+                           c ? A_HC : A_HS, c ? kCorner : kEdge);
+      st.pre_near = 1;
+      st.fam[0] = {A_E, kOutAll, 0};
+      st.fam[1] = {A_MP, kNE, 0};
+      defer(std::move(st), tg, std::move(E), std::move(R), false);
+    }
+  }
+  if (lr && !lf) {
     lr_idx.assign(Ulist.e.size(), -1);
     int64_t n = 0;
     for (size_t g = 0; g < Ulist.e.size(); ++g)
@@ -1239,6 +1303,24 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
     for (auto& e : Wlist[size_t(a)]) { E.push_back({kRelM2T + e.first, f0, e.second}); R.push_back({0, e.second, kap}); }
     if (levels[a] >= 2) E.push_back({kRelL2T, int8_t(f0 + 1), P.leaf_box[a]});
   };
+  if (lf) {  // NEAR+LOCT: each leaf's potential from its own values, what it receives and its local
+    Stage st = leaf_stage(K_NEAR, "NEAR+LOCT", C_LOUT, kRelLO, mats.K[size_t(kRelLO)], 16);
+    st.after_far = 1;
+    std::vector<Entry> E;
+    std::vector<R1> R;
+    st.r1_ptr.push_back(0);
+    for (int32_t a = 0; a < P.n_leaves; ++a) {
+      E.clear();
+      R.clear();
+      loct_terms(a, E, R, 0);
+      for (const R1& r : R) { st.r1_idx.push_back(r.idx); st.r1_coef.push_back(r.coef); }
+      st.r1_ptr.push_back(int32_t(st.r1_idx.size()));
+      P.n_l2t += levels[a] >= 2;
+    }
+    st.flops += 2.0 * kNP * double(st.r1_idx.size());
+    defer(std::move(st), {}, {}, {}, false);
+    halves.clear();
+  }
   for (size_t h = 0; h < halves.size(); ++h) {  // NEAR: the adjacent-leaf tables
     const std::vector<int32_t> part(near_order.begin() + long(halves[h].first), near_order.begin() + long(halves[h].second));
     Stage st; init_stage(st, K_NEAR, halves.size() > 1 ? (h ? "NEAR_B" : "NEAR_A") : (fold ? "NEAR+LOCT" : "NEAR"), -1,
@@ -1307,7 +1389,9 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   {  // AL2T: lbar of leaves at level >= 2
     std::vector<int32_t> tg;
     for (int32_t b = 0; b < NB; ++b) if (P.box_leaf[b] >= 0 && P.box_level[b] >= 2) tg.push_back(b);
-    if (!tg.empty()) {
+    if (lf) {  // and the cotangents of what every leaf receives
+      defer(leaf_stage(K_AUP, "AL2T", C_LIN, kRelLI + kNumFwd, 64, 64), {}, {}, {}, true);
+    } else if (!tg.empty()) {
       Stage st; init_stage(st, K_AUP, "AL2T", -1, kNE, kNP, kLeafDataTile, A_LB, kNE);
         st.fam[0] = {A_IN, kNP, 0};
       std::vector<std::vector<Entry>> E(tg.size());
@@ -1360,13 +1444,22 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
     std::vector<int32_t> tg;
     for (int32_t b : afar_tg) if (!Winv[b].empty()) tg.push_back(b);
     if (!tg.empty()) {
-      Stage st; init_stage(st, K_ADOWN, "AFARW", -1, kNE, kNP, kLeafDataTile, A_AFAR, kNE);
-        st.accumulate = 1;
-      st.fam[0] = {A_IN, kNP, 0};
+      Stage st; init_stage(st, K_ADOWN, "AFARW", -1, kNE, lf ? kEdge : kNP, kLeafDataTile, A_AFAR, kNE);
+      st.accumulate = 1;
+      if (lf) {
+        st.fam[0] = {A_HSA, kEdge, 0};
+        st.fam[1] = {A_HCA, kCorner, 0};
+      } else {
+        st.fam[0] = {A_IN, kNP, 0};
+      }
       std::vector<std::vector<Entry>> E(tg.size());
       std::vector<std::vector<R1>> R(tg.size());
       par_for(int64_t(tg.size()), [&](int64_t i) {
-        for (auto& e : Winv[tg[size_t(i)]]) E[size_t(i)].push_back({kRelM2T + e.first + kNumFwd, 0, e.second});
+        for (auto& e : Winv[tg[size_t(i)]]) {
+          if (!lf) { E[size_t(i)].push_back({kRelM2T + e.first + kNumFwd, 0, e.second}); continue; }
+          const int d = dir_w(e.first);
+          E[size_t(i)].push_back({kRelCW + e.first + kNumFwd, int8_t(d / 4), 4 * e.second + (d & 3)});
+        }
       });
       defer(std::move(st), tg, std::move(E), std::move(R), true);
     }
@@ -1383,7 +1476,44 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
     E.push_back({kRelS2M + kNumFwd, f0, P.leaf_box[b]});
     for (auto& e : Xinv[size_t(b)]) E.push_back({kRelS2L + e.first + kNumFwd, int8_t(f0 + 1), e.second});
   };
-  if (lr)  // ANEARC: U_r^T ubar of the target of every pair, one stage per rank
+  if (lf) {
+    // ANEARC: cotangents of each leaf's outgoing values, from those of what the adjacent leaves
+    // receive across their edges and of the locals that its X boxes take; ANEARC48 adds the corners'
+    for (int c = 0; c < 2; ++c) {
+      std::vector<int32_t> tg;
+      for (int32_t b : leaf_order) {
+        bool any = c == 0;
+        if (c)
+          for (auto& e : Uinv[size_t(b)]) any = any || (e.first != 0 && dir_near(e.first) >= 4);
+        if (any) tg.push_back(b);
+      }
+      if (tg.empty()) continue;
+      std::vector<std::vector<Entry>> E(tg.size());
+      std::vector<std::vector<R1>> R(tg.size());
+      par_for(int64_t(tg.size()), [&](int64_t i) {
+        for (auto& e : Uinv[size_t(tg[size_t(i)])]) {
+          const int d = e.first ? dir_near(e.first) : -1;
+          if (d >= 0 && d / 4 == c) E[size_t(i)].push_back({kRelC + e.first - 1 + kNumFwd, 0, 4 * e.second + (d & 3)});
+        }
+        if (!c)
+          for (auto& e : Xinv[size_t(tg[size_t(i)])]) E[size_t(i)].push_back({kRelXE + e.first + kNumFwd, 1, e.second});
+      });
+      Stage st; init_stage(st, K_ANEARC, c ? "ANEARC48" : "ANEARC", -1, kOutAll, c ? kCorner : kEdge, kLeafDataTile, A_EA, kOutAll);
+      st.pre_near = 1;
+      st.accumulate = int8_t(c);
+      if (c) {
+        st.fam[0] = {A_HCA, kCorner, 0};
+      } else {
+        st.fam[0] = {A_HSA, kEdge, 0};
+        st.fam[1] = {A_LB, kNE, 0};
+      }
+      defer(std::move(st), tg, std::move(E), std::move(R), true);
+    }
+    Stage st = leaf_stage(K_ANEAR, "ANEAR+ALOCT", C_LOUT, kRelLO + kNumFwd, mats.K[size_t(kRelLO + kNumFwd)], 16);
+    st.after_far = 1;
+    defer(std::move(st), {}, {}, {}, true);
+  }
+  if (lr && !lf)  // ANEARC: U_r^T ubar of the target of every pair, one stage per rank
     for (int rank : {kNearRank, kNearRankLow})
       pair_stage(K_ANEARC, rank == kNearRank ? "ANEARC" : "ANEARC48", rank, A_NWA, true, [&](int64_t g, int64_t a) {
         return Entry{kRelNU + Ulist.e[size_t(g)].first - 1 + kNumFwd, 0, int32_t(a)};
@@ -1458,6 +1588,10 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   }
   arrange_stages(P.fwd, false);
   arrange_stages(P.adj, true);
+  if (lf)  // these read multipoles (locals' cotangents) of the upward chain
+    for (auto* v : {&P.fwd, &P.adj})
+      for (Stage& st : *v)
+        if (st.pre_near) { st.join_before = 1; break; }
   return VOLPOT_OK;
 }
 

@@ -81,7 +81,28 @@ constexpr int kRelNU = 156;   // +32: U_r
 constexpr int kRelNV = 188;   // +32: V_r
 constexpr int kRelNSF = 220;  // +4: forward self slices
 constexpr int kRelNSA = 224;  // +4: adjoint self slices
-constexpr int kNumFwd = 228;
+// Compressed leaf form: a leaf's outgoing values (28 per parity part), the values it
+// receives across each edge (kEdge: 48 even and 48 odd along the edge) and each corner (kCorner),
+// and the tables between them (tables.cpp, leaf_form).
+constexpr int kOut = 28;
+constexpr int kOutAll = 4 * kOut;
+constexpr int kEdge = 96;
+constexpr int kCorner = 48;
+constexpr int kRelC = 228;    // +32: near relation r (1..32) from outgoing to received values
+constexpr int kRelCW = 260;   // +20: W offset, from multipoles to received values
+constexpr int kRelXE = 280;   // +20: X offset, from outgoing values to locals
+// The leaf kernels' tables, parity part by part. kRelLI: values to outgoing values and multipoles
+// (48 rows per part: 28, then the part's reals); its adjoint id: cotangents to the received values'
+// and the local's cotangents (row tiles of 16, part fastest). kRelLO: columns of one part's
+// values (64), edges left / right and down / up (48 each), corners (48) and locals, to its values;
+// its adjoint id: columns cotangents (64), outgoing values' cotangents (28 of 32) and multipoles.
+constexpr int kRelLI = 300;
+constexpr int kRelLO = 301;
+constexpr int kLinRows = 4 * 48;
+constexpr int kLinGroups = (kEdge + kCorner) / 16;  // row tiles per part of the adjoint kRelLI, locals not counted
+constexpr int kLoutCols = 64 + kEdge + kCorner;
+constexpr int kLoutAdjCols = 64 + 32;
+constexpr int kNumFwd = 302;
 constexpr int kNumRel = 2 * kNumFwd;
 
 struct Offset { double dx, dy, rho; };
@@ -90,6 +111,10 @@ const std::vector<Offset>& v_offsets();     // 40, in half-widths (rho 1)
 const std::vector<Offset>& w_offsets();     // 20 (rho 1/2)
 const std::vector<Offset>& x_offsets();     // 20 (rho 2)
 int find_offset(const std::vector<Offset>& v, double dx, double dy, double rho);
+// Where a source box at (dx, dy) of half-width rho (target half-widths) lies from the reference
+// target: across its right, left, upper, lower edge (0..3) or its upper right, upper left, lower
+// right, lower left corner (4..7); -1 when it overlaps the target.
+int near_dir(double dx, double dy, double rho);
 
 // ---------------------------------------------------------------- matrices
 struct Matrices {
@@ -123,7 +148,11 @@ void set_table_cache_dir(const char* dir);
 // chains add the parents' contributions into A_LOC / A_AB
 // A_NW / A_NWA: per adjacent-leaf pair (other than a leaf with itself) the 64 values V_r f of the
 // low-rank near field, and U_r^T ubar of its transpose
-enum Arr : int8_t { A_IN = 0, A_INS, A_OUT, A_MP, A_LOC, A_LB, A_AB, A_USUM, A_FAR, A_AFAR, A_NW, A_NWA, A_NONE };
+// A_E: the compressed form's outgoing values of each leaf (kOutAll); A_HS / A_HC: what each leaf
+// receives across its four edges (4 x kEdge) and corners (4 x kCorner); A_EA, A_HSA, A_HCA: their
+// cotangents
+enum Arr : int8_t { A_IN = 0, A_INS, A_OUT, A_MP, A_LOC, A_LB, A_AB, A_USUM, A_FAR, A_AFAR, A_NW, A_NWA, A_E, A_HS, A_HC,
+                    A_EA, A_HSA, A_HCA, A_NONE };
 // timing / accounting kinds: 0 upward (S2M, M2M), 1 downward (FARV/X, L2L), 2 NEAR, 3 LOCT,
 // 4 adjoint upward (AL2T, AL2L), 5 adjoint downward (AFARV/W, AM2M), 6 ANEAR, 7 ALOCT,
 // 8 adjoint row sums, 9 NEARC (the low-rank near field's V_r f per pair), 10 ANEARC (U_r^T ubar)
@@ -132,9 +161,13 @@ enum StageKind : int { K_UP = 0, K_DOWN, K_NEAR, K_LOCT, K_AUP, K_ADOWN, K_ANEAR
 
 struct FamDesc { int8_t arr; int32_t stride; int8_t unused; };
 
-// Stages of the layer-potential evaluation that are not grouped products: per-point
-// expansions and direct sums over the curve's quadrature nodes (their own kernels).
-enum Custom : int8_t { C_NONE = 0, C_P2M, C_P2L, C_P2P };
+// Stages that are not grouped products, with their own kernels: the layer potentials' per-point
+// expansions and direct sums over the curve's quadrature nodes, and the leaf kernels of the
+// compressed near field.
+enum Custom : int8_t { C_NONE = 0, C_P2M, C_P2L, C_P2P, C_LIN, C_LOUT };
+constexpr int kLeafTile = 32;  // leaves per tile of the leaf kernels
+// Volume plans of at least this many leaves take the compressed near field.
+constexpr int64_t kLeafFormMin = 512;
 
 // One piece of a stage's work as run by one block: n_chunks consecutive k-chunks of one tile,
 // starting at chunk k0 / KC of segment seg. A tile cut over several blocks ("split") has its
@@ -174,7 +207,8 @@ struct Stage {
   int8_t join_before = 0;  // waits for the helper stream's work before launching
   int8_t fork_before = 0;  // the helper stream waits for the caller's stream before this stage
   int8_t concurrent = 0;   // runs while helper-stream stages may run: leaves compute units free
-  int8_t custom = C_NONE;  // not a grouped product: c_tgt / c_ptr / c_idx describe the work
+  int8_t custom = C_NONE;  // not a grouped product: c_tgt / c_ptr / c_idx (layer stages), table (leaf kernels)
+  int leaf_rel = -1;       // leaf kernels: relation id of the table
   std::string name;        // stage name for reports, e.g. NEAR or M2M[5]
   FamDesc fam[4];
   FamDesc r1fam[3];
@@ -214,7 +248,8 @@ struct Plan {
   // pair counts
   int64_t pairs_near = 0, pairs_v = 0, pairs_w = 0, pairs_x = 0, n_m2m = 0, n_l2l = 0, n_s2m = 0,
           n_l2t = 0;
-  int64_t pairs_lr = 0;  // adjacent-leaf pairs in low-rank form (rows of A_NW / A_NWA), 0 if dense
+  int64_t pairs_lr = 0;  // adjacent-leaf pairs in low-rank or compressed form, 0 if dense
+  bool leaf_form = false;  // compressed near field: A_E .. A_HCA in place of the pair rows A_NW / A_NWA
   bool adj_leaf_sums = false;  // the adjoint reads leaf sums of ubar (a leaf above level 2)
   // layer potentials (point sources on a curve; empty for the volume potential)
   bool layer = false;

@@ -605,6 +605,461 @@ static const NearFactors& near_factors() {
   return *F;
 }
 
+// ---------------------------------------------------------------- compressed leaf form
+// Tables of the compressed near field, in the parity basis of a leaf's 16 x 16 nodal values:
+// index p 64 + 8 j + i (j, i < 8), p = px + 2 py, holds half of v[j][i] +- v[j][15 - i] +-
+// v[15 - j][i] +- v[15 - j][15 - i], the signs of the mirrored values negative where the part is
+// odd in x (px) or y (py). The transform is orthonormal; it splits every table that commutes with
+// the two reflections (a leaf with itself, S2M, L2T, E and the target bases below) into one block
+// per part.
+static void to_parity(const double* v, int64_t stride, double* out) {
+  for (int j = 0; j < 8; ++j)
+    for (int i = 0; i < 8; ++i) {
+      const double a = v[stride * (16 * j + i)], b = v[stride * (16 * j + 15 - i)];
+      const double c = v[stride * (16 * (15 - j) + i)], d = v[stride * (16 * (15 - j) + 15 - i)];
+      const double ab = a + b, am = a - b, cd_ = c + d, cm = c - d;
+      out[8 * j + i] = 0.5 * (ab + cd_);
+      out[64 + 8 * j + i] = 0.5 * (am + cm);
+      out[128 + 8 * j + i] = 0.5 * (ab - cd_);
+      out[192 + 8 * j + i] = 0.5 * (am - cm);
+    }
+}
+// rows of A (m x 256), then columns of A (256 x n), to the parity basis
+static std::vector<double> parity_rows(const std::vector<double>& A, int m) {
+  std::vector<double> R(A.size());
+  for (int i = 0; i < m; ++i) to_parity(A.data() + size_t(i) * kNP, 1, R.data() + size_t(i) * kNP);
+  return R;
+}
+static std::vector<double> parity_cols(const std::vector<double>& A, int n) {
+  std::vector<double> R(A.size());
+  double col[kNP];
+  for (int c = 0; c < n; ++c) {
+    to_parity(A.data() + c, n, col);
+    for (int i = 0; i < kNP; ++i) R[size_t(i) * n + c] = col[i];
+  }
+  return R;
+}
+
+// E: the 28 outgoing values of each part of a leaf's data. The potential of polynomial data of
+// degree 15 outside the leaf vanishes exactly when the data is the Laplacian of a polynomial with
+// a double zero on the boundary, (1 - x^2)^2 (1 - y^2)^2 q with q of degree 11: 6 x 6 of each
+// part. E is an orthonormal basis of the complement of these (64 - 36 = 28), so every functional
+// of the leaf's exterior field (the tables to other leaves, S2M, S2L) is T E^T E without loss.
+// The 36 are evaluated and orthogonalised in extended precision: in double the second derivatives
+// would leave 3e-14 of the self table's norm.
+static void outgoing_basis(std::vector<double>& E) {  // 4 x 28 x 64
+  typedef long double ld;
+  const Basis& B = basis();
+  ld ph[12][8], p2[12][8];  // phi_a = (1 - x^2)^2 T_a(x) and its second derivative at the first 8 nodes
+  for (int i = 0; i < 8; ++i) {
+    const ld x = B.t[i];
+    ld T[12], T1[12], T2[12];
+    T[0] = 1; T1[0] = 0; T2[0] = 0;
+    T[1] = x; T1[1] = 1; T2[1] = 0;
+    for (int a = 2; a < 12; ++a) {
+      T[a] = 2 * x * T[a - 1] - T[a - 2];
+      T1[a] = 2 * T[a - 1] + 2 * x * T1[a - 1] - T1[a - 2];
+      T2[a] = 4 * T1[a - 1] + 2 * x * T2[a - 1] - T2[a - 2];
+    }
+    const ld g = (1 - x * x) * (1 - x * x), g1 = -4 * x * (1 - x * x), g2 = 12 * x * x - 4;
+    for (int a = 0; a < 12; ++a) {
+      ph[a][i] = g * T[a];
+      p2[a][i] = g2 * T[a] + 2 * g1 * T1[a] + g * T2[a];
+    }
+  }
+  E.assign(size_t(4) * kOut * 64, 0.0);
+  for (int p = 0; p < 4; ++p) {
+    // Gram-Schmidt, each vector twice: the 36 first, then the unit vectors, largest remainder first
+    std::vector<std::vector<ld>> q;
+    auto residual = [&](std::vector<ld>& v) {
+      for (int twice = 0; twice < 2; ++twice)
+        for (auto& u : q) {
+          ld d = 0;
+          for (int k = 0; k < 64; ++k) d += u[size_t(k)] * v[size_t(k)];
+          for (int k = 0; k < 64; ++k) v[size_t(k)] -= d * u[size_t(k)];
+        }
+      ld n = 0;
+      for (ld x : v) n += x * x;
+      return std::sqrt(n);
+    };
+    auto push = [&](std::vector<ld> v, ld n) {
+      for (ld& x : v) x /= n;
+      q.push_back(std::move(v));
+    };
+    for (int b = p >> 1; b < 12; b += 2)
+      for (int a = p & 1; a < 12; a += 2) {
+        std::vector<ld> v(64);
+        ld n0 = 0;
+        for (int j = 0; j < 8; ++j)
+          for (int i = 0; i < 8; ++i) {
+            v[size_t(8 * j + i)] = p2[a][i] * ph[b][j] + ph[a][i] * p2[b][j];
+            n0 += v[size_t(8 * j + i)] * v[size_t(8 * j + i)];
+          }
+        for (ld& x : v) x /= std::sqrt(n0);
+        const ld n = residual(v);
+        push(v, n);
+      }
+    for (int r = 0; r < kOut; ++r) {
+      ld best = -1;
+      std::vector<ld> bv;
+      for (int k = 0; k < 64; ++k) {
+        std::vector<ld> v(64, 0);
+        v[size_t(k)] = 1;
+        const ld n = residual(v);
+        if (n > best) { best = n; bv = v; }
+      }
+      push(bv, best);
+      for (int k = 0; k < 64; ++k) E[(size_t(p) * kOut + r) * 64 + k] = double(q.back()[size_t(k)]);
+    }
+  }
+}
+
+// A (m x 256, parity basis) times E^T: m x 112, columns 28 p + r
+static std::vector<double> times_et(const std::vector<double>& A, int m, const std::vector<double>& E) {
+  std::vector<double> R(size_t(m) * kOutAll);
+  for (int i = 0; i < m; ++i)
+    for (int p = 0; p < 4; ++p)
+      for (int r = 0; r < kOut; ++r) {
+        double s = 0.0;
+        for (int k = 0; k < 64; ++k) s += A[size_t(i) * kNP + 64 * p + k] * E[(size_t(p) * kOut + r) * 64 + k];
+        R[size_t(i) * kOutAll + kOut * p + r] = s;
+      }
+  return R;
+}
+
+// Orthonormal basis (m x k) of the k leading left singular vectors of A (m x n, columns), by
+// pivoted Gram-Schmidt on the columns to 64 vectors and one-sided Jacobi on what it leaves.
+static std::vector<double> leading_basis(const std::vector<std::vector<double>>& cols, int m, int k) {
+  const int n = int(cols.size()), kq = std::min(64, m);
+  std::vector<std::vector<double>> res(cols), Q, R;
+  double b0 = 0.0;
+  for (int r = 0; r < kq; ++r) {
+    int best = -1;
+    double bn = -1.0;
+    for (int c = 0; c < n; ++c) {
+      double s = 0.0;
+      for (double x : res[size_t(c)]) s += x * x;
+      if (s > bn) { bn = s; best = c; }
+    }
+    if (r == 0) b0 = bn;
+    if (!(bn > 1e-32 * b0)) break;  // nothing but rounding is left
+    std::vector<double> v(res[size_t(best)]);
+    for (int pass = 0; pass < 3; ++pass) {  // against the earlier vectors again, and to unit length
+      if (pass > 0)
+        for (auto& u : Q) {
+          double d = 0.0;
+          for (int i = 0; i < m; ++i) d += u[size_t(i)] * v[size_t(i)];
+          for (int i = 0; i < m; ++i) v[size_t(i)] -= d * u[size_t(i)];
+        }
+      double nv = 0.0;
+      for (double x : v) nv += x * x;
+      nv = std::sqrt(nv);
+      for (double& x : v) x /= nv;
+    }
+    // this vector's row of Q^T A, from what the earlier ones left of the columns: its small entries
+    // keep their digits
+    R.emplace_back(size_t(n), 0.0);
+    for (int c = 0; c < n; ++c) {
+      auto& w = res[size_t(c)];
+      double d = 0.0;
+      for (int i = 0; i < m; ++i) d += v[size_t(i)] * w[size_t(i)];
+      for (int i = 0; i < m; ++i) w[size_t(i)] -= d * v[size_t(i)];
+      R.back()[size_t(c)] = d;
+    }
+    Q.push_back(std::move(v));
+  }
+  const int q = int(Q.size());
+  // Jacobi rotations of R's rows, the same rotations of Q's vectors
+  for (int sweep = 0; sweep < 30; ++sweep) {
+    double worst = 0.0;
+    for (int a = 0; a + 1 < q; ++a)
+      for (int b = a + 1; b < q; ++b) {
+        double aa = 0, bb = 0, ab = 0;
+        for (int c = 0; c < n; ++c) {
+          aa += R[size_t(a)][size_t(c)] * R[size_t(a)][size_t(c)];
+          bb += R[size_t(b)][size_t(c)] * R[size_t(b)][size_t(c)];
+          ab += R[size_t(a)][size_t(c)] * R[size_t(b)][size_t(c)];
+        }
+        if (ab == 0.0) continue;
+        worst = std::max(worst, std::fabs(ab) / std::sqrt(aa * bb));
+        const double th = (bb - aa) / (2.0 * ab);
+        const double t = (th >= 0.0 ? 1.0 : -1.0) / (std::fabs(th) + std::sqrt(1.0 + th * th));
+        const double cs = 1.0 / std::sqrt(1.0 + t * t), sn = t * cs;
+        auto rot = [&](std::vector<double>& x, std::vector<double>& y) {
+          for (size_t c = 0; c < x.size(); ++c) {
+            const double u = x[c], w = y[c];
+            x[c] = cs * u - sn * w;
+            y[c] = sn * u + cs * w;
+          }
+        };
+        rot(R[size_t(a)], R[size_t(b)]);
+        rot(Q[size_t(a)], Q[size_t(b)]);
+      }
+    if (worst < 1e-13) break;
+  }
+  std::vector<std::pair<double, int>> ord;
+  for (int a = 0; a < q; ++a) {
+    double s = 0.0;
+    for (double x : R[size_t(a)]) s += x * x;
+    ord.push_back({-s, a});
+  }
+  std::sort(ord.begin(), ord.end());
+  // the rotations leave the vectors orthonormal to about 1e-14 only: Gram-Schmidt, each twice, in
+  // extended precision
+  std::vector<double> U(size_t(m) * k, 0.0);
+  std::vector<std::vector<long double>> X;
+  for (int c = 0; c < std::min(k, q); ++c) {
+    const auto& src = Q[size_t(ord[size_t(c)].second)];
+    std::vector<long double> v(src.begin(), src.end());
+    for (int pass = 0; pass < 2; ++pass)
+      for (auto& u : X) {
+        long double d = 0;
+        for (int i = 0; i < m; ++i) d += u[size_t(i)] * v[size_t(i)];
+        for (int i = 0; i < m; ++i) v[size_t(i)] -= d * u[size_t(i)];
+      }
+    long double nv = 0;
+    for (long double x : v) nv += x * x;
+    nv = std::sqrt(nv);
+    for (long double& x : v) x /= nv;
+    for (int i = 0; i < m; ++i) U[size_t(i) * k + c] = double(v[size_t(i)]);
+    X.push_back(std::move(v));
+  }
+  return U;
+}
+
+// M2T of W offset r for Q complex terms, 256 x 2Q
+static std::vector<double> m2t_table(int r, int Q) {
+  const Basis& B = basis();
+  const Offset& o = w_offsets()[size_t(r)];
+  const cd d(o.dx, o.dy);
+  std::vector<cd> Mt(size_t(kNP) * Q);
+  for (int m = 0; m < kNP; ++m) {
+    const cd z = cd(B.t[m % kP], B.t[m / kP]) - d;
+    Mt[size_t(m) * Q] = -kInv2Pi * std::log(std::abs(z));
+    for (int k = 1; k < Q; ++k) Mt[size_t(m) * Q + k] = -kInv2Pi * std::pow(o.rho, k) * std::pow(z, -k);
+  }
+  std::vector<double> R;
+  real_from_realout(Mt, kNP, Q, R);
+  return R;
+}
+// S2M for Q complex terms (c_n int l_k eta^n, c_0 = 1, c_n = -1/n), 2Q x 256
+static std::vector<double> s2m_table(int Q) {
+  auto S = quad_basis(40, Q, [](int n, cd e) { return n == 0 ? cd(1.0) : -std::pow(e, n) / double(n); });
+  std::vector<double> R;
+  real_from_realin(S, Q, kNP, R);
+  return R;
+}
+
+int near_dir(double dx, double dy, double rho) {
+  // the edge of the reference target that the source touches or faces: its near face lies at or
+  // beyond that edge
+  const int x = dx - rho >= 1.0 - 1e-9 ? 1 : dx + rho <= -1.0 + 1e-9 ? -1 : 0;
+  const int y = dy - rho >= 1.0 - 1e-9 ? 1 : dy + rho <= -1.0 + 1e-9 ? -1 : 0;
+  if (x && y) return 4 + (x < 0) + 2 * (y < 0);
+  if (x) return x > 0 ? 0 : 1;
+  if (y) return y > 0 ? 2 : 3;
+  return -1;
+}
+
+// The bases of what a leaf receives through each of its four edges and four corners, and the
+// tables of the 32 adjacent relations between them and E.
+//   H_E (256 x 96): the potentials in the leaf of everything across its right edge: the same-size
+//   neighbour, the finer and the coarser ones, and the W-list boxes beyond. 48 vectors even in y
+//   (on the parts py = 0) and 48 odd ones. The other edges are its images: W mirrors x (the sign
+//   of the parts px = 1), N swaps x and y, S mirrors N.
+//   H_NE (256 x 48): the same across the upper right corner; NW, SE, SW mirror it.
+// For data of magnitude one the part of the result outside its basis is at most 3e-15 with 48
+// vectors, the size of the tables' own quadrature error (4e-14 with 44, 1e-12 with 40).
+struct LeafForm {
+  std::vector<double> E;               // 4 x 28 x 64
+  std::vector<double> H[8];            // E, W, N, S (256 x 96), NE, NW, SE, SW (256 x 48)
+  std::vector<std::vector<double>> C;  // near relations 1..32: H_d^T T_r E^T
+};
+// H^T A for A 256 x n
+static std::vector<double> ht_times(const std::vector<double>& H, int k, const std::vector<double>& A, int n) {
+  std::vector<double> R(size_t(k) * n, 0.0);
+  for (int i = 0; i < kNP; ++i)
+    for (int c = 0; c < k; ++c) {
+      const double h = H[size_t(i) * k + c];
+      if (h == 0.0) continue;
+      for (int j = 0; j < n; ++j) R[size_t(c) * n + j] += h * A[size_t(i) * n + j];
+    }
+  return R;
+}
+static const LeafForm& leaf_form() {
+  static std::once_flag once;
+  static LeafForm* F = nullptr;
+  std::call_once(once, []() {
+    auto* f = new LeafForm();
+    outgoing_basis(f->E);
+    const auto& T = near_tables();
+    const auto& NO = near_offsets();
+    const auto& WO = w_offsets();
+    std::vector<std::vector<double>> TE(33);  // parity basis, times E^T: 256 x 112
+    {
+      std::vector<std::thread> th;
+      for (int r = 1; r <= 32; ++r)
+        th.emplace_back([&, r]() { TE[size_t(r)] = times_et(parity_rows(parity_cols(T[size_t(r)], kNP), kNP), kNP, f->E); });
+      for (auto& t : th) t.join();
+    }
+    // a W-list box's field is what the multipoles of a leaf there make of its outgoing values
+    const std::vector<double> SE = times_et(parity_rows(s2m_table(kTerms), kNE), kNE, f->E);
+    // outgoing values of the 256 products T_a(x) T_b(y) of Chebyshev polynomials: the data that the
+    // bases are fitted to (constants and low degrees as closely as the rest; fitted to unit vectors
+    // of the outgoing values instead, 48 vectors would leave 1e-13 of a constant)
+    std::vector<double> cheb(size_t(kNP) * kNP), D(size_t(kOutAll) * kNP, 0.0);
+    const Basis& B = basis();
+    for (int b = 0; b < kP; ++b)
+      for (int a = 0; a < kP; ++a)
+        for (int j = 0; j < kP; ++j)
+          for (int i = 0; i < kP; ++i)
+            cheb[size_t(b * kP + a) * kNP + j * kP + i] = std::cos(a * std::acos(B.t[i])) * std::cos(b * std::acos(B.t[j]));
+    {
+      const std::vector<double> ce = times_et(parity_rows(cheb, kNP), kNP, f->E);  // 256 polynomials x 112
+      for (int f2 = 0; f2 < kNP; ++f2)
+        for (int c = 0; c < kOutAll; ++c) D[size_t(c) * kNP + f2] = ce[size_t(f2) * kOutAll + c];
+    }
+    std::vector<std::vector<double>> even, odd, corner;
+    auto take = [&](const std::vector<double>& A, int dir) {  // columns of A (256 x 112) times D
+      std::vector<double> AD(size_t(kNP) * kNP, 0.0);
+      for (int i = 0; i < kNP; ++i)
+        for (int c = 0; c < kOutAll; ++c)
+          for (int k = 0; k < kNP; ++k) AD[size_t(i) * kNP + k] += A[size_t(i) * kOutAll + c] * D[size_t(c) * kNP + k];
+      for (int c = 0; c < kNP; ++c) {
+        std::vector<double> v(kNP);
+        for (int i = 0; i < kNP; ++i) v[size_t(i)] = AD[size_t(i) * kNP + c];
+        if (dir == 4) {
+          corner.push_back(v);
+        } else {
+          even.emplace_back(v.begin(), v.begin() + 128);
+          odd.emplace_back(v.begin() + 128, v.end());
+        }
+      }
+    };
+    for (int r = 1; r <= 32; ++r) {
+      const int d = near_dir(NO[size_t(r)].dx, NO[size_t(r)].dy, NO[size_t(r)].rho);
+      if (d == 0 || d == 4) take(TE[size_t(r)], d);
+    }
+    for (size_t r = 0; r < WO.size(); ++r) {
+      const int d = near_dir(WO[r].dx, WO[r].dy, WO[r].rho);
+      if (d != 0 && d != 4) continue;
+      const std::vector<double> M = parity_cols(m2t_table(int(r), kTerms), kNE);
+      std::vector<double> A(size_t(kNP) * kOutAll, 0.0);
+      for (int i = 0; i < kNP; ++i)
+        for (int k = 0; k < kNE; ++k)
+          for (int c = 0; c < kOutAll; ++c) A[size_t(i) * kOutAll + c] += M[size_t(i) * kNE + k] * SE[size_t(k) * kOutAll + c];
+      take(A, d);
+    }
+    std::vector<double> He, Ho, Hc;
+    {
+      std::thread a([&]() { He = leading_basis(even, 128, kEdge / 2); });
+      std::thread b([&]() { Ho = leading_basis(odd, 128, kEdge / 2); });
+      Hc = leading_basis(corner, kNP, kCorner);
+      a.join();
+      b.join();
+    }
+    f->H[0].assign(size_t(kNP) * kEdge, 0.0);
+    for (int i = 0; i < 128; ++i)
+      for (int c = 0; c < kEdge / 2; ++c) {
+        f->H[0][size_t(i) * kEdge + c] = He[size_t(i) * (kEdge / 2) + c];
+        f->H[0][size_t(128 + i) * kEdge + kEdge / 2 + c] = Ho[size_t(i) * (kEdge / 2) + c];
+      }
+    f->H[2].assign(size_t(kNP) * kEdge, 0.0);
+    for (int p = 0; p < 4; ++p)
+      for (int j = 0; j < 8; ++j)
+        for (int i = 0; i < 8; ++i) {
+          const int pt = (p >> 1) + 2 * (p & 1);
+          for (int c = 0; c < kEdge; ++c)
+            f->H[2][size_t(64 * p + 8 * j + i) * kEdge + c] = f->H[0][size_t(64 * pt + 8 * i + j) * kEdge + c];
+        }
+    f->H[4] = Hc;
+    auto mirror = [&](const std::vector<double>& H, int k, int parts) {  // negative on the parts with a bit of `parts` odd
+      std::vector<double> R(H);
+      for (int p = 0; p < 4; ++p)
+        if (__builtin_popcount(unsigned(p & parts)) & 1)
+          for (int i = 0; i < 64 * k; ++i) R[size_t(p) * 64 * k + i] = -R[size_t(p) * 64 * k + i];
+      return R;
+    };
+    f->H[1] = mirror(f->H[0], kEdge, 1);
+    f->H[3] = mirror(f->H[2], kEdge, 2);
+    f->H[5] = mirror(f->H[4], kCorner, 1);
+    f->H[6] = mirror(f->H[4], kCorner, 2);
+    f->H[7] = mirror(f->H[4], kCorner, 3);
+    f->C.resize(33);
+    std::vector<std::thread> th;
+    for (int r = 1; r <= 32; ++r)
+      th.emplace_back([&, r]() {
+        const int d = near_dir(NO[size_t(r)].dx, NO[size_t(r)].dy, NO[size_t(r)].rho);
+        f->C[size_t(r)] = ht_times(f->H[d], d < 4 ? kEdge : kCorner, TE[size_t(r)], kOutAll);
+      });
+    for (auto& t : th) t.join();
+    F = f;
+  });
+  return *F;
+}
+
+// The relation tables of the compressed form for expansions of Q complex terms.
+static void leaf_form_tables(Matrices& M, int Q) {
+  const LeafForm& F = leaf_form();
+  const int ne = 2 * Q, qh = Q / 2, qp = pad16(qh);
+  auto set = [&](int id, int rows, int cols, std::vector<double>&& a) {
+    M.M[id] = rows; M.K[id] = cols; M.a[id] = std::move(a);
+  };
+  for (int r = 1; r <= 32; ++r) {
+    const Offset& o = near_offsets()[size_t(r)];
+    set(kRelC + r - 1, near_dir(o.dx, o.dy, o.rho) < 4 ? kEdge : kCorner, kOutAll, std::vector<double>(F.C[size_t(r)]));
+  }
+  for (int r = 0; r < 20; ++r) {
+    const Offset& w = w_offsets()[size_t(r)];
+    const int d = near_dir(w.dx, w.dy, w.rho), k = d < 4 ? kEdge : kCorner;
+    set(kRelCW + r, k, ne, ht_times(F.H[d], k, parity_cols(M.a[kRelM2T + r], ne), ne));
+    set(kRelXE + r, ne, kOutAll, times_et(parity_rows(M.a[kRelS2L + r], ne), ne, F.E));
+  }
+  // real i of part p in an expansion of interleaved reals: the series' terms z^n have Re even in y
+  // and Im odd in y, their parity in x that of n (Re) or n - 1 (Im)
+  auto real_of = [](int p, int i) { return 4 * i + (p == 0 ? 0 : p == 1 ? 2 : p == 2 ? 3 : 1); };
+  const std::vector<double> S = parity_rows(M.a[kRelS2M], ne), L = parity_cols(M.a[kRelL2T], ne);
+  const std::vector<double> T0 = parity_rows(parity_cols(M.a[kRelNear], kNP), kNP);
+  const int groups = kLinGroups + qp / 16;
+  std::vector<double> li(size_t(kLinRows) * 64, 0.0), lia(size_t(groups) * 64 * 64, 0.0);
+  std::vector<double> lo(size_t(kNP) * (kLoutCols + qp), 0.0), loa(size_t(kNP) * (kLoutAdjCols + qp), 0.0);
+  // the kernels' parity sums leave out the factor 1/2, on the way in and on the way out: the
+  // tables carry it
+  for (int p = 0; p < 4; ++p) {
+    for (int k = 0; k < 64; ++k) {
+      for (int r = 0; r < kOut; ++r) li[size_t(48 * p + r) * 64 + k] = 0.5 * F.E[(size_t(p) * kOut + r) * 64 + k];
+      for (int i = 0; i < qh; ++i) li[size_t(48 * p + kOut + i) * 64 + k] = 0.5 * S[size_t(real_of(p, i)) * kNP + 64 * p + k];
+    }
+    const int py = p >> 1, px = p & 1, h = kEdge / 2;
+    for (int k = 0; k < 64; ++k) {  // node k of part p
+      const size_t row = size_t(64 * p + k);
+      double* o = lo.data() + row * (kLoutCols + qp);
+      double* a = loa.data() + row * (kLoutAdjCols + qp);
+      for (int c = 0; c < 64; ++c) {
+        o[c] = 0.25 * T0[row * kNP + 64 * p + c];
+        a[c] = 0.25 * T0[size_t(64 * p + c) * kNP + row];
+      }
+      for (int c = 0; c < h; ++c) {
+        o[64 + c] = 0.5 * F.H[0][row * kEdge + h * py + c];
+        o[64 + h + c] = 0.5 * F.H[2][row * kEdge + h * px + c];
+      }
+      for (int c = 0; c < kCorner; ++c) o[64 + kEdge + c] = 0.5 * F.H[4][row * kCorner + c];
+      for (int i = 0; i < qh; ++i) o[kLoutCols + i] = 0.5 * L[row * ne + real_of(p, i)];
+      for (int r = 0; r < kOut; ++r) a[64 + r] = 0.5 * F.E[(size_t(p) * kOut + r) * 64 + k];
+      for (int i = 0; i < qh; ++i) a[kLoutAdjCols + i] = 0.5 * S[size_t(real_of(p, i)) * kNP + row];
+      // the transpose of the incoming columns: row tile (4 g + p) holds rows 16 g .. of part p
+      for (int c = 64; c < kLoutCols + qp; ++c) {
+        const int g = (c - 64) / 16;
+        lia[size_t((4 * g + p) * 16 + (c - 64) % 16) * 64 + k] = o[c];
+      }
+    }
+  }
+  set(kRelLI, kLinRows, 64, std::move(li));
+  set(kRelLO, kNP, kLoutCols + qp, std::move(lo));
+  set(kRelLI + kNumFwd, groups * 64, 64, std::move(lia));
+  set(kRelLO + kNumFwd, kNP, kLoutAdjCols + qp, std::move(loa));
+}
+
 static Matrices build_matrices(const int Q) {
   const int kNE = 2 * Q;  // reals per expansion for this order
   Matrices M;
@@ -623,12 +1078,7 @@ static Matrices build_matrices(const int Q) {
     M.M[id] = rows; M.K[id] = cols; M.a[id] = std::move(a);
   };
   // S2M: c_n int l_k eta^n, c_0 = 1, c_n = -1/n
-  {
-    auto S = quad_basis(40, Q, [](int n, cd e) { return n == 0 ? cd(1.0) : -std::pow(e, n) / double(n); });
-    std::vector<double> R;
-    real_from_realin(S, Q, kNP, R);
-    set(kRelS2M, kNE, kNP, std::move(R));
-  }
+  set(kRelS2M, kNE, kNP, s2m_table(Q));
   // M2M_q and L2L_q
   for (int q = 0; q < 4; ++q) {
     cd z0((q & 1) ? 0.5 : -0.5, (q & 2) ? 0.5 : -0.5);
@@ -743,20 +1193,7 @@ static Matrices build_matrices(const int Q) {
     }
   }
   // M2T_r: source box (rho = 1/2) at d = (source - target centre) / s_target
-  const auto& WO = w_offsets();
-  for (size_t r = 0; r < WO.size(); ++r) {
-    cd d(WO[r].dx, WO[r].dy);
-    double rho = WO[r].rho;
-    std::vector<cd> Mt(size_t(kNP) * Q);
-    for (int m = 0; m < kNP; ++m) {
-      cd z = xi[m] - d;
-      Mt[size_t(m) * Q] = -kInv2Pi * std::log(std::abs(z));
-      for (int k = 1; k < Q; ++k) Mt[size_t(m) * Q + k] = -kInv2Pi * std::pow(rho, k) * std::pow(z, -k);
-    }
-    std::vector<double> R;
-    real_from_realout(Mt, kNP, Q, R);
-    set(kRelM2T + int(r), kNP, kNE, std::move(R));
-  }
+  for (int r = 0; r < int(w_offsets().size()); ++r) set(kRelM2T + r, kNP, kNE, m2t_table(r, Q));
   // L2T
   {
     std::vector<cd> Lt(size_t(kNP) * Q);
@@ -766,8 +1203,10 @@ static Matrices build_matrices(const int Q) {
     real_from_realout(Lt, kNP, Q, R);
     set(kRelL2T, kNP, kNE, std::move(R));
   }
-  // transposes
+  leaf_form_tables(M, Q);
+  // transposes (the leaf kernels' adjoint tables have their own layout and are set already)
   for (int id = 0; id < kNumFwd; ++id) {
+    if (id == kRelLI || id == kRelLO) continue;
     int r = M.M[id], c = M.K[id];
     std::vector<double> T(size_t(r) * c);
     for (int i = 0; i < r; ++i)
