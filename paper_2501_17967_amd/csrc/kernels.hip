@@ -365,6 +365,8 @@ __device__ __forceinline__ void tile_epilogue(const GrgParams& p, const EpiIdx<N
 template <int MT, int NTT, int WM, int WN, int KC, bool CX>
 constexpr int min_blocks() {
   if (!CX && WM == 1 && WN == 4 && NTT == 1 && MT <= 4) return 4;
+  if (!CX && WM == 1 && WN == 4 && NTT == 1 && KC == 16) return 3;
+  if (!CX && MT == 3 && NTT == 2 && WM == 2 && WN == 2) return 4;
   if (CX && NTT == 4) return 3;
   return (!CX && MT == 4 && NTT == 2 && WM == 4 && WN == 1) ? (KC == 32 ? 2 : KC == 16 ? 3 : 1) : 1;
 }
@@ -550,7 +552,7 @@ __global__ void rowsum_kernel(const double* __restrict__ x, double* __restrict__
 #define VP_CONFIGS(X)                                                                            \
   X(256, 32, 32, 4, 2, 4, 1, 256) X(256, 64, 32, 4, 2, 4, 2, 512) X(256, 16, 16, 4, 1, 4, 1, 256) \
   X(256, 32, 16, 4, 2, 4, 1, 256) X(256, 64, 16, 4, 2, 4, 2, 512)                                 \
-  X(112, 64, 16, 7, 1, 1, 4, 256) X(96, 64, 16, 6, 1, 1, 4, 256) X(80, 64, 16, 5, 1, 1, 4, 256)   \
+  X(112, 64, 16, 7, 1, 1, 4, 256) X(96, 64, 16, 3, 2, 2, 2, 256) X(80, 64, 16, 5, 1, 1, 4, 256)   \
   X(80, 64, 40, 5, 1, 1, 4, 256) X(80, 32, 40, 5, 1, 1, 2, 128) X(80, 16, 40, 5, 1, 1, 1, 64)     \
   X(80, 64, 32, 5, 1, 1, 4, 256) X(80, 32, 32, 5, 1, 1, 2, 128) X(80, 16, 32, 5, 1, 1, 1, 64)     \
   X(64, 64, 16, 4, 1, 1, 4, 256) X(64, 32, 16, 4, 1, 1, 2, 128) X(64, 16, 16, 4, 1, 1, 1, 64)     \
