@@ -7,6 +7,17 @@
 
 namespace vp {
 
+#ifdef __HIPCC__
+// A 16 x 16 x 4 FP64 product of a table fragment (row l % 16, column l / 16 in lane l) and a source
+// fragment (slot l % 16, value l / 16). The sources are the instruction's first operand, so that
+// accumulator r of lane l is row l % 16 of slot 4 r + l / 16: 16 lanes hold 16 consecutive rows of
+// one slot, and every store writes whole 128-byte lines of four outputs.
+typedef double mfma_d4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ mfma_d4 mfma_16x16x4(double table, double source, mfma_d4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(source, table, c, 0, 0, 0);
+}
+#endif
+
 // Work of one block: n_chunks k-chunks of one tile (mirrors the host plan's Piece)
 struct PieceDesc {
   int32_t tile, seg, k0, n_chunks, slot, slot0, n_pieces, pad;

@@ -13,16 +13,13 @@
 //
 // Each output vector has exactly one owner and a fixed relation order: no atomics, bitwise
 // deterministic, identical whether a tree is applied alone or inside a forest.
-//
-// MFMA f64 16x16x4 operand layout (lane l, checked on gfx950):
-//   A: A[l % 16][l / 16]   B: B[l / 16][l % 16]   D (4 regs r): D[4 r + l / 16][l % 16]
 #include <hip/hip_runtime.h>
 
 #include "device.hpp"
 
 namespace vp {
 
-typedef double d4 __attribute__((ext_vector_type(4)));
+typedef mfma_d4 d4;
 typedef double d2 __attribute__((ext_vector_type(2)));  // native vector: keeps staging arrays in registers
 
 // Blocks are dispatched round-robin over the 8 XCDs; give each XCD a contiguous range of
@@ -194,21 +191,6 @@ struct LoaderCX {
   }
 };
 
-// One k-step (4 values of k) of the tile product for one wave: MT x NTT MFMA fragments.
-template <int MT, int NTT, int M, int LDB>
-__device__ __forceinline__ void mfma_step(const double* __restrict__ Aw, const double* __restrict__ Bw, int kk,
-                                          d4 (&acc)[MT][NTT]) {
-  double a[MT], b[NTT];
-#pragma unroll
-  for (int i = 0; i < MT; ++i) a[i] = Aw[(kk * (M / 16) + i) * 64];
-#pragma unroll
-  for (int j = 0; j < NTT; ++j) b[j] = Bw[j * 16 * LDB + kk * 4];
-#pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int j = 0; j < NTT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-}
-
 // One k-chunk of the tile product for one wave, with the operands of k-step kk + 1 read from
 // LDS before the products of step kk issue, so that the LDS latency hides behind them. The
 // scheduling barriers keep that order (left to itself, the compiler sinks the reads below the
@@ -236,7 +218,7 @@ __device__ __forceinline__ void mfma_chunk(const double* __restrict__ Aw, const 
     for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int j = 0; j < NTT; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[cur][i], b[cur][j], acc[i][j], 0, 0, 0);
+        acc[i][j] = mfma_16x16x4(a[cur][i], b[cur][j], acc[i][j]);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -251,31 +233,32 @@ __device__ __forceinline__ void mfma_chunk(const double* __restrict__ Aw, const 
 // (c / 32) 16 + c % 16 (the inverse of cx_col).
 __device__ __forceinline__ int cx_slot(int col) { return (col >> 5) * 16 + (col & 15); }
 
-template <int NTT, int NT, int NTHR, bool CX>
+template <int NT, int NTHR>
 struct EpiIdx {
-  int tgt[NTT];
-  double sc[NTT];
+  int tgt;    // of slot tid (tid < NT)
+  double sc;
   int e0, e1;
-  __device__ __forceinline__ void load(const GrgParams& p, int tile, int tid, int lane, int wn) {
-#pragma unroll
-    for (int j = 0; j < NTT; ++j) {
-      const int col = (wn * NTT + j) * 16 + (lane & 15);
-      tgt[j] = p.tile_tgt[tile * NT + (CX ? cx_slot(col) : col)];
-    }
+  __device__ __forceinline__ void load(const GrgParams& p, int tile, int tid) {
+    tgt = tid < NT ? p.tile_tgt[tile * NT + tid] : -1;
     const int ti = tile * NT + tid / (NTHR / NT);
     e0 = p.r1_ptr[ti];
     e1 = p.r1_ptr[ti + 1];
-#pragma unroll
-    for (int j = 0; j < NTT; ++j) sc[j] = (p.out_scaled && tgt[j] >= 0) ? p.leaf_s2[tgt[j]] : 1.0;
+    sc = (p.out_scaled && tgt >= 0) ? p.leaf_s2[tgt] : 1.0;
   }
+};
+// What the output needs of each slot, in LDS: its target, scale and rank-one sum.
+template <int NT>
+struct SlotInfo {
+  double r1[NT], sc[NT];
+  int tgt[NT];
 };
 
 // Factored stages (CX) have NT slots in 2 NT columns and write only the QV complex rows of
-// the padded core: reals 2 l and 2 l + 1 of each slot's expansion.
+// the padded core: reals 2 l and 2 l + 1 of each slot's expansion, from the two fragments that
+// hold the parts of the same slots.
 template <int MT, int NTT, int WM, int NT, int NTHR, bool CX, int QV>
-__device__ __forceinline__ void tile_epilogue(const GrgParams& p, const EpiIdx<NTT, NT, NTHR, CX>& ix,
-                                              const d4 (&acc)[MT][NTT], double* r1s, double* r1p, int tid, int lane,
-                                              int wm, int wn) {
+__device__ __forceinline__ void tile_epilogue(const GrgParams& p, const EpiIdx<NT, NTHR>& ix, const d4 (&acc)[MT][NTT],
+                                              SlotInfo<NT>& si, double* r1p, int tid, int lane, int wm, int wn) {
   constexpr int TPS = NTHR / NT;
   static_assert(TPS >= 1 && NTHR % NT == 0, "threads per slot");
   {
@@ -302,47 +285,51 @@ __device__ __forceinline__ void tile_epilogue(const GrgParams& p, const EpiIdx<N
   if (tid < NT) {
     double c = r1p[tid * TPS];
     for (int q = 1; q < TPS; ++q) c += r1p[tid * TPS + q];
-    r1s[tid] = c;
+    si.r1[tid] = c;
+    si.sc[tid] = ix.sc;
+    si.tgt[tid] = ix.tgt;
   }
   __syncthreads();
+  const double* __restrict__ prev = p.acc_src ? p.acc_src : p.out;
 #pragma unroll
-  for (int j = 0; j < NTT; ++j) {
-    const int col = (wn * NTT + j) * 16 + (lane & 15);
-    const int slot = CX ? cx_slot(col) : col;
-    const int part = CX ? (col >> 4) & 1 : 0;
-    const int tgt = ix.tgt[j];
-    if (tgt < 0) continue;
-    const double sc = ix.sc[j];
-    const double r1 = r1s[slot];
-    double* __restrict__ o = p.out + (size_t)tgt * p.out_stride;
-    // output index of accumulator row `row` (-1: a padding row of a factored stage)
-    auto index = [&](int row) { return CX ? (row < QV ? 2 * row + part : -1) : row; };
-    double prev[MT][4];
+  for (int j = 0; j < NTT; j += CX ? 2 : 1)
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+    for (int r = 0; r < 4; ++r) {
+      const int col = (wn * NTT + j) * 16 + 4 * r + (lane >> 4);
+      const int slot = CX ? cx_slot(col) : col;
+      const int tgt = si.tgt[slot];
+      if (tgt < 0) continue;
+      const double r1 = si.r1[slot], sc = si.sc[slot];
+      const size_t o = (size_t)tgt * p.out_stride;
+      if constexpr (CX) {
+        d2 v[MT];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) prev[i][r] = 0.0;
-    if (p.accumulate) {
-      const double* __restrict__ a = (p.acc_src ? p.acc_src : p.out) + (size_t)tgt * p.out_stride;
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int x = index((wm * MT + i) * 16 + 4 * r + (lane >> 4));
-          if (x >= 0) prev[i][r] = a[x];
+        for (int i = 0; i < MT; ++i) {
+          const int row = (wm * MT + i) * 16 + (lane & 15);
+          v[i] = d2{acc[i][j][r], acc[i][j + 1][r]};
+          if (p.r1_all_rows || row == 0) v[i].x += r1;
+          v[i] *= sc;
+          if (p.accumulate && row < QV) v[i] += *reinterpret_cast<const d2*>(prev + o + 2 * row);
         }
-    }
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+        for (int i = 0; i < MT; ++i) {
+          const int row = (wm * MT + i) * 16 + (lane & 15);
+          if (row < QV) *reinterpret_cast<d2*>(p.out + o + 2 * row) = v[i];
+        }
+      } else {
+        double v[MT];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int x = index((wm * MT + i) * 16 + 4 * r + (lane >> 4));
-        if (x < 0) continue;
-        double v = acc[i][j][r];
-        if (p.r1_all_rows || x == 0) v += r1;
-        o[x] = v * sc + prev[i][r];
+        for (int i = 0; i < MT; ++i) {
+          const int row = (wm * MT + i) * 16 + (lane & 15);
+          v[i] = acc[i][j][r];
+          if (p.r1_all_rows || row == 0) v[i] += r1;
+          v[i] *= sc;
+          if (p.accumulate) v[i] += prev[o + row];
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i) p.out[o + (wm * MT + i) * 16 + (lane & 15)] = v[i];
       }
-  }
+    }
 }
 
 // Persistent, balanced launch: block b runs the pieces the plan gave it. A piece that is a
@@ -391,7 +378,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
   __shared__ double As[M * KC];
   __shared__ double Bs[NCOL * LDB];
   __shared__ double Ws[CX ? 2 * M : 2];
-  __shared__ double r1s[NT];
+  __shared__ SlotInfo<NT> slots;
   __shared__ double r1p[NTHR];
   __shared__ int last_s;
 
@@ -409,8 +396,8 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
   }
   for (int pc = pc0; pc < pc1; ++pc) {
     const PieceDesc P = p.pieces[pc];
-    EpiIdx<NTT, NT, NTHR, CX> ix;
-    ix.load(p, P.tile, tid, lane, wn);
+    EpiIdx<NT, NTHR> ix;
+    ix.load(p, P.tile, tid);
     d4 acc[MT][NTT];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -443,17 +430,17 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
         // acc += w_out[l] * part, complex: fragments 2j and 2j + 1 hold the real and the
         // imaginary part of (l, slot) in the same lane
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+        for (int i = 0; i < MT; ++i) {
+          const d2 w = W2[(wm * MT + i) * 16 + (lane & 15)];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const d2 w = W2[(wm * MT + i) * 16 + 4 * r + (lane >> 4)];
+          for (int r = 0; r < 4; ++r)
 #pragma unroll
             for (int j = 0; j < NTT; j += 2) {
               const double re = part[i][j][r], im = part[i][j + 1][r];
               acc[i][j][r] = fma(w.x, re, fma(-w.y, im, acc[i][j][r]));
               acc[i][j + 1][r] = fma(w.x, im, fma(w.y, re, acc[i][j + 1][r]));
             }
-          }
+        }
         if (!more) break;
         __syncthreads();  // every wave is done reading the segment and its weights
         L.template store<LDB>(tid, Bs, Ws);
@@ -524,7 +511,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
       }
       if (tid == 0) __hip_atomic_store(p.tile_count + P.tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    tile_epilogue<MT, NTT, WM, NT, NTHR, CX, KC>(p, ix, acc, r1s, r1p, tid, lane, wm, wn);
+    tile_epilogue<MT, NTT, WM, NT, NTHR, CX, KC>(p, ix, acc, slots, r1p, tid, lane, wm, wn);
   }
 }
 

@@ -12,7 +12,7 @@
 // Both work on leaves in the caller's order: they stream the leaf arrays.
 //
 // Part p = px + 2 py. Sums are left without the factor 1/2 of the orthonormal transform; the
-// tables carry it. MFMA layout as in kernels.hip.
+// tables carry it. MFMA operands as in device.hpp.
 #include <hip/hip_runtime.h>
 
 #include "device.hpp"
@@ -20,7 +20,7 @@
 
 namespace vp {
 
-typedef double d4 __attribute__((ext_vector_type(4)));
+typedef mfma_d4 d4;
 typedef double d2 __attribute__((ext_vector_type(2)));
 #define GLOBAL __attribute__((address_space(1)))
 typedef const GLOBAL double* gdp;
@@ -31,10 +31,6 @@ __device__ __forceinline__ int leaf_block(int b, int G) {
   const int q = G >> 3, r = G & 7, x = b & 7;
   return x * q + min(x, r) + (b >> 3);
 }
-__device__ __forceinline__ d4 mfma(double a, double b, d4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-
 // The real of part p's term i in an expansion of interleaved (Re, Im): Re z^n is even in y, Im z^n
 // odd; in x they have the parity of n and of n - 1.
 __device__ __forceinline__ int part_real(int p, int i) { return 4 * i + (p == 0 ? 0 : (p == 1 ? 2 : (p == 2 ? 3 : 1))); }
@@ -134,25 +130,25 @@ __global__ void __launch_bounds__(kThreads, 2) leaf_in_kernel(const LeafParams p
       const double b0 = B0[4 * kk], b1 = B0[16 * kLdIn + 4 * kk];
 #pragma unroll
       for (int t = 0; t < 3; ++t) {
-        acc[t][0] = mfma(a[kk][t], b0, acc[t][0]);
-        acc[t][1] = mfma(a[kk][t], b1, acc[t][1]);
+        acc[t][0] = mfma_16x16x4(a[kk][t], b0, acc[t][0]);
+        acc[t][1] = mfma_16x16x4(a[kk][t], b1, acc[t][1]);
       }
     }
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int leaf = tile * kSlots + 16 * j + (lane & 15);
-      if (leaf >= p.n_leaves) continue;
-      double* __restrict__ e = p.out_e + (size_t)leaf * kOutAll + kOut * part;
-      double* __restrict__ m = p.out_exp + (size_t)p.leaf_box[leaf] * p.ne;
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int t = 0; t < 3; ++t)
+      for (int r = 0; r < 4; ++r) {
+        const int leaf = tile * kSlots + 16 * j + 4 * r + (lane >> 4);
+        if (leaf >= p.n_leaves) continue;
+        double* __restrict__ e = p.out_e + (size_t)leaf * kOutAll + kOut * part;
+        double* __restrict__ m = p.out_exp + (size_t)p.leaf_box[leaf] * p.ne;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int row = 16 * t + 4 * q + (lane >> 4);
-          if (row < kOut) e[row] = acc[t][j][q];
-          else if (row - kOut < p.ne / 4) m[part_real(part, row - kOut)] = acc[t][j][q];
+        for (int t = 0; t < 3; ++t) {
+          const int row = 16 * t + (lane & 15);
+          if (row < kOut) e[row] = acc[t][j][r];
+          else if (row - kOut < p.ne / 4) m[part_real(part, row - kOut)] = acc[t][j][r];
         }
-    }
+      }
   }
 }
 
@@ -198,17 +194,16 @@ __global__ void __launch_bounds__(kThreads, 2) leaf_in_adj_kernel(const LeafPara
 #pragma unroll
           for (int pt = 0; pt < 4; ++pt) {
             const double* b = B0 + pt * kSlots * kLdIn + 4 * (4 * kq + k);
-            acc[pt][0] = mfma(a[kq & 1][k][pt], b[0], acc[pt][0]);
-            acc[pt][1] = mfma(a[kq & 1][k][pt], b[16 * kLdIn], acc[pt][1]);
+            acc[pt][0] = mfma_16x16x4(a[kq & 1][k][pt], b[0], acc[pt][0]);
+            acc[pt][1] = mfma_16x16x4(a[kq & 1][k][pt], b[16 * kLdIn], acc[pt][1]);
           }
       }
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const int leaf = tile * kSlots + 16 * j + (lane & 15);
-        if (leaf >= p.n_leaves) continue;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int row = 4 * q + (lane >> 4);
+          const int leaf = tile * kSlots + 16 * j + 4 * q + (lane >> 4), row = lane & 15;
+          if (leaf >= p.n_leaves) continue;
           const double x0 = acc[0][j][q], x1 = acc[1][j][q], x2 = acc[2][j][q], x3 = acc[3][j][q];
           if (g < 3) {  // right and left edge: even and odd in y
             double* o = p.out_edge + (size_t)leaf * (4 * kEdge) + 16 * g + row;
@@ -392,8 +387,8 @@ __global__ void __launch_bounds__(kThreads, 2) leaf_out_kernel(const LeafParams 
         }
 #pragma unroll
         for (int pt = 0; pt < 4; ++pt) {
-          acc[pt][0] = mfma(a[pt], b[pt][0], acc[pt][0]);
-          acc[pt][1] = mfma(a[pt], b[pt][1], acc[pt][1]);
+          acc[pt][0] = mfma_16x16x4(a[pt], b[pt][0], acc[pt][0]);
+          acc[pt][1] = mfma_16x16x4(a[pt], b[pt][1], acc[pt][1]);
         }
       }
       if (!more) break;
@@ -402,26 +397,24 @@ __global__ void __launch_bounds__(kThreads, 2) leaf_out_kernel(const LeafParams 
       L.store(c, scale, tid, As, Bs);
       __syncthreads();  // the next chunk is visible
     }
-    // rows 16 w + 4 q + lane / 16 of each part: node row j = 2 w + q / 2, column i = 4 (q % 2) + lane / 16
+    // row 16 w + l % 16 of each part: node row j = 2 w + l % 16 / 8, column i = l % 8
+    const int j = 2 * wave + ((lane & 15) >> 3), i = lane & 7;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int s = 16 * h + (lane & 15), lf = tile * kSlots + s;
-      if (lf < p.n_leaves) {
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int s = 16 * h + 4 * q + (lane >> 4), lf = tile * kSlots + s;
+        if (lf >= p.n_leaves) continue;
         const double r1 = ADJ ? 0.0 : r1s[s];
         const double so = ADJ ? p.leaf_s2[lf] : 1.0;
         double* __restrict__ o = p.out + (size_t)lf * 256;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int j = 2 * wave + (q >> 1), i = 4 * (q & 1) + (lane >> 4);
-          const double x0 = acc[0][h][q], x1 = acc[1][h][q], x2 = acc[2][h][q], x3 = acc[3][h][q];
-          const double s0 = x0 + x1, d0 = x0 - x1, s1 = x2 + x3, d1 = x2 - x3;
-          o[16 * j + i] = (s0 + s1 + r1) * so;
-          o[16 * j + 15 - i] = (d0 + d1 + r1) * so;
-          o[16 * (15 - j) + i] = (s0 - s1 + r1) * so;
-          o[16 * (15 - j) + 15 - i] = (d0 - d1 + r1) * so;
-        }
+        const double x0 = acc[0][h][q], x1 = acc[1][h][q], x2 = acc[2][h][q], x3 = acc[3][h][q];
+        const double s0 = x0 + x1, d0 = x0 - x1, s1 = x2 + x3, d1 = x2 - x3;
+        o[16 * j + i] = (s0 + s1 + r1) * so;
+        o[16 * j + 15 - i] = (d0 + d1 + r1) * so;
+        o[16 * (15 - j) + i] = (s0 - s1 + r1) * so;
+        o[16 * (15 - j) + 15 - i] = (d0 - d1 + r1) * so;
       }
-    }
     __syncthreads();  // LDS is free for the next tile
   }
 }
