@@ -196,7 +196,7 @@ struct LoaderCX {
 // scheduling barriers keep that order (left to itself, the compiler sinks the reads below the
 // products to reuse the operand registers, and each step then waits for its reads).
 template <int MT, int NTT, int M, int LDB, int KC>
-__device__ __forceinline__ void mfma_chunk(const double* __restrict__ Aw, const double* __restrict__ Bw,
+__device__ __forceinline__ void mfma_chunk_(const double* __restrict__ Aw, const double* __restrict__ Bw,
                                            d4 (&acc)[MT][NTT]) {
   constexpr int NK = KC / 4;
   double a[2][MT], b[2][NTT];
@@ -221,6 +221,14 @@ __device__ __forceinline__ void mfma_chunk(const double* __restrict__ Aw, const 
         acc[i][j] = mfma_16x16x4(a[cur][i], b[cur][j], acc[i][j]);
     __builtin_amdgcn_sched_barrier(0);
   }
+}
+
+template <int MT, int NTT, int M, int LDB, int KC>
+__device__ __forceinline__ void mfma_chunk(const double* __restrict__ Aw, const double* __restrict__ Bw,
+                                           d4 (&acc)[MT][NTT]) {
+  __builtin_amdgcn_s_setprio(0);
+  mfma_chunk_<MT, NTT, M, LDB, KC>(Aw, Bw, acc);
+  __builtin_amdgcn_s_setprio(2);
 }
 
 // Output of one tile: rank-one terms, optional s^2 scaling, overwrite or accumulate.
@@ -382,6 +390,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
   __shared__ double r1p[NTHR];
   __shared__ int last_s;
 
+  __builtin_amdgcn_s_setprio(2);
   const int blk = xcd_tile(blockIdx.x, gridDim.x);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WM, wn = wave / WM;

@@ -35,14 +35,22 @@ __device__ __forceinline__ int leaf_block(int b, int G) {
 // odd; in x they have the parity of n and of n - 1.
 __device__ __forceinline__ int part_real(int p, int i) { return 4 * i + (p == 0 ? 0 : (p == 1 ? 2 : (p == 2 ? 3 : 1))); }
 
+// Loads at a byte offset from an address that is the same for the whole wave: the address stays in
+// scalar registers, the offset takes one vector register.
+typedef const GLOBAL char* gcp;
+__device__ __forceinline__ d2 pair_at(const double* base, uint32_t byte) { return *(gd2p)((gcp)base + byte); }
+__device__ __forceinline__ double value_at(const double* base, uint32_t byte) { return *(gdp)((gcp)base + byte); }
+
 // Four raw pairs of one leaf: the mirrored nodes of rows j, 15 - j and columns i, i + 1, 15 - i, 14 - i
 struct Raw {
   d2 v[4];
-  __device__ __forceinline__ void leaf(gdp x, int j, int i) {
-    v[0] = *(gd2p)(x + 16 * j + i);
-    v[1] = *(gd2p)(x + 16 * j + 14 - i);
-    v[2] = *(gd2p)(x + 16 * (15 - j) + i);
-    v[3] = *(gd2p)(x + 16 * (15 - j) + 14 - i);
+  // x: values of the tile's first leaf
+  __device__ __forceinline__ void leaf(const double* x, int slot, int j, int i) {
+    const uint32_t row = 2048 * slot + 128 * j, mir = 2048 * slot + 128 * (15 - j);
+    v[0] = pair_at(x, row + 8 * i);
+    v[1] = pair_at(x, row + 8 * (14 - i));
+    v[2] = pair_at(x, mir + 8 * i);
+    v[3] = pair_at(x, mir + 8 * (14 - i));
   }
   __device__ __forceinline__ void unmirror() {
     v[1] = d2{v[1].y, v[1].x};
@@ -75,14 +83,14 @@ constexpr int kThreads = 256;
 constexpr int kLdIn = 65;
 
 __device__ __forceinline__ void in_load(const LeafParams& p, int tile, int tid, Raw (&r)[4], double (&sc)[4]) {
+  const int first = tile * kSlots, last = p.n_leaves - 1 - first;  // the tile's first leaf, its last slot with one
+  const double* x = p.x + (size_t)first * 256;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int idx = tid + q * kThreads, leaf = tile * kSlots + (idx >> 5);
-    const bool ok = leaf < p.n_leaves;
-    const int l = ok ? leaf : 0;
-    sc[q] = ok ? (p.s2_in ? p.leaf_s2[l] : 1.0) : 0.0;
-    r[q].leaf((gdp)p.x + (size_t)l * 256, (idx & 31) >> 2, 2 * (idx & 3));
-    if (!ok) r[q].zero();
+    const int idx = tid + q * kThreads, slot = idx >> 5, s = min(slot, last);
+    sc[q] = slot <= last ? (p.s2_in ? p.leaf_s2[first + s] : 1.0) : 0.0;
+    r[q].leaf(x, s, (idx & 31) >> 2, 2 * (idx & 3));
+    if (slot > last) r[q].zero();
   }
 }
 __device__ __forceinline__ void in_store(int tid, Raw (&r)[4], const double (&sc)[4], double* Bs) {
@@ -125,6 +133,7 @@ __global__ void __launch_bounds__(kThreads, 2) leaf_in_kernel(const LeafParams p
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[t][j] = d4{0.0, 0.0, 0.0, 0.0};
     const double* B0 = Bs + (part * kSlots + (lane & 15)) * kLdIn + (lane >> 4);
+    __builtin_amdgcn_s_setprio(0);
 #pragma unroll
     for (int kk = 0; kk < 16; ++kk) {
       const double b0 = B0[4 * kk], b1 = B0[16 * kLdIn + 4 * kk];
@@ -134,6 +143,7 @@ __global__ void __launch_bounds__(kThreads, 2) leaf_in_kernel(const LeafParams p
         acc[t][1] = mfma_16x16x4(a[kk][t], b1, acc[t][1]);
       }
     }
+    __builtin_amdgcn_s_setprio(2);
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -152,86 +162,93 @@ __global__ void __launch_bounds__(kThreads, 2) leaf_in_kernel(const LeafParams p
   }
 }
 
-__global__ void __launch_bounds__(kThreads, 2) leaf_in_adj_kernel(const LeafParams p) {
+constexpr int kAdjThreads = 512;
+
+__global__ void __launch_bounds__(kAdjThreads, 4) leaf_in_adj_kernel(const LeafParams p) {
   __shared__ double Bs[4 * kSlots * kLdIn];
   const int tid = threadIdx.x, lane = tid & 63;
-  // waves take the groups in turn; every other block starts two waves on, so that the SIMDs
-  // share the groups left over
-  const int wave = ((tid >> 6) + 2 * (blockIdx.x >> 3)) & 3;
   const int blk = leaf_block(blockIdx.x, gridDim.x);
   const int t0 = (int)((int64_t)blk * p.n_tiles / gridDim.x), t1 = (int)((int64_t)(blk + 1) * p.n_tiles / gridDim.x);
-  Raw r[4];
-  double sc[4];
-  if (t0 < t1) in_load(p, t0, tid, r, sc);
+  const size_t step = (size_t)p.n_groups * 4 * 64;
   for (int tile = t0; tile < t1; ++tile) {
+    __syncthreads();  // the previous tile's values are read
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int idx = tid + q * kAdjThreads, slot = idx >> 5, last = p.n_leaves - 1 - tile * kSlots;
+      const int k = 8 * ((idx & 31) >> 2) + 2 * (idx & 3);
+      Raw r;
+      r.leaf(p.x + (size_t)tile * kSlots * 256, min(slot, last), (idx & 31) >> 2, 2 * (idx & 3));
+      if (slot > last) r.zero();
+      r.unmirror();
+      r.sum_x();
+      r.sum_y();
+#pragma unroll
+      for (int pt = 0; pt < 4; ++pt) {
+        double* b = Bs + (pt * kSlots + slot) * kLdIn + k;
+        b[0] = r.v[pt].x;
+        b[1] = r.v[pt].y;
+      }
+    }
     __syncthreads();
-    in_store(tid, r, sc, Bs);
-    __syncthreads();
-    if (tile + 1 < t1) in_load(p, tile + 1, tid, r, sc);
-    const double* B0 = Bs + (lane & 15) * kLdIn + (lane >> 4);
-    for (int g = wave; g < p.n_groups; g += 4) {
-      gdp A = (gdp)p.table + (size_t)g * 4 * 64 + lane;
-      const size_t step = (size_t)p.n_groups * 4 * 64;
-      d4 acc[4][2];
+    // units of 16 rows of the four parts and 16 leaves; the wave that starts changes with the tile, so
+    // that the waves share the units left over
+    for (int u = __builtin_amdgcn_readfirstlane(((tid >> 6) + 3 * tile) & 7); u < 2 * p.n_groups; u += 8) {
+      const int g = u >> 1, half = u & 1;
+      const double* B0 = Bs + (16 * half + (lane & 15)) * kLdIn + (lane >> 4);
+      const double* A = p.table + (size_t)g * 4 * 64;
+      const uint32_t at = 8 * lane;
+      d4 acc[4];
 #pragma unroll
-      for (int pt = 0; pt < 4; ++pt)
+      for (int pt = 0; pt < 4; ++pt) acc[pt] = d4{0.0, 0.0, 0.0, 0.0};
+      double a[2][2][4];  // two k-steps of fragments, and the next two in flight
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[pt][j] = d4{0.0, 0.0, 0.0, 0.0};
-      double a[2][4][4];  // four k-steps of fragments, and the next four in flight
+      for (int k = 0; k < 2; ++k)
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
+        for (int pt = 0; pt < 4; ++pt) a[0][k][pt] = value_at(A + k * step + pt * 64, at);
 #pragma unroll
-        for (int pt = 0; pt < 4; ++pt) a[0][k][pt] = A[k * step + pt * 64];
+      for (int kq = 0; kq < 8; ++kq) {
+        if (kq < 7)
 #pragma unroll
-      for (int kq = 0; kq < 4; ++kq) {
-        if (kq < 3)
+          for (int k = 0; k < 2; ++k)
 #pragma unroll
-          for (int k = 0; k < 4; ++k)
+            for (int pt = 0; pt < 4; ++pt) a[(kq + 1) & 1][k][pt] = value_at(A + (2 * (kq + 1) + k) * step + pt * 64, at);
 #pragma unroll
-            for (int pt = 0; pt < 4; ++pt) a[(kq + 1) & 1][k][pt] = A[(4 * (kq + 1) + k) * step + pt * 64];
+        for (int k = 0; k < 2; ++k)
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-          for (int pt = 0; pt < 4; ++pt) {
-            const double* b = B0 + pt * kSlots * kLdIn + 4 * (4 * kq + k);
-            acc[pt][0] = mfma_16x16x4(a[kq & 1][k][pt], b[0], acc[pt][0]);
-            acc[pt][1] = mfma_16x16x4(a[kq & 1][k][pt], b[16 * kLdIn], acc[pt][1]);
-          }
+          for (int pt = 0; pt < 4; ++pt)
+            acc[pt] = mfma_16x16x4(a[kq & 1][k][pt], B0[pt * kSlots * kLdIn + 4 * (2 * kq + k)], acc[pt]);
       }
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int leaf = tile * kSlots + 16 * j + 4 * q + (lane >> 4), row = lane & 15;
-          if (leaf >= p.n_leaves) continue;
-          const double x0 = acc[0][j][q], x1 = acc[1][j][q], x2 = acc[2][j][q], x3 = acc[3][j][q];
-          if (g < 3) {  // right and left edge: even and odd in y
-            double* o = p.out_edge + (size_t)leaf * (4 * kEdge) + 16 * g + row;
-            o[0] = x0 + x1;
-            o[kEdge] = x0 - x1;
-            o[kEdge / 2] = x2 + x3;
-            o[kEdge + kEdge / 2] = x2 - x3;
-          } else if (g < 6) {  // upper and lower edge: even and odd in x
-            double* o = p.out_edge + (size_t)leaf * (4 * kEdge) + 2 * kEdge + 16 * (g - 3) + row;
-            o[0] = x0 + x2;
-            o[kEdge] = x0 - x2;
-            o[kEdge / 2] = x1 + x3;
-            o[kEdge + kEdge / 2] = x1 - x3;
-          } else if (g < kLinGroups) {  // corners
-            double* o = p.out_corner + (size_t)leaf * (4 * kCorner) + 16 * (g - 6) + row;
-            const double s0 = x0 + x1, d0 = x0 - x1, s1 = x2 + x3, d1 = x2 - x3;
-            o[0] = s0 + s1;
-            o[kCorner] = d0 + d1;
-            o[2 * kCorner] = s0 - s1;
-            o[3 * kCorner] = d0 - d1;
-          } else {
-            const int i = 16 * (g - kLinGroups) + row;
-            const int box = p.loc_box[leaf];
-            if (i < p.ne / 4 && box >= 0) {  // reals 4i .. 4i + 3 are parts 0, 3, 1, 2
-              double* o = p.out_exp + (size_t)box * p.ne + 4 * i;
-              *reinterpret_cast<d2*>(o) = d2{x0, x3};
-              *reinterpret_cast<d2*>(o + 2) = d2{x1, x2};
-            }
+      for (int q = 0; q < 4; ++q) {
+        const int leaf = tile * kSlots + 16 * half + 4 * q + (lane >> 4), row = lane & 15;
+        if (leaf >= p.n_leaves) continue;
+        const double x0 = acc[0][q], x1 = acc[1][q], x2 = acc[2][q], x3 = acc[3][q];
+        if (g < 3) {  // right and left edge: even and odd in y
+          double* o = p.out_edge + (size_t)leaf * (4 * kEdge) + 16 * g + row;
+          o[0] = x0 + x1;
+          o[kEdge] = x0 - x1;
+          o[kEdge / 2] = x2 + x3;
+          o[kEdge + kEdge / 2] = x2 - x3;
+        } else if (g < 6) {  // upper and lower edge: even and odd in x
+          double* o = p.out_edge + (size_t)leaf * (4 * kEdge) + 2 * kEdge + 16 * (g - 3) + row;
+          o[0] = x0 + x2;
+          o[kEdge] = x0 - x2;
+          o[kEdge / 2] = x1 + x3;
+          o[kEdge + kEdge / 2] = x1 - x3;
+        } else if (g < kLinGroups) {  // corners
+          double* o = p.out_corner + (size_t)leaf * (4 * kCorner) + 16 * (g - 6) + row;
+          const double s0 = x0 + x1, d0 = x0 - x1, s1 = x2 + x3, d1 = x2 - x3;
+          o[0] = s0 + s1;
+          o[kCorner] = d0 + d1;
+          o[2 * kCorner] = s0 - s1;
+          o[3 * kCorner] = d0 - d1;
+        } else {
+          const int i = 16 * (g - kLinGroups) + row;
+          const int box = p.loc_box[leaf];
+          if (i < p.ne / 4 && box >= 0) {  // reals 4i .. 4i + 3 are parts 0, 3, 1, 2
+            double* o = p.out_exp + (size_t)box * p.ne + 4 * i;
+            *reinterpret_cast<d2*>(o) = d2{x0, x3};
+            *reinterpret_cast<d2*>(o + 2) = d2{x1, x2};
           }
         }
       }
@@ -242,57 +259,58 @@ __global__ void __launch_bounds__(kThreads, 2) leaf_in_adj_kernel(const LeafPara
 // ---------------------------------------------------------------- leaf_out
 // The product of a tile's 256 rows (64 of each part) with its columns in chunks of 16 per part:
 // wave w holds rows 16 w .. 16 w + 15 of all four parts, so the sums that give the mirrored nodes
-// are between its own accumulators. A chunk (256 x 16 of the table, 4 x 16 values of 32 leaves)
-// goes through LDS while the next one's loads are in flight, as in grg_kernel. Every kind of
-// column is four raw pairs per thread and sums of them: mirrored nodes, the two edges or four
-// corners that the parts add or subtract, or an expansion's reals.
+// are between its own accumulators. No two waves read the same table fragment, so those go from the
+// L2 straight to registers, each refilled for the next chunk as soon as it has been multiplied; only
+// the 4 x 16 values of 32 leaves go through LDS, in two buffers, one barrier per chunk. (Staged
+// through LDS as well, the fragments took LDS to 56% of the matrix cores' time.) Every kind of column
+// is four raw pairs per thread and sums of them: mirrored nodes, the two edges or four corners that
+// the parts add or subtract, or an expansion's reals.
 constexpr int kLdOut = 17;
 constexpr int kCorner0 = (64 + kEdge) / 16;  // first chunk of the corners' columns
 
 template <bool ADJ>
 struct OutLoader {
   Raw r;
-  d2 a[8];
-  // the raw pairs of chunk c for leaf `leaf`, term pair starting at 2 m
-  __device__ __forceinline__ void load(const LeafParams& p, int c, int leaf, int box, int tid) {
-    gd2p A2 = (gd2p)p.table + (size_t)c * (256 * 16 / 2);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) a[q] = A2[tid + q * kThreads];
+  // the raw pairs of chunk c for leaf first + slot, term pair starting at o = 2 m
+  __device__ __forceinline__ void load(const LeafParams& p, int c, int first, int slot, int box, int tid) {
+    // opaque: the offsets of every kind of column are formed when needed, not kept through the loop
+    asm volatile("" : "+v"(slot), "+v"(tid));
     const int m = tid & 7, o = 2 * m;
     if (c < 4) {
-      r.leaf((gdp)p.x + (size_t)leaf * 256, 2 * c + (m >> 2), 2 * (m & 3));
+      r.leaf(p.x + (size_t)first * 256, slot, 2 * c + (m >> 2), 2 * (m & 3));
       return;
     }
     if (ADJ) {
       if (c < 6) {
         const int k = 16 * (c - 4) + o;
-        gdp e = (gdp)p.in_e + (size_t)leaf * kOutAll + (k < kOut ? k : 0);
+        const double* e = p.in_e + (size_t)first * kOutAll;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) r.v[q] = *(gd2p)(e + q * kOut);
+        for (int q = 0; q < 4; ++q) r.v[q] = pair_at(e + q * kOut, 8 * (slot * kOutAll + (k < kOut ? k : 0)));
         if (k >= kOut) r.zero();
         return;
       }
     } else {
+      const uint32_t at = 8 * (slot * (4 * kEdge) + o);
       if (c < 7) {
-        gdp h = (gdp)p.in_edge + (size_t)leaf * (4 * kEdge) + 16 * (c - 4) + o;
-        r.v[0] = *(gd2p)(h);
-        r.v[1] = *(gd2p)(h + kEdge);
-        r.v[2] = *(gd2p)(h + kEdge / 2);
-        r.v[3] = *(gd2p)(h + kEdge + kEdge / 2);
+        const double* h = p.in_edge + (size_t)first * (4 * kEdge) + 16 * (c - 4);
+        r.v[0] = pair_at(h, at);
+        r.v[1] = pair_at(h + kEdge, at);
+        r.v[2] = pair_at(h + kEdge / 2, at);
+        r.v[3] = pair_at(h + kEdge + kEdge / 2, at);
         return;
       }
       if (c < 10) {
-        gdp h = (gdp)p.in_edge + (size_t)leaf * (4 * kEdge) + 2 * kEdge + 16 * (c - 7) + o;
-        r.v[0] = *(gd2p)(h);
-        r.v[1] = *(gd2p)(h + kEdge / 2);
-        r.v[2] = *(gd2p)(h + kEdge);
-        r.v[3] = *(gd2p)(h + kEdge + kEdge / 2);
+        const double* h = p.in_edge + (size_t)first * (4 * kEdge) + 2 * kEdge + 16 * (c - 7);
+        r.v[0] = pair_at(h, at);
+        r.v[1] = pair_at(h + kEdge / 2, at);
+        r.v[2] = pair_at(h + kEdge, at);
+        r.v[3] = pair_at(h + kEdge + kEdge / 2, at);
         return;
       }
       if (c < kCorner0 + kCorner / 16) {
-        gdp h = (gdp)p.in_corner + (size_t)leaf * (4 * kCorner) + 16 * (c - kCorner0) + o;
+        const double* h = p.in_corner + (size_t)first * (4 * kCorner) + 16 * (c - kCorner0);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) r.v[q] = *(gd2p)(h + q * kCorner);
+        for (int q = 0; q < 4; ++q) r.v[q] = pair_at(h + q * kCorner, 8 * (slot * (4 * kCorner) + o));
         return;
       }
     }
@@ -303,10 +321,7 @@ struct OutLoader {
     for (int q = 0; q < 4; ++q) r.v[q] = *(gd2p)(x + 2 * q);
     if (!ok) r.zero();
   }
-  __device__ __forceinline__ void store(int c, double scale, int tid, double* As, double* Bs) {
-    d2* As2 = reinterpret_cast<d2*>(As);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) As2[tid + q * kThreads] = a[q];
+  __device__ __forceinline__ void store(int c, double scale, int tid, double* Bs) {
     if (c < 4) {
       r.unmirror();
       r.sum_x();
@@ -338,24 +353,23 @@ struct OutLoader {
 };
 
 template <bool ADJ>
-__global__ void __launch_bounds__(kThreads, 2) leaf_out_kernel(const LeafParams p) {
-  __shared__ double As[256 * 16];
-  __shared__ double Bs[4 * kSlots * kLdOut];
-  __shared__ double r1s[kSlots];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+__global__ void __launch_bounds__(kThreads, 3) leaf_out_kernel(const LeafParams p) {
+  __shared__ double Bs[2][4 * kSlots * kLdOut];
+  __shared__ double r1s_[2][kSlots];  // of even and of odd tiles: a fast wave forms the next tile's while this one's are read
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int blk = leaf_block(blockIdx.x, gridDim.x);
   const int t0 = (int)((int64_t)blk * p.n_tiles / gridDim.x), t1 = (int)((int64_t)(blk + 1) * p.n_tiles / gridDim.x);
   const int n_chunks = p.n_chunks;
-  const double* __restrict__ Aw = As + wave * 64 + lane;
-  const double* __restrict__ Bw = Bs + (lane & 15) * kLdOut + (lane >> 4);
+  const int b_at = (lane & 15) * kLdOut + (lane >> 4);
   for (int tile = t0; tile < t1; ++tile) {
-    const int sl = tile * kSlots + (tid >> 3);  // the leaf whose values this thread stages
-    const bool ok = sl < p.n_leaves;
-    const int leaf = ok ? sl : 0;
+    const int first = tile * kSlots, last = p.n_leaves - 1 - first;
+    double* r1s = r1s_[tile & 1];
+    const bool ok = (tid >> 3) <= last;            // this thread stages values of a leaf, not of an empty slot
+    const int slot = min(tid >> 3, last), leaf = first + slot;
     const int box = ok ? p.loc_box[leaf] : -1;
     const double scale = ok ? (p.s2_in ? p.leaf_s2[leaf] : 1.0) : 0.0;
     OutLoader<ADJ> L;
-    L.load(p, 0, leaf, box, tid);
+    L.load(p, 0, first, slot, box, tid);
     if (!ADJ) {  // the leaf's log terms, summed by its eight threads in a fixed order
       double c = 0.0;
       if (ok)
@@ -371,31 +385,40 @@ __global__ void __launch_bounds__(kThreads, 2) leaf_out_kernel(const LeafParams 
     for (int pt = 0; pt < 4; ++pt)
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[pt][j] = d4{0.0, 0.0, 0.0, 0.0};
-    L.store(0, scale, tid, As, Bs);
+    double a[4][4];  // fragments [k-step][part] of the current chunk
+    int a_off = wave * 64;  // of the current chunk's fragments
+    const uint32_t a_at = 8 * lane;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int pt = 0; pt < 4; ++pt) a[kk][pt] = value_at(p.table + a_off + (kk * 16 + pt * 4) * 64, a_at);
+    L.store(0, scale, tid, Bs[0]);
+    if (n_chunks > 1) L.load(p, 1, first, slot, box, tid);
     __syncthreads();
-    for (int c = 0;;) {
+#pragma clang loop unroll(disable)
+    for (int c = 0; c < n_chunks; ++c) {
       const bool more = c + 1 < n_chunks;
-      if (more) L.load(p, c + 1, leaf, box, tid);
+      const double* __restrict__ Bw = Bs[c & 1] + b_at;
+      a_off += more ? 256 * 16 : 0;  // the last chunk reloads its own fragments
+      // opaque, so that the fragments' addresses stay scalar instead of becoming 16 vector pointers
+      asm volatile("" : "+s"(a_off));
+      const double* A = p.table + a_off;
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
-        double a[4], b[4][2];
 #pragma unroll
         for (int pt = 0; pt < 4; ++pt) {
-          a[pt] = Aw[(kk * 16 + pt * 4) * 64];
-          b[pt][0] = Bw[pt * kSlots * kLdOut + 4 * kk];
-          b[pt][1] = Bw[(pt * kSlots + 16) * kLdOut + 4 * kk];
+          acc[pt][0] = mfma_16x16x4(a[kk][pt], Bw[pt * kSlots * kLdOut + 4 * kk], acc[pt][0]);
+          acc[pt][1] = mfma_16x16x4(a[kk][pt], Bw[(pt * kSlots + 16) * kLdOut + 4 * kk], acc[pt][1]);
         }
 #pragma unroll
-        for (int pt = 0; pt < 4; ++pt) {
-          acc[pt][0] = mfma_16x16x4(a[pt], b[pt][0], acc[pt][0]);
-          acc[pt][1] = mfma_16x16x4(a[pt], b[pt][1], acc[pt][1]);
-        }
+        for (int pt = 0; pt < 4; ++pt) a[kk][pt] = value_at(A + (kk * 16 + pt * 4) * 64, a_at);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      if (!more) break;
-      ++c;
-      __syncthreads();  // every wave is done reading the chunk
-      L.store(c, scale, tid, As, Bs);
-      __syncthreads();  // the next chunk is visible
+      if (more) {
+        L.store(c + 1, scale, tid, Bs[(c + 1) & 1]);
+        if (c + 2 < n_chunks) L.load(p, c + 2, first, slot, box, tid);
+      }
+      __syncthreads();  // the next chunk is visible, this one is read
     }
     // row 16 w + l % 16 of each part: node row j = 2 w + l % 16 / 8, column i = l % 8
     const int j = 2 * wave + ((lane & 15) >> 3), i = lane & 7;
@@ -415,10 +438,10 @@ __global__ void __launch_bounds__(kThreads, 2) leaf_out_kernel(const LeafParams 
         o[16 * (15 - j) + i] = (s0 - s1 + r1) * so;
         o[16 * (15 - j) + 15 - i] = (d0 - d1 + r1) * so;
       }
-    __syncthreads();  // LDS is free for the next tile
   }
 }
 
+static int leaf_threads(bool out, bool adjoint) { return !out && adjoint ? kAdjThreads : kThreads; }
 static const void* leaf_kernel(bool out, bool adjoint) {
   if (out)
     return adjoint ? reinterpret_cast<const void*>(&leaf_out_kernel<true>) : reinterpret_cast<const void*>(&leaf_out_kernel<false>);
@@ -429,7 +452,7 @@ int leaf_resident_blocks(bool out, bool adjoint) {
   int dev = 0, cus = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, leaf_kernel(out, adjoint), kThreads, 0) != hipSuccess)
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, leaf_kernel(out, adjoint), leaf_threads(out, adjoint), 0) != hipSuccess)
     return 0;
   return per_cu * cus;
 }
@@ -437,7 +460,7 @@ int leaf_resident_blocks(bool out, bool adjoint) {
 hipError_t launch_leaf_in(const LeafParams& p, bool adjoint, int n_blocks, hipStream_t stream) {
   if (p.n_tiles <= 0) return hipSuccess;
   const dim3 grid(unsigned(n_blocks < p.n_tiles ? n_blocks : p.n_tiles));
-  if (adjoint) hipLaunchKernelGGL(leaf_in_adj_kernel, grid, dim3(kThreads), 0, stream, p);
+  if (adjoint) hipLaunchKernelGGL(leaf_in_adj_kernel, grid, dim3(kAdjThreads), 0, stream, p);
   else hipLaunchKernelGGL(leaf_in_kernel, grid, dim3(kThreads), 0, stream, p);
   return hipGetLastError();
 }
