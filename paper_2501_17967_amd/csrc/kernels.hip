@@ -300,44 +300,56 @@ __device__ __forceinline__ void tile_epilogue(const GrgParams& p, const EpiIdx<N
   __syncthreads();
   const double* __restrict__ prev = p.acc_src ? p.acc_src : p.out;
 #pragma unroll
-  for (int j = 0; j < NTT; j += CX ? 2 : 1)
+  for (int j = 0; j < NTT; j += CX ? 2 : 1) {
+    // what is accumulated onto: 4 MT loads in flight before the first is used (adjoint corner stage of
+    // a 345k-leaf forest: 445 -> 321 us against one row of slots at a time)
+    d2 old[4][CX ? MT : (MT + 1) / 2];
+    int tgts[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int col = (wn * NTT + j) * 16 + 4 * r + (lane >> 4);
+      tgts[r] = si.tgt[CX ? cx_slot(col) : col];
+    }
+    if (p.accumulate) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double* __restrict__ o = prev + (size_t)max(tgts[r], 0) * p.out_stride;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+          const int row = (wm * MT + i) * 16 + (lane & 15);
+          if constexpr (CX) old[r][i] = *reinterpret_cast<const d2*>(o + 2 * (row < QV ? row : 0));
+          else old[r][i / 2][i % 2] = o[row];
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int col = (wn * NTT + j) * 16 + 4 * r + (lane >> 4);
       const int slot = CX ? cx_slot(col) : col;
-      const int tgt = si.tgt[slot];
+      const int tgt = tgts[r];
       if (tgt < 0) continue;
       const double r1 = si.r1[slot], sc = si.sc[slot];
-      const size_t o = (size_t)tgt * p.out_stride;
-      if constexpr (CX) {
-        d2 v[MT];
+      double* __restrict__ out = p.out + (size_t)tgt * p.out_stride;
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
-          const int row = (wm * MT + i) * 16 + (lane & 15);
-          v[i] = d2{acc[i][j][r], acc[i][j + 1][r]};
-          if (p.r1_all_rows || row == 0) v[i].x += r1;
-          v[i] *= sc;
-          if (p.accumulate && row < QV) v[i] += *reinterpret_cast<const d2*>(prev + o + 2 * row);
+      for (int i = 0; i < MT; ++i) {
+        const int row = (wm * MT + i) * 16 + (lane & 15);
+        if constexpr (CX) {
+          d2 v = d2{acc[i][j][r], acc[i][j + 1][r]};
+          if (p.r1_all_rows || row == 0) v.x += r1;
+          v *= sc;
+          if (p.accumulate) v += old[r][i];
+          if (row < QV) *reinterpret_cast<d2*>(out + 2 * row) = v;
+        } else {
+          double v = acc[i][j][r];
+          if (p.r1_all_rows || row == 0) v += r1;
+          v *= sc;
+          if (p.accumulate) v += old[r][i / 2][i % 2];
+          out[row] = v;
         }
-#pragma unroll
-        for (int i = 0; i < MT; ++i) {
-          const int row = (wm * MT + i) * 16 + (lane & 15);
-          if (row < QV) *reinterpret_cast<d2*>(p.out + o + 2 * row) = v[i];
-        }
-      } else {
-        double v[MT];
-#pragma unroll
-        for (int i = 0; i < MT; ++i) {
-          const int row = (wm * MT + i) * 16 + (lane & 15);
-          v[i] = acc[i][j][r];
-          if (p.r1_all_rows || row == 0) v[i] += r1;
-          v[i] *= sc;
-          if (p.accumulate) v[i] += prev[o + row];
-        }
-#pragma unroll
-        for (int i = 0; i < MT; ++i) p.out[o + (wm * MT + i) * 16 + (lane & 15)] = v[i];
       }
     }
+  }
 }
 
 // Persistent, balanced launch: block b runs the pieces the plan gave it. A piece that is a
@@ -505,18 +517,36 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
       __syncthreads();
       __atomic_signal_fence(__ATOMIC_SEQ_CST);
       if (!last_s) continue;
-      for (int q = 0; q < P.n_pieces; ++q) {
-        const double* __restrict__ part = p.partial + (size_t)(P.slot0 + q) * (M * NCOL) + wave * WPART + lane;
+      // The loads of PB pieces are all issued before the first is waited for: left to itself the
+      // compiler loads one value at a time where registers are tight (edge stage of a 1501-leaf
+      // tree, whose W-list tile has 55 pieces: 66 -> 25 us).
+      constexpr int NV = MT * NTT * 4, PB = NV <= 16 ? 2 : 1;
+      const double* __restrict__ part = p.partial + (size_t)P.slot0 * (M * NCOL) + wave * WPART + lane;
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+      for (int i = 0; i < MT; ++i)
 #pragma unroll
-          for (int j = 0; j < NTT; ++j)
+        for (int j = 0; j < NTT; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma clang loop unroll(disable)
+      for (int q = 0; q < P.n_pieces; q += PB, part += (size_t)PB * (M * NCOL)) {
+        double v[PB][NV];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const double v = __hip_atomic_load(part + ((i * NTT + j) * 4 + r) * 64, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-              acc[i][j][r] = q == 0 ? v : acc[i][j][r] + v;
-            }
+        for (int b = 0; b < PB; ++b) {
+          const double* __restrict__ src = part + (q + b < P.n_pieces ? b * (M * NCOL) : 0);
+#pragma unroll
+          for (int k = 0; k < NV; ++k)
+            v[b][k] = __hip_atomic_load(src + k * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < PB; ++b) {
+          if (b > 0 && q + b >= P.n_pieces) break;
+#pragma unroll
+          for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NTT; ++j)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) acc[i][j][r] += v[b][(i * NTT + j) * 4 + r];
+        }
       }
       if (tid == 0) __hip_atomic_store(p.tile_count + P.tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
