@@ -241,7 +241,7 @@ int upload(volpot_plan_s* p) {
   int rc = schedule_all(p, 0);
   if (rc != VOLPOT_OK) return rc;
   size_t total = 0;
-  const size_t nb = size_t(P.n_boxes) * P.ne * sizeof(double);
+  const size_t nb = (size_t(P.n_boxes) + 1) * P.ne * sizeof(double);  // the row after the last box stays zero
   struct Off { size_t tt, tsp, sd, ss, rp, ri, rf, rc, pc, bp, tc, ct, cp, ci; };
   std::vector<std::vector<int32_t>> zeros;  // arrival counters start at zero
   std::vector<std::vector<SegDesc>> segd;   // segment descriptors (table pointers of this device)
@@ -308,6 +308,9 @@ int upload(volpot_plan_s* p) {
   size_t si_ = 0;
   auto put_stage = [&](const Stage& s, const Off& o) {
     put(o.tt, s.tile_tgt); put(o.tsp, s.tile_seg_ptr); put(o.sd, segd[si_++]); put(o.ss, s.seg_src);
+    if (s.cx_rel >= 0)  // factored stages: a slot without a source reads the zero row
+      for (size_t i = 0; i < s.seg_src.size(); ++i)
+        if (s.seg_src[i] < 0) reinterpret_cast<int32_t*>(host.data() + o.ss)[i] = int32_t(P.n_boxes);
     put(o.rp, s.r1_ptr); put(o.ri, s.r1_idx); put(o.rf, s.r1_fam); put(o.rc, s.r1_coef);
     put(o.pc, s.pieces); put(o.bp, s.blk_ptr);
     put(o.ct, s.c_tgt); put(o.cp, s.c_ptr); put(o.ci, s.c_idx);

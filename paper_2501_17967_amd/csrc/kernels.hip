@@ -15,6 +15,8 @@
 // deterministic, identical whether a tree is applied alone or inside a forest.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "device.hpp"
 
 namespace vp {
@@ -46,6 +48,20 @@ __device__ __forceinline__ T pick3(const T (&a)[3], int i) {
 typedef const GLOBAL double* gdp;
 typedef const GLOBAL d2* gd2p;
 typedef const GLOBAL int32_t* gip;
+// What a launch only reads at addresses common to a wave goes through the scalar cache.
+#define CONSTANT __attribute__((address_space(4)))
+
+template <typename T>
+__device__ __forceinline__ T scalar_load(const T* x) {
+  static_assert(sizeof(T) % 8 == 0, "whole pairs of dwords");
+  T v;
+  const CONSTANT uint64_t* s = (const CONSTANT uint64_t*)(const void*)x;
+  uint64_t w[sizeof(T) / 8];
+#pragma unroll
+  for (size_t i = 0; i < sizeof(T) / 8; ++i) w[i] = s[i];
+  __builtin_memcpy(&v, w, sizeof(T));
+  return v;
+}
 
 // The loading side of a tile's walk over (segment, k-chunk) steps. Every relation of a stage has
 // the same K, a multiple of KC, so every chunk is full. Thread tid owns the A pairs
@@ -73,7 +89,7 @@ struct Loader {
       const int t = (tid + q * NTHR) / HALF;
       si[q] = t < NT ? src[t] : -1;
     }
-    const SegDesc sd = p.segs[s];
+    const SegDesc sd = scalar_load(p.segs + s);
     A = (gdp)sd.A;
     K = sd.K;
     base = (gdp)pick4(p.fam_base, sd.fam) + sd.k_off;
@@ -123,73 +139,81 @@ struct Loader {
   }
 };
 
-// Column of part h (0 real, 1 imaginary) of slot t in a factored tile: each group of 16 slots
-// takes 32 columns, the real parts first, so that one wave's two column fragments hold both
-// parts of the same 16 slots in the same lanes.
-__device__ __forceinline__ int cx_col(int t, int h) { return (t >> 4) * 32 + h * 16 + (t & 15); }
-
-// The loading side of a factored M2L stage: one chunk is one whole segment, the Q complex terms
-// of NT sources. Thread tid owns term k = tid % Q of the slots t = tid / Q + G q (G = NTHR / Q
-// thread groups; threads past G Q idle here), so it needs one input weight w_in[k] per segment.
-// Each source term is scaled by its complex weight on the way into LDS, its parts to columns
-// cx_col(t, 0) and cx_col(t, 1); thread tid < MP also stages the output weight w_out[tid] of
-// the segment.
-template <int NT, int NTHR, int Q, int MP>
+// A factored M2L stage: each wave has 16 slots, all rows and both parts of them, and one chunk is one
+// whole segment, the Q complex terms of its 16 sources. Nothing but the core is shared, so the walk
+// over the segments needs no barrier: a wave stages its sources in its own part of LDS. A source's
+// address is the same for the wave: its index comes through the scalar cache and the scalar unit forms
+// the address (a slot without a source reads the zero row that ends every expansion array). The vector
+// unit, which the matrix instructions share, is left with the scaling: a lane holds one real of the
+// source (a whole term for Q > 32) and gets the term's other real from its neighbour.
+template <int NT, int Q, int MT>
 struct LoaderCX {
-  static constexpr int G = NTHR / Q;
-  static constexpr int B_PER = (NT + G - 1) / G;
-  static_assert(G >= 1 && NTHR >= MP, "factored loader needs a thread per term and per output row");
-  int s;
-  gdp base;
+  static constexpr int RW = 16;
+  static constexpr bool TERM = Q > 32;
+  static_assert(Q <= 64, "a lane per real or term");
+  using real_t = std::conditional_t<TERM, d2, double>;
+  int idx[RW];    // sources of the segment to be loaded
+  const double *base, *w_in, *w_out;
   int stride;
-  int si[B_PER];  // source index per owned slot (-1: none)
-  d2 rb[B_PER], rw, ro;
+  real_t v[RW];   // the wave's sources
+  d2 rw, wo[MT];  // the lane's weights: of its term, and of its rows l % 16 of the MT fragments
 
-  __device__ __forceinline__ void segment(const GrgParams& p, int tid) {
-    gip src = (gip)(p.seg_src + (size_t)s * NT);
-    const int g = tid / Q;
+  __device__ __forceinline__ void fetch(const GrgParams& p, int s, int wave) {
+    const CONSTANT int32_t* src = (const CONSTANT int32_t*)(p.seg_src + (size_t)s * NT + wave * RW);
 #pragma unroll
-    for (int q = 0; q < B_PER; ++q) {
-      const int t = g + G * q;
-      si[q] = (g < G && t < NT) ? src[t] : -1;
-    }
-    const SegDesc sd = p.segs[s];
-    base = (gdp)pick4(p.fam_base, sd.fam);
-    stride = pick4(p.fam_stride, sd.fam);
-    const int k = tid % Q;
-    rw = ((gd2p)sd.w_in)[k];
-    ro = ((gd2p)sd.w_out)[tid < MP ? tid : 0];
+    for (int q = 0; q < RW; ++q) idx[q] = src[q];
+    const CONSTANT SegDesc* sd = (const CONSTANT SegDesc*)(p.segs + s);
+    const int fam = sd->fam;
+    base = pick4(p.fam_base, fam);
+    stride = pick4(p.fam_stride, fam);
+    w_in = sd->w_in;
+    w_out = sd->w_out;
   }
-  __device__ __forceinline__ void load(int tid) {
-    const int k = tid % Q;
+  __device__ __forceinline__ void load(int lane) {
+    uint32_t at = TERM ? 16 * min(lane, Q - 1) : 8 * min(lane, 2 * Q - 1);
+    uint32_t wat = 16 * min(TERM ? lane : lane >> 1, Q - 1), oat = 16 * (lane & 15);
+    asm volatile("" : "+v"(at), "+v"(wat), "+v"(oat));  // opaque, so that the rows' addresses stay scalar
 #pragma unroll
-    for (int q = 0; q < B_PER; ++q) {
-      const bool ok = si[q] >= 0;
-      const d2 v = *(gd2p)(base + (size_t)(ok ? si[q] : 0) * stride + 2 * k);
-      rb[q] = ok ? v : d2{0.0, 0.0};
-    }
+    for (int q = 0; q < RW; ++q)
+      v[q] = *(const GLOBAL real_t*)((const GLOBAL char*)(base + (size_t)(uint32_t)idx[q] * (uint32_t)stride) + at);
+    rw = *(gd2p)((const GLOBAL char*)w_in + wat);
+#pragma unroll
+    for (int i = 0; i < MT; ++i) wo[i] = *(gd2p)((const GLOBAL char*)w_out + 256 * i + oat);
   }
+  // the scaled terms of slot q: real parts in column q, imaginary parts in column 16 + q of the wave's 32
   template <int LDB>
-  __device__ __forceinline__ void store(int tid, double* Bs, double* Ws) const {
-    const int k = tid % Q, g = tid / Q;
-    if (g < G) {
+  __device__ __forceinline__ void store(int lane, double* Bs) const {
+    double* b = Bs + (TERM ? lane : (lane >> 1) + (lane & 1) * 16 * LDB);
+    const double wy = (TERM || (lane & 1)) ? rw.y : -rw.y;
 #pragma unroll
-      for (int q = 0; q < B_PER; ++q) {
-        const int t = g + G * q;
-        if (NT % G == 0 || t < NT) {
-          const d2 v = rb[q];
-          Bs[cx_col(t, 0) * LDB + k] = v.x * rw.x - v.y * rw.y;
-          Bs[cx_col(t, 1) * LDB + k] = v.x * rw.y + v.y * rw.x;
+    for (int q = 0; q < RW; ++q) {
+      if constexpr (TERM) {
+        const double re = v[q].x * rw.x - v[q].y * rw.y, im = v[q].x * rw.y + v[q].y * rw.x;
+        if (lane < Q) {
+          b[q * LDB] = re;
+          b[(q + 16) * LDB] = im;
         }
+      } else {
+        // even lanes: Re Re(w) - Im Im(w); odd lanes: Im Re(w) + Re Im(w)
+        const double x = v[q] * rw.x + other(v[q]) * wy;
+        if (2 * Q == 64 || lane < 2 * Q) b[q * LDB] = x;
       }
     }
-    if (tid < MP) reinterpret_cast<d2*>(Ws)[tid] = ro;
   }
-  __device__ __forceinline__ void advance(const GrgParams& p, int tid) {
-    ++s;
-    segment(p, tid);
+  // the value of lane ^ 1
+  static __device__ __forceinline__ double other(double x) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), 0xB1, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), 0xB1, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
   }
 };
+
+// The lanes of one wave exchange values through LDS: its operations run in order, so only the
+// compiler has to be kept from moving them.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
 // One k-chunk of the tile product for one wave, with the operands of k-step kk + 1 read from
 // LDS before the products of step kk issue, so that the LDS latency hides behind them. The
@@ -238,7 +262,7 @@ __device__ __forceinline__ void mfma_chunk(const double* __restrict__ Aw, const 
 // Indices the epilogue of a tile needs, loaded when its piece starts so that their latency
 // hides behind the piece's products.
 // In a factored stage column c of the tile is part (c / 16) % 2 (real, imaginary) of slot
-// (c / 32) 16 + c % 16 (the inverse of cx_col).
+// (c / 32) 16 + c % 16.
 __device__ __forceinline__ int cx_slot(int col) { return (col >> 5) * 16 + (col & 15); }
 
 template <int NT, int NTHR>
@@ -366,15 +390,14 @@ __device__ __forceinline__ void tile_epilogue(const GrgParams& p, const EpiIdx<N
 // segment of K = 256 in eight chunks), and the compiler's own choice, three blocks with the
 // accumulators in extra registers, left the pair stages 15% slower. The other
 // instantiations keep the compiler's own choice.
-// The factored M2L instantiations ask for three waves per SIMD (two for q = 40, whose
-// accumulators are half as large again); the one with waves of 32 slots is held to three
-// blocks (164 registers, no spills; the compiler's choice, 176, left two).
+// The factored M2L instantiations are held to three waves per SIMD (two for q = 40, whose
+// accumulators are half as large again).
 template <int MT, int NTT, int WM, int WN, int KC, bool CX>
 constexpr int min_blocks() {
   if (!CX && WM == 1 && WN == 4 && NTT == 1 && MT <= 4) return 4;
   if (!CX && WM == 1 && WN == 4 && NTT == 1 && KC == 16) return 3;
   if (!CX && MT == 3 && NTT == 2 && WM == 2 && WN == 2) return 4;
-  if (CX && NTT == 4) return 3;
+  if (CX && MT == 2) return 3;
   return (!CX && MT == 4 && NTT == 2 && WM == 4 && WN == 1) ? (KC == 32 ? 2 : KC == 16 ? 3 : 1) : 1;
 }
 template <int KC, bool CX>
@@ -385,7 +408,12 @@ constexpr int waves_per_simd() { return CX ? (KC == 40 ? 2 : 3) : 1; }
 // whole launch. Each chunk is one whole segment (one offset): its sources are scaled by the
 // offset's input diagonal while staged, multiplied by the core into a fresh accumulator, and the
 // product is scaled by the offset's output diagonal (a complex multiply across each lane pair)
-// as it is added to the tile's sum.
+// as it is added to the tile's sum. Bound by the matrix cores and the vector work between their
+// instructions, which share a SIMD's time: with four waves sharing staged sources across two
+// barriers per segment, index arithmetic on the vector unit and selects for empty slots, they were
+// busy 62% of the time; waves of their own slots, addresses on the scalar unit and a zero row for
+// empty slots took the 345k-leaf forest (order 31, 118k segments of 32 to 64 slots) from 861 to 719 us
+// forward and 906 to 809 adjoint, and the order-39 stage of 17k leaves from 133 to 116.
 template <int MT, int NTT, int WM, int WN, int KC, bool CX>
 __global__ void __launch_bounds__(64 * WM * WN, (min_blocks<MT, NTT, WM, WN, KC, CX>()))
 __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const GrgParams p) {
@@ -397,26 +425,27 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
   constexpr int WPART = MT * NTT * 256;  // partial-sum doubles per wave
   __shared__ double As[M * KC];
   __shared__ double Bs[NCOL * LDB];
-  __shared__ double Ws[CX ? 2 * M : 2];
   __shared__ SlotInfo<NT> slots;
   __shared__ double r1p[NTHR];
   __shared__ int last_s;
 
   __builtin_amdgcn_s_setprio(2);
   const int blk = xcd_tile(blockIdx.x, gridDim.x);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % WM, wn = wave / WM;
   const double* __restrict__ Aw = As + (wm * MT) * 64 + lane;
   const double* __restrict__ Bw = Bs + ((wn * NTT) * 16 + (lane & 15)) * LDB + (lane >> 4);
 
   const int pc0 = p.blk_ptr[blk], pc1 = p.blk_ptr[blk + 1];
-  if (CX && pc0 < pc1) {  // the core, once (made visible by the first piece's barrier)
+  static_assert(!CX || (WM == 1 && NTT == 2), "a factored wave has all rows and both parts of 16 slots");
+  if (CX && pc0 < pc1) {  // the core, once
     gd2p A2 = (gd2p)p.cx_core;
     d2* As2 = reinterpret_cast<d2*>(As);
     for (int i = tid; i < M * KC / 2; i += NTHR) As2[i] = A2[i];
   }
+  bool core_ready = false;
   for (int pc = pc0; pc < pc1; ++pc) {
-    const PieceDesc P = p.pieces[pc];
+    const PieceDesc P = scalar_load(p.pieces + pc);
     EpiIdx<NT, NTHR> ix;
     ix.load(p, P.tile, tid);
     d4 acc[MT][NTT];
@@ -424,23 +453,29 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
     for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int j = 0; j < NTT; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-    __syncthreads();  // the previous piece no longer reads LDS
+    if (!CX) __syncthreads();  // the previous piece no longer reads LDS
 
     if constexpr (CX) {
      if (P.n_chunks > 0) {
-      LoaderCX<NT, NTHR, KC, M> L;
-      L.s = P.seg;
-      L.segment(p, tid);
-      L.load(tid);
-      L.template store<LDB>(tid, Bs, Ws);
-      __syncthreads();
-      const d2* __restrict__ W2 = reinterpret_cast<const d2*>(Ws);
-      static_assert(!CX || NTT % 2 == 0, "a factored wave holds both parts of its slots");
+      LoaderCX<NT, KC, MT> L;
+      double* Bmine = Bs + wave * (32 * LDB);
+      d2 wo[MT];
+      int s = P.seg;
+      L.fetch(p, s, wave);
+      L.load(lane);
+      if (P.n_chunks > 1) L.fetch(p, ++s, wave);
+      if (!core_ready) __syncthreads();  // the core is visible
+      core_ready = true;
       for (int left = P.n_chunks;;) {
+        wave_lds_fence();  // the previous segment is read
+        L.template store<LDB>(lane, Bmine);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) wo[i] = L.wo[i];
+        wave_lds_fence();  // this one is visible
         const bool more = --left > 0;
-        if (more) {  // next segment in flight while this one is multiplied
-          L.advance(p, tid);
-          L.load(tid);
+        if (more) {  // next segment in flight while this one is multiplied, the indices of the one after it
+          L.load(lane);
+          if (left > 1) L.fetch(p, ++s, wave);
         }
         d4 part[MT][NTT];
 #pragma unroll
@@ -448,24 +483,17 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
 #pragma unroll
           for (int j = 0; j < NTT; ++j) part[i][j] = d4{0.0, 0.0, 0.0, 0.0};
         mfma_chunk<MT, NTT, M, LDB, KC>(Aw, Bw, part);
-        // acc += w_out[l] * part, complex: fragments 2j and 2j + 1 hold the real and the
-        // imaginary part of (l, slot) in the same lane
+        // acc += w_out[l] * part, complex: fragments 0 and 1 hold the real and the imaginary part of
+        // (l, slot) in the same lane
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
-          const d2 w = W2[(wm * MT + i) * 16 + (lane & 15)];
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int j = 0; j < NTT; j += 2) {
-              const double re = part[i][j][r], im = part[i][j + 1][r];
-              acc[i][j][r] = fma(w.x, re, fma(-w.y, im, acc[i][j][r]));
-              acc[i][j + 1][r] = fma(w.x, im, fma(w.y, re, acc[i][j + 1][r]));
-            }
-        }
+          for (int r = 0; r < 4; ++r) {
+            const double re = part[i][0][r], im = part[i][1][r];
+            acc[i][0][r] = fma(wo[i].x, re, fma(-wo[i].y, im, acc[i][0][r]));
+            acc[i][1][r] = fma(wo[i].x, im, fma(wo[i].y, re, acc[i][1][r]));
+          }
         if (!more) break;
-        __syncthreads();  // every wave is done reading the segment and its weights
-        L.template store<LDB>(tid, Bs, Ws);
-        __syncthreads();  // the next segment is visible
       }
      }
     } else if (P.n_chunks > 0) {
@@ -589,14 +617,10 @@ __global__ void rowsum_kernel(const double* __restrict__ x, double* __restrict__
   X(32, 64, 32, 2, 1, 1, 4, 256) X(32, 32, 32, 2, 1, 1, 2, 128) X(32, 16, 32, 2, 1, 1, 1, 64)
 
 // Factored M2L instantiations: padded core rows, slots, complex terms q (= k-chunk); MT, NTT, WM,
-// WN, threads (2 NT columns in 16-wide fragments, an even number per wave). At q = 32 the rows
-// split over two waves (16 rows each): with 32 slots (one real and one imaginary fragment per
-// wave, 114 registers, four blocks per compute unit) the order-31 M2L of the 256-tree forest
-// took 3% less time than with 32-row waves (192 registers, two blocks); with 64 slots (waves of
-// 32 slots, four fragments, three blocks) 3% less again, which the plan uses at q = 32.
+// WN, threads. A wave has all rows and both parts of 16 slots, so tiles of more slots only share the core.
 #define VP_CONFIGS_CX(X)                                                                          \
   X(48, 16, 40, 3, 2, 1, 1, 64) X(48, 32, 40, 3, 2, 1, 2, 128) X(48, 64, 40, 3, 2, 1, 4, 256)     \
-  X(32, 16, 32, 2, 2, 1, 1, 64) X(32, 32, 32, 1, 2, 2, 2, 256) X(32, 64, 32, 1, 4, 2, 2, 256)     \
+  X(32, 16, 32, 2, 2, 1, 1, 64) X(32, 32, 32, 2, 2, 1, 2, 128) X(32, 64, 32, 2, 2, 1, 4, 256)     \
   X(32, 16, 24, 2, 2, 1, 1, 64) X(32, 32, 24, 2, 2, 1, 2, 128) X(32, 64, 24, 2, 2, 1, 4, 256)     \
   X(16, 16, 16, 1, 2, 1, 1, 64) X(16, 32, 16, 1, 2, 1, 2, 128) X(16, 64, 16, 1, 2, 1, 4, 256)
 
