@@ -872,7 +872,12 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   const bool lf = lr && P.n_leaves >= kLeafFormMin;
   P.leaf_form = lf;
   const int KCL = (lr || kchunk_leaf == 16) ? 16 : 32;
-  const int NTB = (tile_box == 16 || tile_box == 32 || tile_box == 64) ? tile_box : 32;
+  // Slots per tile of the expansion stages (M2L and the chains). Up to 8192 targets 32-slot tiles do
+  // not give every compute unit one, and 16-slot tiles, cut less often, are faster: 1501 leaves M2L 47
+  // -> 27 us, chain stages 17 -> 15; 64 leaves M2L 35 -> 29. Beyond, 32 slots read the tables half as
+  // often: 22k boxes M2L 116 us (130 at 16 slots), 345k leaves 719 (850).
+  const int tile_box_opt = (tile_box == 16 || tile_box == 32 || tile_box == 64) ? tile_box : 0;
+  auto box_tile = [&](size_t targets) { return tile_box_opt ? tile_box_opt : targets <= 8192 ? 16 : 32; };
   // the expansion-row stages that read or write leaf data (K or M = 256: S2M, S2L and their
   // transposes, and the pair stages of the low-rank near field) take kLeafDataTile slots
   // The leaf stages with K = 80 (L2T, M2T and their transposes' counterparts S2M^T, S2L^T) do
@@ -906,13 +911,11 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
     for (auto& f : st.r1fam) f = {A_NONE, 0, 0};
   };
   // the factored M2L: rows of the padded core, K and the k-chunk in complex terms (one chunk a
-  // segment); the output keeps its 2q reals per box. At q = 32 the default 32-slot tiles become
-  // 64-slot ones (waves of 16 rows and 32 slots); 16 slots, which small trees tune to, stay
+  // segment); the output keeps its 2q reals per box
   auto m2l_factored = [&](Stage& st, bool adj) {
     st.cx_rel = kRelH + (adj ? kNumFwd : 0);
     st.M = mats.M[size_t(st.cx_rel)];
     st.K = st.KC = mats.K[size_t(st.cx_rel)];
-    if (st.KC == 32 && st.NT == 32) st.NT = 64;
   };
   // one launch of a leaf kernel over all leaves: reported as n_tiles segments of the kernel's table
   auto leaf_stage = [&](int kind, const char* name, int8_t custom, int rel, int K, int KC) {
@@ -1011,7 +1014,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
       if (tg.empty()) continue;
       std::string name = std::string(adj ? "AL2L[" : "M2M[") + std::to_string(l) +
                          (l - 1 >= 2 ? "," + std::to_string(l - 1) : std::string()) + "]";
-      Stage st; init_stage(st, adj ? K_AUP : K_UP, name, l, kNE, kNE, NTB, arr, kNE);
+      Stage st; init_stage(st, adj ? K_AUP : K_UP, name, l, kNE, kNE, box_tile(tg.size()), arr, kNE);
       st.fam[0] = {arr, kNE, 0};
       std::vector<std::vector<R1>> R(tg.size());
       defer(std::move(st), tg, std::move(E), std::move(R), adj);
@@ -1055,7 +1058,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
       if (!tg.empty()) {
         std::string name = std::string(adj ? "AM2M[" : "L2L[") + std::to_string(l) +
                            (l + 1 <= P.max_level ? "," + std::to_string(l + 1) : std::string()) + "]";
-        Stage st; init_stage(st, adj ? K_ADOWN : K_DOWN, name, l, kNE, kNE, NTB, tot, kNE);
+        Stage st; init_stage(st, adj ? K_ADOWN : K_DOWN, name, l, kNE, kNE, box_tile(tg.size()), tot, kNE);
         st.accumulate = 1;
         st.acc_arr = farp;
         st.fam[0] = {tot, kNE, 0}; st.fam[1] = {farp, kNE, 0};
@@ -1080,7 +1083,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
       for (auto& kv : cls) kv.second = rank++;
       std::stable_sort(tg.begin(), tg.end(), [&](int32_t x, int32_t y) { return cls[sig[size_t(x)]] < cls[sig[size_t(y)]]; });
     }
-    Stage st; init_stage(st, K_DOWN, "FARV", -1, kNE, kNE, NTB, A_FAR, kNE);
+    Stage st; init_stage(st, K_DOWN, "FARV", -1, kNE, kNE, box_tile(tg.size()), A_FAR, kNE);
     if (!dense_m2l) m2l_factored(st, false);
     st.fam[0] = {A_MP, kNE, 0};
     st.r1fam[0] = {A_MP, kNE, 0};
@@ -1417,7 +1420,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   for (int64_t a = 0; a < P.n_leaves && !P.adj_leaf_sums; ++a) P.adj_leaf_sums = levels[a] < 2;
   {  // AFARV: M2L^T plus every log term
     const auto& tg = afar_tg;
-    Stage st; init_stage(st, K_ADOWN, "AFARV", -1, kNE, kNE, NTB, A_AFAR, kNE);
+    Stage st; init_stage(st, K_ADOWN, "AFARV", -1, kNE, kNE, box_tile(tg.size()), A_AFAR, kNE);
     if (!dense_m2l) m2l_factored(st, true);
     st.fam[0] = {A_LB, kNE, 0};
     st.r1fam[0] = {A_LB, kNE, 0}; st.r1fam[1] = {A_USUM, 1, 0};
