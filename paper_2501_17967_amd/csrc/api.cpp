@@ -225,8 +225,12 @@ int schedule_all(volpot_plan_s* p, int nominal) {
         // default: a block gets at least one whole segment (K / KC chunks). A tile's fixed cost
         // (index loads, rank-one terms, the output pass) is weighted as one segment: without it,
         // blocks whose share is many one-segment tiles ran about twice as long as the others
-        // in the leaf stages
-        build_schedule(s, blocks, p->split_min != 0 ? p->split_min : s.K / s.KC, s.K / s.KC);
+        // in the leaf stages. Tiles of one wave load the next tile during the last chunk: two
+        // chunks (edge stage of 345k leaves 899 us weighted as seven, 770 as two, 760 as one), four
+        // where the output is read back to be added to.
+        const bool wave_tile = s.cx_rel < 0 && s.NT == kWaveTile && s.KC == 16 && s.M < kNP;
+        const int cost = wave_tile ? (s.accumulate ? 4 : 2) : s.K / s.KC;
+        build_schedule(s, blocks, p->split_min != 0 ? p->split_min : s.K / s.KC, cost);
       }
   } catch (const std::bad_alloc&) {
     return VOLPOT_ERR_OOM;

@@ -215,6 +215,76 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// A tile of one wave (32 slots): no other wave shares its table fragments, so they go from the L2
+// straight to registers, two k-steps ahead, and its sources through its own two LDS buffers, without a
+// barrier. The stream of chunks runs on from piece to piece: the next tile's first sources and
+// fragments are loaded during the last chunk, ahead of this tile's stores. Lane l loads the pair
+// l % 8 of each 16-term chunk of the sources l / 8 + 8 q. Bound by the matrix cores (0.72 of their
+// time at 112 rows) and, where a tile has one segment, by its stores: 345k-leaf forest, edge stage
+// 877 -> 770 us (1.4M targets, 96 rows, mostly one segment of K = 112), adjoint 910 -> 770 (345k targets,
+// 112 rows, 3.4 segments), corners 477 -> 423 and 317 -> 295, far-field pair stages 280 -> 256, 192 -> 182.
+__device__ const double kZeroRow[512] = {};  // what a slot without a source reads
+
+struct LoaderW {
+  static constexpr int LDB = 17;
+  int s, last, k0, K;
+  const double* A;     // the chunk's fragments
+  gdp src[4];          // the lane's pair of the segment's sources
+  int next_idx[4];     // its sources of the next segment
+  d2 rb[4];
+
+  static __device__ __forceinline__ void indices(const GrgParams& p, int seg, int lane, int (&idx)[4]) {
+    gip src_ = (gip)(p.seg_src + (size_t)seg * 32) + (lane >> 3);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) idx[q] = src_[8 * q];
+  }
+  // the first chunk of piece P, whose first segment has the sources idx
+  __device__ __forceinline__ void begin(const GrgParams& p, const PieceDesc& P, int M, int lane, const int (&idx)[4]) {
+    s = P.seg;
+    k0 = P.k0;
+    last = ((const CONSTANT int32_t*)p.tile_seg_ptr)[P.tile + 1] - 1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) next_idx[q] = idx[q];
+    segment(p, M, lane);
+  }
+  // start of segment s at k0, with its indices in next_idx; fetches those of the one after it
+  __device__ __forceinline__ void segment(const GrgParams& p, int M, int lane) {
+    const SegDesc sd = scalar_load(p.segs + s);
+    A = sd.A + (size_t)k0 * M;
+    K = sd.K;
+    const double* base = pick4(p.fam_base, sd.fam) + sd.k_off + k0;
+    const uint32_t stride = pick4(p.fam_stride, sd.fam);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      src[q] = (gdp)(next_idx[q] < 0 ? kZeroRow : base + (size_t)(uint32_t)next_idx[q] * stride) + 2 * (lane & 7);
+    indices(p, min(s + 1, last), lane, next_idx);
+  }
+  __device__ __forceinline__ void load() {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) rb[q] = *(gd2p)src[q];
+  }
+  __device__ __forceinline__ void store(int lane, double* Bs) const {
+    double* b = Bs + (lane >> 3) * LDB + 2 * (lane & 7);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      b[8 * q * LDB] = rb[q].x;
+      b[8 * q * LDB + 1] = rb[q].y;
+    }
+  }
+  __device__ __forceinline__ void advance(const GrgParams& p, int M, int lane) {
+    k0 += 16;
+    if (k0 >= K) {
+      ++s;
+      k0 = 0;
+      segment(p, M, lane);
+    } else {
+      A += 16 * M;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) src[q] += 16;
+    }
+  }
+};
+
 // One k-chunk of the tile product for one wave, with the operands of k-step kk + 1 read from
 // LDS before the products of step kk issue, so that the LDS latency hides behind them. The
 // scheduling barriers keep that order (left to itself, the compiler sinks the reads below the
@@ -327,28 +397,31 @@ __device__ __forceinline__ void tile_epilogue(const GrgParams& p, const EpiIdx<N
   for (int j = 0; j < NTT; j += CX ? 2 : 1) {
     // what is accumulated onto: 4 MT loads in flight before the first is used (adjoint corner stage of
     // a 345k-leaf forest: 445 -> 321 us against one row of slots at a time)
-    d2 old[4][CX ? MT : (MT + 1) / 2];
+    constexpr int RB = NT == 32 && NTHR == 64 ? 2 : 4;  // slots' rows at a time
+    d2 old[RB][CX ? MT : (MT + 1) / 2];
     int tgts[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int col = (wn * NTT + j) * 16 + 4 * r + (lane >> 4);
       tgts[r] = si.tgt[CX ? cx_slot(col) : col];
     }
+#pragma unroll
+    for (int r0 = 0; r0 < 4; r0 += RB) {
     if (p.accumulate) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
+      for (int r = r0; r < r0 + RB; ++r) {
         const double* __restrict__ o = prev + (size_t)max(tgts[r], 0) * p.out_stride;
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
           const int row = (wm * MT + i) * 16 + (lane & 15);
-          if constexpr (CX) old[r][i] = *reinterpret_cast<const d2*>(o + 2 * (row < QV ? row : 0));
-          else old[r][i / 2][i % 2] = o[row];
+          if constexpr (CX) old[r - r0][i] = *reinterpret_cast<const d2*>(o + 2 * (row < QV ? row : 0));
+          else old[r - r0][i / 2][i % 2] = o[row];
         }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int r = r0; r < r0 + RB; ++r) {
       const int col = (wn * NTT + j) * 16 + 4 * r + (lane >> 4);
       const int slot = CX ? cx_slot(col) : col;
       const int tgt = tgts[r];
@@ -362,16 +435,17 @@ __device__ __forceinline__ void tile_epilogue(const GrgParams& p, const EpiIdx<N
           d2 v = d2{acc[i][j][r], acc[i][j + 1][r]};
           if (p.r1_all_rows || row == 0) v.x += r1;
           v *= sc;
-          if (p.accumulate) v += old[r][i];
+          if (p.accumulate) v += old[r - r0][i];
           if (row < QV) *reinterpret_cast<d2*>(out + 2 * row) = v;
         } else {
           double v = acc[i][j][r];
           if (p.r1_all_rows || row == 0) v += r1;
           v *= sc;
-          if (p.accumulate) v += old[r][i / 2][i % 2];
+          if (p.accumulate) v += old[r - r0][i / 2][i % 2];
           out[row] = v;
         }
       }
+    }
     }
   }
 }
@@ -386,10 +460,11 @@ __device__ __forceinline__ void tile_epilogue(const GrgParams& p, const EpiIdx<N
 // for memory. Its k-chunk-16 form, which also runs the leaf stages that read expansions
 // (K = 64 or 80), is held to three (168 registers): those stages are latency-bound, and the
 // third block took 7% off them. The expansion-row instantiations of four 16-slot waves (up to
-// 64 rows) are held to four blocks (128 registers, no spills): their tiles are short (one
-// segment of K = 256 in eight chunks), and the compiler's own choice, three blocks with the
-// accumulators in extra registers, left the pair stages 15% slower. The other
-// instantiations keep the compiler's own choice.
+// 64 rows) are held to four blocks (128 registers): their tiles are short, and the compiler's own
+// choice, three blocks with the accumulators in extra registers, left the pair stages 15% slower. The
+// edge stage's (96 rows as 2 x 2 waves of 48 rows and 32 slots) is held to four as well, those of 80 to
+// 112 rows to three, tiles of one wave to two waves per SIMD above 48 rows (64 rows at three waves
+// spill and took 15% more) and three below. The other instantiations keep the compiler's own choice.
 // The factored M2L instantiations are held to three waves per SIMD (two for q = 40, whose
 // accumulators are half as large again).
 template <int MT, int NTT, int WM, int WN, int KC, bool CX>
@@ -398,6 +473,7 @@ constexpr int min_blocks() {
   if (!CX && WM == 1 && WN == 4 && NTT == 1 && KC == 16) return 3;
   if (!CX && MT == 3 && NTT == 2 && WM == 2 && WN == 2) return 4;
   if (CX && MT == 2) return 3;
+  if (!CX && WM == 1 && WN == 1 && NTT == 2) return MT > 3 ? 2 : 3;
   return (!CX && MT == 4 && NTT == 2 && WM == 4 && WN == 1) ? (KC == 32 ? 2 : KC == 16 ? 3 : 1) : 1;
 }
 template <int KC, bool CX>
@@ -423,8 +499,9 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
   constexpr int NTHR = 64 * WM * WN;
   constexpr int LDB = KC + 1;  // odd row stride: conflict-free B fragment reads
   constexpr int WPART = MT * NTT * 256;  // partial-sum doubles per wave
-  __shared__ double As[M * KC];
-  __shared__ double Bs[NCOL * LDB];
+  constexpr bool WAVE = !CX && WM == 1 && WN == 1 && NTT == 2;
+  __shared__ double As[WAVE ? 1 : M * KC];
+  __shared__ double Bs[(WAVE ? 2 : 1) * NCOL * LDB];
   __shared__ SlotInfo<NT> slots;
   __shared__ double r1p[NTHR];
   __shared__ int last_s;
@@ -444,6 +521,13 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
     for (int i = tid; i < M * KC / 2; i += NTHR) As2[i] = A2[i];
   }
   bool core_ready = false;
+  LoaderW L;                 // one wave's tile: the walk's state goes from piece to piece
+  double a[2][MT], b[2][2];  // its fragments of the current k-step and the next
+  bool primed = false;       // they and LDS buffer buf hold the start of the piece
+  int buf = 0;
+  auto frag = [lane](const double* A, int k, int i) {
+    return *(gdp)((const GLOBAL char*)(A + (k * MT + i) * 64) + uint32_t(8 * lane));
+  };
   for (int pc = pc0; pc < pc1; ++pc) {
     const PieceDesc P = scalar_load(p.pieces + pc);
     EpiIdx<NT, NTHR> ix;
@@ -453,7 +537,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
     for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int j = 0; j < NTT; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-    if (!CX) __syncthreads();  // the previous piece no longer reads LDS
+    if (!CX && !WAVE) __syncthreads();  // the previous piece no longer reads LDS
 
     if constexpr (CX) {
      if (P.n_chunks > 0) {
@@ -496,6 +580,62 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
         if (!more) break;
       }
      }
+    } else if constexpr (WAVE) {
+      const PieceDesc Pn = scalar_load(p.pieces + min(pc + 1, pc1 - 1));
+      const bool follow = P.n_chunks > 0 && pc + 1 < pc1 && Pn.n_chunks > 0;
+      int first_idx[4];  // sources of the next piece's first segment
+      if (follow) LoaderW::indices(p, Pn.seg, lane, first_idx);
+      if (P.n_chunks > 0) {
+        if (!primed) {
+          int idx[4];
+          LoaderW::indices(p, P.seg, lane, idx);
+          L.begin(p, P, M, lane, idx);
+          L.load();
+#pragma unroll
+          for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[k][i] = frag(L.A, k, i);
+          L.store(lane, Bs + buf * (NCOL * LDB));
+          wave_lds_fence();
+#pragma unroll
+          for (int j = 0; j < 2; ++j) b[0][j] = Bw[buf * (NCOL * LDB) + j * 16 * LDB];
+        }
+        for (int left = P.n_chunks;;) {
+          --left;
+          const double* A = L.A;
+          if (left > 0) {  // the next chunk's sources in flight, after the last those of the next piece
+            L.advance(p, M, lane);
+            L.load();
+          } else if (follow) {
+            L.begin(p, Pn, M, lane, first_idx);
+            L.load();
+          }
+          const double* A1 = L.A;
+          asm volatile("" : "+s"(A), "+s"(A1));  // opaque: the fragments' addresses stay scalar
+          const double* Bc = Bw + buf * (NCOL * LDB);
+          const double* Bn = Bw + (buf ^ 1) * (NCOL * LDB);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            if (k == 3) {
+              L.store(lane, Bs + (buf ^ 1) * (NCOL * LDB));
+              wave_lds_fence();
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) b[(k + 1) & 1][j] = k < 3 ? Bc[j * 16 * LDB + 4 * (k + 1)] : Bn[j * 16 * LDB];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+              for (int j = 0; j < 2; ++j) acc[i][j] = mfma_16x16x4(a[k & 1][i], b[k & 1][j], acc[i][j]);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[k & 1][i] = k < 2 ? frag(A, k + 2, i) : frag(A1, k - 2, i);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          buf ^= 1;
+          if (left <= 0) break;
+        }
+      }
+      primed = follow;
     } else if (P.n_chunks > 0) {
       Loader<M, NT, NTHR, KC> L;
       L.s = P.seg;
@@ -548,32 +688,36 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
       // The loads of PB pieces are all issued before the first is waited for: left to itself the
       // compiler loads one value at a time where registers are tight (edge stage of a 1501-leaf
       // tree, whose W-list tile has 55 pieces: 66 -> 25 us).
-      constexpr int NV = MT * NTT * 4, PB = NV <= 16 ? 2 : 1;
-      const double* __restrict__ part = p.partial + (size_t)P.slot0 * (M * NCOL) + wave * WPART + lane;
+      // Rows in two halves where one wave's tile leaves no registers for all of a piece.
+      constexpr int GI = WAVE ? (MT + 1) / 2 : MT, NV = GI * NTT * 4, PB = NV <= 16 ? 2 : 1;
 #pragma unroll
-      for (int i = 0; i < MT; ++i)
+      for (int i0 = 0; i0 < MT; i0 += GI) {
+        const double* __restrict__ part = p.partial + (size_t)P.slot0 * (M * NCOL) + wave * WPART + lane + i0 * (NTT * 256);
 #pragma unroll
-        for (int j = 0; j < NTT; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+        for (int i = i0; i < i0 + GI && i < MT; ++i)
+#pragma unroll
+          for (int j = 0; j < NTT; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma clang loop unroll(disable)
-      for (int q = 0; q < P.n_pieces; q += PB, part += (size_t)PB * (M * NCOL)) {
-        double v[PB][NV];
+        for (int q = 0; q < P.n_pieces; q += PB, part += (size_t)PB * (M * NCOL)) {
+          double v[PB][NV];
 #pragma unroll
-        for (int b = 0; b < PB; ++b) {
-          const double* __restrict__ src = part + (q + b < P.n_pieces ? b * (M * NCOL) : 0);
+          for (int b = 0; b < PB; ++b) {
+            const double* __restrict__ src = part + (q + b < P.n_pieces ? b * (M * NCOL) : 0);
 #pragma unroll
-          for (int k = 0; k < NV; ++k)
-            v[b][k] = __hip_atomic_load(src + k * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+            for (int k = 0; k < NV && i0 * NTT * 4 + k < MT * NTT * 4; ++k)
+              v[b][k] = __hip_atomic_load(src + k * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int b = 0; b < PB; ++b) {
-          if (b > 0 && q + b >= P.n_pieces) break;
+          for (int b = 0; b < PB; ++b) {
+            if (b > 0 && q + b >= P.n_pieces) break;
 #pragma unroll
-          for (int i = 0; i < MT; ++i)
+            for (int i = i0; i < i0 + GI && i < MT; ++i)
 #pragma unroll
-            for (int j = 0; j < NTT; ++j)
+              for (int j = 0; j < NTT; ++j)
 #pragma unroll
-              for (int r = 0; r < 4; ++r) acc[i][j][r] += v[b][(i * NTT + j) * 4 + r];
+                for (int r = 0; r < 4; ++r) acc[i][j][r] += v[b][((i - i0) * NTT + j) * 4 + r];
+          }
         }
       }
       if (tid == 0) __hip_atomic_store(p.tile_count + P.tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -607,13 +751,14 @@ __global__ void rowsum_kernel(const double* __restrict__ x, double* __restrict__
   X(256, 32, 32, 4, 2, 4, 1, 256) X(256, 64, 32, 4, 2, 4, 2, 512) X(256, 16, 16, 4, 1, 4, 1, 256) \
   X(256, 32, 16, 4, 2, 4, 1, 256) X(256, 64, 16, 4, 2, 4, 2, 512)                                 \
   X(112, 64, 16, 7, 1, 1, 4, 256) X(96, 64, 16, 3, 2, 2, 2, 256) X(80, 64, 16, 5, 1, 1, 4, 256)   \
+  X(112, 32, 16, 7, 2, 1, 1, 64) X(96, 32, 16, 6, 2, 1, 1, 64) X(80, 32, 16, 5, 2, 1, 1, 64)      \
   X(80, 64, 40, 5, 1, 1, 4, 256) X(80, 32, 40, 5, 1, 1, 2, 128) X(80, 16, 40, 5, 1, 1, 1, 64)     \
   X(80, 64, 32, 5, 1, 1, 4, 256) X(80, 32, 32, 5, 1, 1, 2, 128) X(80, 16, 32, 5, 1, 1, 1, 64)     \
-  X(64, 64, 16, 4, 1, 1, 4, 256) X(64, 32, 16, 4, 1, 1, 2, 128) X(64, 16, 16, 4, 1, 1, 1, 64)     \
+  X(64, 64, 16, 4, 1, 1, 4, 256) X(64, 32, 16, 4, 2, 1, 1, 64) X(64, 16, 16, 4, 1, 1, 1, 64)     \
   X(64, 64, 32, 4, 1, 1, 4, 256) X(64, 32, 32, 4, 1, 1, 2, 128) X(64, 16, 32, 4, 1, 1, 1, 64)     \
-  X(48, 64, 16, 3, 1, 1, 4, 256) X(48, 32, 16, 3, 1, 1, 2, 128) X(48, 16, 16, 3, 1, 1, 1, 64)     \
+  X(48, 64, 16, 3, 1, 1, 4, 256) X(48, 32, 16, 3, 2, 1, 1, 64) X(48, 16, 16, 3, 1, 1, 1, 64)     \
   X(48, 64, 32, 3, 1, 1, 4, 256) X(48, 32, 32, 3, 1, 1, 2, 128) X(48, 16, 32, 3, 1, 1, 1, 64)     \
-  X(32, 64, 16, 2, 1, 1, 4, 256) X(32, 32, 16, 2, 1, 1, 2, 128) X(32, 16, 16, 2, 1, 1, 1, 64)     \
+  X(32, 64, 16, 2, 1, 1, 4, 256) X(32, 32, 16, 2, 2, 1, 1, 64) X(32, 16, 16, 2, 1, 1, 1, 64)     \
   X(32, 64, 32, 2, 1, 1, 4, 256) X(32, 32, 32, 2, 1, 1, 2, 128) X(32, 16, 32, 2, 1, 1, 1, 64)
 
 // Factored M2L instantiations: padded core rows, slots, complex terms q (= k-chunk); MT, NTT, WM,

@@ -880,6 +880,11 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   auto box_tile = [&](size_t targets) { return tile_box_opt ? tile_box_opt : targets <= 8192 ? 16 : 32; };
   // the expansion-row stages that read or write leaf data (K or M = 256: S2M, S2L and their
   // transposes, and the pair stages of the low-rank near field) take kLeafDataTile slots
+  // In the compressed near field those stages take tiles of one wave once there are two for every
+  // SIMD (65536 targets): below, such tiles are cut along their segments to fill the chip, and 64 slots
+  // shared by four waves need fewer cuts. Edge stage of 345k leaves (1.4M targets) 877 -> 770 us, its
+  // adjoint (345k) 910 -> 770; 16.7k leaves (67k / 16.7k targets) 60 -> 61 and 66 -> 76.
+  auto data_tile = [&](size_t targets) { return lf && targets >= 65536 ? kWaveTile : kLeafDataTile; };
   // The leaf stages with K = 80 (L2T, M2T and their transposes' counterparts S2M^T, S2L^T) do
   // little work per tile: on small trees 16-slot tiles give more independent workgroups to hide
   // the latency of their few dependent k-chunks; on large trees and forests wider tiles read
@@ -1126,7 +1131,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
     std::vector<int32_t> tg;
     for (int32_t b : deep_by_quadrant) if (!Xlist[b].empty()) tg.push_back(b);
     if (!tg.empty()) {
-      Stage st; init_stage(st, K_DOWN, "FARX", -1, kNE, lf ? kOutAll : kNP, kLeafDataTile, A_FAR, kNE);
+      Stage st; init_stage(st, K_DOWN, "FARX", -1, kNE, lf ? kOutAll : kNP, data_tile(tg.size()), A_FAR, kNE);
       st.accumulate = 1;
       st.fam[0] = {int8_t(lf ? A_E : A_INS), lf ? kOutAll : kNP, 0};
       std::vector<std::vector<Entry>> E(tg.size());
@@ -1273,7 +1278,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
         for (auto& e : Wlist[size_t(a)])
           if (dir_w(e.first) / 4 == c) E[slot(dir_w(e.first) & 3)].push_back({kRelCW + e.first, 1, e.second});
       });
-      Stage st; init_stage(st, K_NEARC, c ? "NEARC48" : "NEARC", -1, c ? kCorner : kEdge, kOutAll, kLeafDataTile,
+      Stage st; init_stage(st, K_NEARC, c ? "NEARC48" : "NEARC", -1, c ? kCorner : kEdge, kOutAll, data_tile(tg.size()),
                            c ? A_HC : A_HS, c ? kCorner : kEdge);
       st.pre_near = 1;
       st.fam[0] = {A_E, kOutAll, 0};
@@ -1447,7 +1452,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
     std::vector<int32_t> tg;
     for (int32_t b : afar_tg) if (!Winv[b].empty()) tg.push_back(b);
     if (!tg.empty()) {
-      Stage st; init_stage(st, K_ADOWN, "AFARW", -1, kNE, lf ? kEdge : kNP, kLeafDataTile, A_AFAR, kNE);
+      Stage st; init_stage(st, K_ADOWN, "AFARW", -1, kNE, lf ? kEdge : kNP, data_tile(tg.size()), A_AFAR, kNE);
       st.accumulate = 1;
       if (lf) {
         st.fam[0] = {A_HSA, kEdge, 0};
@@ -1501,7 +1506,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
         if (!c)
           for (auto& e : Xinv[size_t(tg[size_t(i)])]) E[size_t(i)].push_back({kRelXE + e.first + kNumFwd, 1, e.second});
       });
-      Stage st; init_stage(st, K_ANEARC, c ? "ANEARC48" : "ANEARC", -1, kOutAll, c ? kCorner : kEdge, kLeafDataTile, A_EA, kOutAll);
+      Stage st; init_stage(st, K_ANEARC, c ? "ANEARC48" : "ANEARC", -1, kOutAll, c ? kCorner : kEdge, data_tile(tg.size()), A_EA, kOutAll);
       st.pre_near = 1;
       st.accumulate = int8_t(c);
       if (c) {
