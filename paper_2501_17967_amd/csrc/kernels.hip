@@ -689,7 +689,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
       // compiler loads one value at a time where registers are tight (edge stage of a 1501-leaf
       // tree, whose W-list tile has 55 pieces: 66 -> 25 us).
       // Rows in two halves where one wave's tile leaves no registers for all of a piece.
-      constexpr int GI = WAVE ? (MT + 1) / 2 : MT, NV = GI * NTT * 4, PB = NV <= 16 ? 2 : 1;
+      constexpr int GI = WAVE ? (MT + 1) / 2 : MT, NV = GI * NTT * 4, PB = CX && WN == 1 && NV == 24 ? 2 : NV < 32 ? 32 / NV : 1;
 #pragma unroll
       for (int i0 = 0; i0 < MT; i0 += GI) {
         const double* __restrict__ part = p.partial + (size_t)P.slot0 * (M * NCOL) + wave * WPART + lane + i0 * (NTT * 256);
@@ -746,20 +746,24 @@ __global__ void rowsum_kernel(const double* __restrict__ x, double* __restrict__
   if (lane == 0) out[leaf] = s;
 }
 
-// Every (M, NT, KC) instantiation: MT, NTT, WM, WN, KC, threads
+// Every (M, NT, KC) instantiation: MT, NTT, WM, WN, KC, threads. Tiles of 16 slots serve stages too small
+// to fill the chip, whose time is the dependent steps of one tile: their rows are shared out over the
+// waves (16 rows each; 32 of the leaf stages' 256), which divides a chunk's products, 50 to 80 in a
+// row, and the sum over a split tile's pieces by the number of waves.
 #define VP_CONFIGS(X)                                                                            \
-  X(256, 32, 32, 4, 2, 4, 1, 256) X(256, 64, 32, 4, 2, 4, 2, 512) X(256, 16, 16, 4, 1, 4, 1, 256) \
+  X(256, 32, 32, 4, 2, 4, 1, 256) X(256, 64, 32, 4, 2, 4, 2, 512) X(256, 16, 16, 2, 1, 8, 1, 512) \
   X(256, 32, 16, 4, 2, 4, 1, 256) X(256, 64, 16, 4, 2, 4, 2, 512)                                 \
   X(112, 64, 16, 7, 1, 1, 4, 256) X(96, 64, 16, 3, 2, 2, 2, 256) X(80, 64, 16, 5, 1, 1, 4, 256)   \
   X(112, 32, 16, 7, 2, 1, 1, 64) X(96, 32, 16, 6, 2, 1, 1, 64) X(80, 32, 16, 5, 2, 1, 1, 64)      \
-  X(80, 64, 40, 5, 1, 1, 4, 256) X(80, 32, 40, 5, 1, 1, 2, 128) X(80, 16, 40, 5, 1, 1, 1, 64)     \
-  X(80, 64, 32, 5, 1, 1, 4, 256) X(80, 32, 32, 5, 1, 1, 2, 128) X(80, 16, 32, 5, 1, 1, 1, 64)     \
-  X(64, 64, 16, 4, 1, 1, 4, 256) X(64, 32, 16, 4, 2, 1, 1, 64) X(64, 16, 16, 4, 1, 1, 1, 64)     \
-  X(64, 64, 32, 4, 1, 1, 4, 256) X(64, 32, 32, 4, 1, 1, 2, 128) X(64, 16, 32, 4, 1, 1, 1, 64)     \
-  X(48, 64, 16, 3, 1, 1, 4, 256) X(48, 32, 16, 3, 2, 1, 1, 64) X(48, 16, 16, 3, 1, 1, 1, 64)     \
-  X(48, 64, 32, 3, 1, 1, 4, 256) X(48, 32, 32, 3, 1, 1, 2, 128) X(48, 16, 32, 3, 1, 1, 1, 64)     \
-  X(32, 64, 16, 2, 1, 1, 4, 256) X(32, 32, 16, 2, 2, 1, 1, 64) X(32, 16, 16, 2, 1, 1, 1, 64)     \
-  X(32, 64, 32, 2, 1, 1, 4, 256) X(32, 32, 32, 2, 1, 1, 2, 128) X(32, 16, 32, 2, 1, 1, 1, 64)
+  X(112, 16, 16, 1, 1, 7, 1, 448) X(96, 16, 16, 1, 1, 6, 1, 384) X(80, 16, 16, 1, 1, 5, 1, 320)   \
+  X(80, 64, 40, 5, 1, 1, 4, 256) X(80, 32, 40, 5, 1, 1, 2, 128) X(80, 16, 40, 1, 1, 5, 1, 320)     \
+  X(80, 64, 32, 5, 1, 1, 4, 256) X(80, 32, 32, 5, 1, 1, 2, 128) X(80, 16, 32, 1, 1, 5, 1, 320)     \
+  X(64, 64, 16, 4, 1, 1, 4, 256) X(64, 32, 16, 4, 2, 1, 1, 64) X(64, 16, 16, 1, 1, 4, 1, 256)     \
+  X(64, 64, 32, 4, 1, 1, 4, 256) X(64, 32, 32, 4, 1, 1, 2, 128) X(64, 16, 32, 1, 1, 4, 1, 256)     \
+  X(48, 64, 16, 3, 1, 1, 4, 256) X(48, 32, 16, 3, 2, 1, 1, 64) X(48, 16, 16, 1, 1, 3, 1, 192)     \
+  X(48, 64, 32, 3, 1, 1, 4, 256) X(48, 32, 32, 3, 1, 1, 2, 128) X(48, 16, 32, 1, 1, 3, 1, 192)     \
+  X(32, 64, 16, 2, 1, 1, 4, 256) X(32, 32, 16, 2, 2, 1, 1, 64) X(32, 16, 16, 1, 1, 2, 1, 128)     \
+  X(32, 64, 32, 2, 1, 1, 4, 256) X(32, 32, 32, 2, 1, 1, 2, 128) X(32, 16, 32, 1, 1, 2, 1, 128)
 
 // Factored M2L instantiations: padded core rows, slots, complex terms q (= k-chunk); MT, NTT, WM,
 // WN, threads. A wave has all rows and both parts of 16 slots, so tiles of more slots only share the core.

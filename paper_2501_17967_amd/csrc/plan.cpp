@@ -865,6 +865,9 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   // ---------------------------------------------------------------- stages
   const Matrices& mats = matrices(ne / 2);
   const int NTL = (tile_leaf == 32 || tile_leaf == 64) ? tile_leaf : 32;
+  // the low-rank form's leaf stage serves trees of less than kLeafFormMin leaves: 16 slots, eight waves of
+  // 32 rows (64 leaves: 18 us, 28 with 32 slots and four waves of 64 rows)
+  const int NTLR = (tile_leaf == 32 || tile_leaf == 64) ? tile_leaf : 16;
   // k-chunk of the near-field stages; the low-rank form's segments (K = 48 or 64) take 16
   const bool lr = !layer && !dense_near;
   // compressed form of the low-rank near field (leaf.hip): the pair rows give way to what a leaf
@@ -872,19 +875,22 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   const bool lf = lr && P.n_leaves >= kLeafFormMin;
   P.leaf_form = lf;
   const int KCL = (lr || kchunk_leaf == 16) ? 16 : 32;
-  // Slots per tile of the expansion stages (M2L and the chains). Up to 8192 targets 32-slot tiles do
-  // not give every compute unit one, and 16-slot tiles, cut less often, are faster: 1501 leaves M2L 47
-  // -> 27 us, chain stages 17 -> 15; 64 leaves M2L 35 -> 29. Beyond, 32 slots read the tables half as
-  // often: 22k boxes M2L 116 us (130 at 16 slots), 345k leaves 719 (850).
+  // Slots per tile of the expansion stages (M2L and the chains). Up to 8192 targets a launch is a few
+  // dependent steps long, and tiles of 16 slots whose rows are shared out over the waves take the
+  // fewest: chain stages of 1501 leaves 11 us where 32 slots took 17, M2L 27 (47), of 64 leaves 8 (12)
+  // and 24 (35). Beyond, 32 slots read the tables half as often: M2L of 22k boxes 116 us (130 at 16
+  // slots), of the 345k-leaf forest 719 (850), its chains 448 (560).
   const int tile_box_opt = (tile_box == 16 || tile_box == 32 || tile_box == 64) ? tile_box : 0;
   auto box_tile = [&](size_t targets) { return tile_box_opt ? tile_box_opt : targets <= 8192 ? 16 : 32; };
   // the expansion-row stages that read or write leaf data (K or M = 256: S2M, S2L and their
   // transposes, and the pair stages of the low-rank near field) take kLeafDataTile slots
-  // In the compressed near field those stages take tiles of one wave once there are two for every
-  // SIMD (65536 targets): below, such tiles are cut along their segments to fill the chip, and 64 slots
+  // Up to 8192 targets they take 16-slot tiles too (64 leaves: S2M 13 us where 64 slots took 21, pair
+  // stages 13 and 12 where 20 and 17; 1501 leaves: edge stage 21 (25), far-field pair stage 14 (24)).
+  // In the compressed near field they take tiles of one wave once there are two for every SIMD
+  // (65536 targets): below, such tiles are cut along their segments to fill the chip, and 64 slots
   // shared by four waves need fewer cuts. Edge stage of 345k leaves (1.4M targets) 877 -> 770 us, its
   // adjoint (345k) 910 -> 770; 16.7k leaves (67k / 16.7k targets) 60 -> 61 and 66 -> 76.
-  auto data_tile = [&](size_t targets) { return lf && targets >= 65536 ? kWaveTile : kLeafDataTile; };
+  auto data_tile = [&](size_t targets) { return targets <= 8192 ? 16 : lf && targets >= 65536 ? kWaveTile : kLeafDataTile; };
   // The leaf stages with K = 80 (L2T, M2T and their transposes' counterparts S2M^T, S2L^T) do
   // little work per tile: on small trees 16-slot tiles give more independent workgroups to hide
   // the latency of their few dependent k-chunks; on large trees and forests wider tiles read
@@ -976,7 +982,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   if (!layer && !lf) {  // S2M: every leaf's multipole
     std::vector<int32_t> tg;
     for (int32_t b = 0; b < NB; ++b) if (P.box_leaf[b] >= 0) tg.push_back(b);
-    Stage st; init_stage(st, K_UP, "S2M", -1, kNE, kNP, kLeafDataTile, A_MP, kNE);
+    Stage st; init_stage(st, K_UP, "S2M", -1, kNE, kNP, data_tile(size_t(P.n_leaves)), A_MP, kNE);
     st.fam[0] = {A_INS, kNP, 0};
     std::vector<std::vector<Entry>> E(tg.size());
     std::vector<std::vector<R1>> R(tg.size());
@@ -1238,7 +1244,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
           E[size_t(i++)] = {entry(g, a)};
         }
     });
-    Stage st; init_stage(st, kind, name, -1, rank, kNP, kLeafDataTile, out, kNearRank);
+    Stage st; init_stage(st, kind, name, -1, rank, kNP, data_tile(tg.size()), out, kNearRank);
     st.pre_near = 1;
     st.fam[0] = {adj ? A_IN : A_INS, kNP, 0};
     std::vector<std::vector<R1>> R(tg.size());
@@ -1332,7 +1338,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   for (size_t h = 0; h < halves.size(); ++h) {  // NEAR: the adjacent-leaf tables
     const std::vector<int32_t> part(near_order.begin() + long(halves[h].first), near_order.begin() + long(halves[h].second));
     Stage st; init_stage(st, K_NEAR, halves.size() > 1 ? (h ? "NEAR_B" : "NEAR_A") : (fold ? "NEAR+LOCT" : "NEAR"), -1,
-                         kNP, lr ? 64 : kNP, NTL, A_OUT, kNP);
+                         kNP, lr ? 64 : kNP, lr ? NTLR : NTL, A_OUT, kNP);
     st.KC = KCL;
     st.fam[0] = {A_INS, kNP, 0};
     if (lr) st.fam[1] = {A_NW, kNearRank, 0};
@@ -1400,7 +1406,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
     if (lf) {  // and the cotangents of what every leaf receives
       defer(leaf_stage(K_AUP, "AL2T", C_LIN, kRelLI + kNumFwd, 64, 64), {}, {}, {}, true);
     } else if (!tg.empty()) {
-      Stage st; init_stage(st, K_AUP, "AL2T", -1, kNE, kNP, kLeafDataTile, A_LB, kNE);
+      Stage st; init_stage(st, K_AUP, "AL2T", -1, kNE, kNP, data_tile(size_t(P.n_leaves)), A_LB, kNE);
         st.fam[0] = {A_IN, kNP, 0};
       std::vector<std::vector<Entry>> E(tg.size());
       std::vector<std::vector<R1>> R(tg.size());
@@ -1529,7 +1535,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   for (size_t h = 0; h < halves.size(); ++h) {  // ANEAR: transposed near tables
     const std::vector<int32_t> part(anear_order.begin() + long(halves[h].first), anear_order.begin() + long(halves[h].second));
     Stage st; init_stage(st, K_ANEAR, halves.size() > 1 ? (h ? "ANEAR_B" : "ANEAR_A") : (fold ? "ANEAR+ALOCT" : "ANEAR"),
-                         -1, kNP, lr ? 64 : kNP, NTL, A_OUT, kNP);
+                         -1, kNP, lr ? 64 : kNP, lr ? NTLR : NTL, A_OUT, kNP);
     st.KC = KCL;
     st.out_scaled = 1;
     st.fam[0] = {A_IN, kNP, 0};
