@@ -2,12 +2,17 @@
 // launches:
 //   strip_rhs_kernel       per element and 4 rows: s_k = E_k[S, :] b_k and w_k = U~_{k-1} E_k b_k,
 //                          b_k = f * rs at the PDE rows (2m dot products of length Bi, a wave each)
-//   strip_sweep_kernel     one workgroup: the forward sweep z_{k+1} = s_k + F_k z_k, then
+//   strip_middle_kernel    block 0: the forward sweep z_{k+1} = s_k + F_k z_k, then
 //                          g_k = w_k + G_k z_k and the backward sweep t_k = g_k - H_k t_{k+1},
-//                          then the periodic corner h = K [z_n; w_0 - H_0 t_1]
+//                          then the periodic corner h = K [z_n; w_0 - H_0 t_1];
+//                          every other block: E_k b_k on a 64-row tile of an element
 //   strip_solution_kernel  per element and 64-row tile: z*_k = z_k + Pz_k h_lo,
-//                          t*_{k+1} = t_{k+1} + Pt_{k+1} h, x_k = E_k (b_k + P' z*_k - P t*_{k+1})
+//                          t*_{k+1} = t_{k+1} + Pt_{k+1} h, x_k = E_k b_k + E_k (P' z*_k - P t*_{k+1})
 //                          on the interior rows; the Dirichlet rows are zero
+// The blocks of E are most of the bytes (Bi^2 per element, 50 MB at 56 elements of 24 x 16 nodes) and wait
+// for nothing but b, so their product (14 us) runs beside the sweep, a chain in one workgroup (24 us);
+// only the 2m columns that meet z* and t* are left for the last launch: 4 + 28 + 6 us where the
+// launches took 5 + 24 + 14.
 // In the sweep, wave 0 runs the recurrence with lane a holding component a of the vector (each
 // step writes the vector to a wave-private LDS slot and reads it back as a broadcast), reading
 // its m x m matrices from LDS, while waves 1-3 stage the next chunk of matrices (double buffer,
@@ -24,7 +29,6 @@ namespace vp {
 namespace {
 
 constexpr int kStripThreads = 256;
-constexpr int kSolThreads = 512;  // solution kernel: 8 waves split the columns of a 64-row tile
 constexpr int kMaxM = 30;  // n_r <= 32
 
 __device__ __forceinline__ double lane_value(double v, int lane) {
@@ -128,8 +132,7 @@ __device__ __forceinline__ void stage(double* dst, const double* __restrict__ sr
 }
 
 template <int m>
-__global__ void __launch_bounds__(kStripThreads) strip_sweep_kernel(StripDevice d) {
-  extern __shared__ double sm[];
+__device__ __forceinline__ void strip_sweep(const StripDevice& d, double* sm) {
   // a chunk buffer holds C matrices (m x m each) followed by C vectors (m each)
   const int n = d.n, C = d.chunk, mm = m * m, st = mm + m;
   // buffer i of the double buffer, computed from the LDS base so that the accesses stay LDS
@@ -229,40 +232,31 @@ __global__ void __launch_bounds__(kStripThreads) strip_sweep_kernel(StripDevice 
   }
 }
 
-__global__ void __launch_bounds__(kSolThreads)
-    strip_solution_kernel(StripDevice d, const double* __restrict__ f, double* __restrict__ x) {
-  extern __shared__ double sm[];  // r (Bi), z* (m), t* (m), partial sums (kSolThreads)
-  const int k = blockIdx.x, tile = blockIdx.y, q = d.q, Bi = d.Bi, m = d.m, B = d.B;
-  double* r = sm;
-  double* zs = r + Bi;
-  double* ts = zs + m;
-  double* red = ts + m;
+template <int m>
+__global__ void __launch_bounds__(kStripThreads)
+    strip_middle_kernel(StripDevice d, const double* __restrict__ f, double* __restrict__ x) {
+  extern __shared__ double sm[];  // the sweep's buffers; r (Bi) and partial sums (kStripThreads)
+  if (blockIdx.x == 0) {
+    strip_sweep<m>(d, sm);
+    return;
+  }
+  // E_k b_k on 64 rows, the waves sharing the columns
+  constexpr int kWaves = kStripThreads / 64;
+  const int q = d.q, Bi = d.Bi, B = d.B, tiles = (Bi + 63) / 64;
+  const int k = (blockIdx.x - 1) / tiles, tile = (blockIdx.x - 1) % tiles;
+  double *r = sm, *red = sm + Bi;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  if (tid < m) {
-    const double* P = d.Pz + size_t(k) * m * m + size_t(tid) * m;
-    double v = d.z[size_t(k) * m + tid];
-    for (int b = 0; b < m; ++b) v = fma(P[b], d.h[b], v);
-    zs[tid] = v;
-  } else if (tid >= 64 && tid < 64 + m) {
-    const int a = tid - 64, m2 = 2 * m;
-    const double* P = d.Pt + size_t(k + 1) * m * m2 + size_t(a) * m2;
-    double v = d.t[size_t(k + 1) * m + a];
-    for (int j = 0; j < m2; ++j) v = fma(P[j], d.h[j], v);
-    ts[a] = v;
-  }
-  __syncthreads();
   const size_t base = size_t(k) * B + q;
-  for (int c = tid; c < Bi; c += kSolThreads) {
-    const int j = c % q, a = c / q;
-    r[c] = j == 0 ? zs[a] : (j == q - 1 ? -ts[a] : f[base + c] * d.rs[base + c]);
+  for (int c = tid; c < Bi; c += kStripThreads) {
+    const int j = c % q;
+    r[c] = (j != 0 && j != q - 1) ? f[base + c] * d.rs[base + c] : 0.0;
   }
   __syncthreads();
-  constexpr int kWaves = kSolThreads / 64;
   const int p = tile * 64 + lane, per = (Bi + kWaves - 1) / kWaves, c0 = wave * per, c1 = min(Bi, c0 + per);
   double acc = 0.0;
   if (p < Bi) {
     const double* E = d.EiT + size_t(k) * Bi * Bi + p;
-#pragma unroll 8
+#pragma unroll 16
     for (int c = c0; c < c1; ++c) acc = fma(E[size_t(c) * Bi], r[c], acc);
   }
   red[tid] = acc;
@@ -274,6 +268,49 @@ __global__ void __launch_bounds__(kSolThreads)
     x[base + p] = v;
   }
   if (tile == 0 && tid < 2 * q) x[size_t(k) * B + (tid < q ? tid : B - 2 * q + tid)] = 0.0;
+}
+
+__global__ void __launch_bounds__(kStripThreads) strip_solution_kernel(StripDevice d, double* __restrict__ x) {
+  __shared__ double zt[64], red[kStripThreads];  // z*, -t*; partial sums
+  const int k = blockIdx.x, tile = blockIdx.y, q = d.q, Bi = d.Bi, m = d.m, m2 = 2 * m;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  constexpr int kWaves = kStripThreads / 64, kCols = (2 * kMaxM + kWaves - 1) / kWaves;
+  const int p = tile * 64 + lane;
+  const size_t at = size_t(k) * d.B + q + min(p, Bi - 1);
+  // the wave's columns of E and the row's E_k b_k, in flight while the corner's terms are formed
+  const double* E = d.EiT + size_t(k) * Bi * Bi + min(p, Bi - 1);
+  double e[kCols];
+#pragma unroll
+  for (int i = 0; i < kCols; ++i) {
+    const int o = wave + i * kWaves;
+    if (o < m2) e[i] = E[size_t(o < m ? o * q : (o - m) * q + q - 1) * Bi];
+  }
+  const double eb = x[at];
+  for (int o = tid >> 5; o < m2; o += kStripThreads / 32) {  // 32 lanes per component
+    const int b = tid & 31;
+    const bool lo = o < m;
+    const double* P = lo ? d.Pz + (size_t(k) * m + o) * m : d.Pt + (size_t(k + 1) * m + (o - m)) * m2;
+    const int len = lo ? m : m2;
+    double v = b < len ? P[b] * d.h[b] : 0.0;
+    if (b + 32 < len) v = fma(P[b + 32], d.h[b + 32], v);
+    for (int s = 16; s > 0; s >>= 1) v += __shfl_xor(v, s, 32);
+    if (b == 0) zt[o] = lo ? d.z[size_t(k) * m + o] + v : -(d.t[size_t(k + 1) * m + (o - m)] + v);
+  }
+  __syncthreads();
+  double acc = 0.0;
+#pragma unroll
+  for (int i = 0; i < kCols; ++i) {
+    const int o = wave + i * kWaves;
+    if (o < m2) acc = fma(e[i], zt[o], acc);
+  }
+  red[tid] = acc;
+  __syncthreads();
+  if (wave == 0 && p < Bi) {
+    double v = eb;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) v += red[w * 64 + lane];
+    x[at] = v;
+  }
 }
 
 // Work vectors of the apply (s, w, z, t, h) for callers that cannot allocate: one static array
@@ -304,21 +341,22 @@ hipError_t strip_scratch(double** out) {
 
 hipError_t launch_strip_solve(const StripDevice& d, const double* f, double* v, hipStream_t stream) {
   if (d.m < 2 || d.m > kMaxM) return hipErrorInvalidValue;  // the plan keeps 4 <= n_r <= 32
-  const size_t lds_sweep = (size_t(2) * d.chunk * (d.m * d.m + d.m) + 32) * sizeof(double);
+  const size_t sweep = size_t(2) * d.chunk * (d.m * d.m + d.m) + 32, product = size_t(d.Bi) + kStripThreads;
   hipLaunchKernelGGL(strip_rhs_kernel, dim3(unsigned(d.n), unsigned((2 * d.m + 3) / 4)), dim3(kStripThreads),
                      size_t(d.Bi) * sizeof(double), stream, d, f);
-  using Sweep = void (*)(StripDevice);
-  static const Sweep sweeps[kMaxM + 1] = {
-      nullptr, nullptr, strip_sweep_kernel<2>, strip_sweep_kernel<3>, strip_sweep_kernel<4>, strip_sweep_kernel<5>,
-      strip_sweep_kernel<6>, strip_sweep_kernel<7>, strip_sweep_kernel<8>, strip_sweep_kernel<9>, strip_sweep_kernel<10>,
-      strip_sweep_kernel<11>, strip_sweep_kernel<12>, strip_sweep_kernel<13>, strip_sweep_kernel<14>,
-      strip_sweep_kernel<15>, strip_sweep_kernel<16>, strip_sweep_kernel<17>, strip_sweep_kernel<18>,
-      strip_sweep_kernel<19>, strip_sweep_kernel<20>, strip_sweep_kernel<21>, strip_sweep_kernel<22>,
-      strip_sweep_kernel<23>, strip_sweep_kernel<24>, strip_sweep_kernel<25>, strip_sweep_kernel<26>,
-      strip_sweep_kernel<27>, strip_sweep_kernel<28>, strip_sweep_kernel<29>, strip_sweep_kernel<30>};
-  hipLaunchKernelGGL(sweeps[d.m], dim3(1), dim3(kStripThreads), lds_sweep, stream, d);
-  hipLaunchKernelGGL(strip_solution_kernel, dim3(unsigned(d.n), unsigned((d.Bi + 63) / 64)), dim3(kSolThreads),
-                     size_t(d.Bi + 2 * d.m + kSolThreads) * sizeof(double), stream, d, f, v);
+  using Middle = void (*)(StripDevice, const double*, double*);
+  static const Middle middle[kMaxM + 1] = {
+      nullptr, nullptr, strip_middle_kernel<2>, strip_middle_kernel<3>, strip_middle_kernel<4>, strip_middle_kernel<5>,
+      strip_middle_kernel<6>, strip_middle_kernel<7>, strip_middle_kernel<8>, strip_middle_kernel<9>, strip_middle_kernel<10>,
+      strip_middle_kernel<11>, strip_middle_kernel<12>, strip_middle_kernel<13>, strip_middle_kernel<14>,
+      strip_middle_kernel<15>, strip_middle_kernel<16>, strip_middle_kernel<17>, strip_middle_kernel<18>,
+      strip_middle_kernel<19>, strip_middle_kernel<20>, strip_middle_kernel<21>, strip_middle_kernel<22>,
+      strip_middle_kernel<23>, strip_middle_kernel<24>, strip_middle_kernel<25>, strip_middle_kernel<26>,
+      strip_middle_kernel<27>, strip_middle_kernel<28>, strip_middle_kernel<29>, strip_middle_kernel<30>};
+  const unsigned tiles = unsigned((d.Bi + 63) / 64);
+  hipLaunchKernelGGL(middle[d.m], dim3(1 + unsigned(d.n) * tiles), dim3(kStripThreads),
+                     (sweep > product ? sweep : product) * sizeof(double), stream, d, f, v);
+  hipLaunchKernelGGL(strip_solution_kernel, dim3(unsigned(d.n), tiles), dim3(kStripThreads), 0, stream, d, v);
   return hipGetLastError();
 }
 
