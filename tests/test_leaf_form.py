@@ -1,0 +1,146 @@
+"""The compressed near field (plans of 512 leaves and more) and the tile sizes chosen by the number of a
+stage's targets, against the general path: the dense near field and the dense M2L of the same plan.
+
+Tolerance: the compressed tables reproduce the dense ones to 3e-15 of their norm, a leaf has at
+most 13 adjacent leaves and twelve W or X partners, and the far field is the same map summed in
+another order: 25 x 3e-15 < 1e-13 of the output's norm.
+"""
+import numpy as np
+import pytest
+
+from workloads import gen
+
+KLEAF = 512   # leaves from which a plan takes the compressed form
+
+
+def _uniform(level):
+    n = 1 << level
+    return {(level, x, y) for x in range(n) for y in range(n)}
+
+
+def _random(seed, n_splits, max_level):
+    # splits without balancing in between: one final balance, coarse leaves beside deep ones
+    rng = np.random.default_rng(seed)
+    leaves = [(1, x, y) for x in (0, 1) for y in (0, 1)]
+    for _ in range(n_splits):
+        cand = [i for i, k in enumerate(leaves) if k[0] < max_level]
+        l, x, y = leaves.pop(cand[int(rng.integers(len(cand)))])
+        leaves += [(l + 1, 2 * x + a, 2 * y + b) for a in (0, 1) for b in (0, 1)]
+    return gen.balance(set(leaves))
+
+
+def _corner():
+    # one quadrant of four level-2 leaves, graded against the others' level 5
+    return gen.balance({(2, x, y) for x in (0, 1) for y in (0, 1)} |
+                       {(5, x, y) for x in range(32) for y in range(32) if not (x < 16 and y < 16)})
+
+
+def _plan_data(trees, seed):
+    C, L, off = [], [], [0]
+    rng = np.random.default_rng(seed)
+    for leaves in trees:
+        keys = sorted(leaves)
+        rng.shuffle(keys)
+        k = np.array(keys, dtype=np.int64)
+        h = 1.0 / (1 << k[:, 0]).astype(np.float64)   # half width on [-1, 1]^2
+        C.append(np.stack([-1 + (2 * k[:, 1] + 1) * h, -1 + (2 * k[:, 2] + 1) * h], axis=1))
+        L.append(k[:, 0].astype(np.int32))
+        off.append(off[-1] + len(keys))
+    return np.vstack(C), np.concatenate(L), off
+
+
+CASES = {
+    "uniform-1024": lambda: [_uniform(5)],
+    "random": lambda: [_random(3, 260, 9)],
+    "coarse-quadrant": lambda: [_corner()],
+    "forest-ragged": lambda: [_random(5, 150, 7), _uniform(4), _random(6, 140, 10)],
+    "wave-tiles": lambda: [_uniform(7), _random(7, 400, 9), _uniform(6)],
+}
+
+
+@pytest.fixture(scope="module")
+def vp():
+    from paper_2501_17967_amd import volpot
+    return volpot
+
+
+def test_compressed_stages_take_every_adjacent_pair_once(vp):
+    # without W lists the edge and corner stages' flops count the pairs across edges and corners, each
+    # once, forward (96 or 48 received values from 112 outgoing ones) and adjoint
+    for level in (5, 6):
+        n = 1 << level
+        C, L, off = _plan_data([_uniform(level)], level)
+        plan = vp.Plan(C, L, host_only=True)
+        for adj, names in ((False, ("NEARC", "NEARC48")), (True, ("ANEARC", "ANEARC48"))):
+            st = {s["name"]: s for s in plan.stages(adj)}
+            assert st[names[0]]["flops"] == 2 * 96 * 112 * 4 * n * (n - 1)
+            assert st[names[1]]["flops"] == 2 * 48 * 112 * 4 * (n - 1) ** 2
+        assert plan.info()["pairs_lowrank"] == 4 * n * (n - 1) + 4 * (n - 1) ** 2
+        plan.close()
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_tiles_follow_the_number_of_targets(vp, name):
+    # 16 slots up to 8192 targets; beyond, 32 for the expansion stages, and for the compressed near field
+    # 64, or 32 (tiles of one wave) from 65536 targets on. A given tile_box is kept.
+    trees = CASES[name]()
+    C, L, off = _plan_data(trees, 1)
+    assert len(L) >= KLEAF
+    kw = {"tree_offsets": off} if len(trees) > 1 else {}
+    seen = set()
+    for given in (0, 16, 32, 64):
+        plan = vp.Plan(C, L, host_only=True, tile_box=given, **kw)
+        for s in plan.stages() + plan.stages(adjoint=True):
+            if s["kind"] in ("nearc", "adj_nearc") or s["name"] in ("FARX", "AFARW"):
+                want = (16, 64, 32)
+            elif s["kind"] in ("up", "down", "adj_up", "adj_down") and s["name"] not in ("S2M", "AL2T"):
+                want = (given,) if given else (16, 32)
+            else:
+                continue
+            assert s["tile"] in want, s
+            seen.add(s["tile"])
+            # the number of tiles bounds the number of targets from both sides
+            lo, hi = (s["n_tiles"] - 1) * s["tile"], s["n_tiles"] * s["tile"]
+            if len(want) > 1:
+                if s["tile"] == 16:
+                    assert lo < 8192, s
+                elif len(want) == 3 and s["tile"] == 32:
+                    assert hi >= 65536, s
+                else:
+                    assert hi > 8192 and (len(want) == 2 or lo < 65536), s
+        plan.close()
+    assert seen >= {16, 32, 64}
+
+
+def rel(a, b):
+    return float(np.max(np.abs(a - b)) / np.max(np.abs(b)))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("eps", [0.0, 1e-9, 1e-6])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_compressed_form_matches_dense_tables(vp, name, eps):
+    import torch
+    if name == "wave-tiles" and eps == 1e-9:
+        eps = 1e-11
+    trees = CASES[name]()
+    C, L, off = _plan_data(trees, 2)
+    kw = {"tree_offsets": off} if len(trees) > 1 else {}
+    print("case", name, "eps", eps, len(L), "leaves", flush=True)
+    rng = np.random.default_rng(11)
+    x = [torch.from_numpy(rng.standard_normal((len(L), 256))).cuda() for _ in range(3)]
+    ref = vp.Plan(C, L, eps=eps, dense_near=True, dense_m2l=True, **kw)
+    want = [(ref.apply(v).cpu().numpy(), ref.apply_adjoint(v).cpu().numpy()) for v in x]
+    ref.close()
+    plan = vp.Plan(C, L, eps=eps, use_graph=True, **kw)
+    assert "NEAR+LOCT" in [s["name"] for s in plan.stages()]
+    buf, out, outa = torch.empty_like(x[0]), torch.empty_like(x[0]), torch.empty_like(x[0])
+    for v, (u, a) in zip(x, want):   # the second and third pass replay the captured graphs on new values
+        buf.copy_(v)
+        plan.apply(buf, out=out)
+        plan.apply_adjoint(buf, out=outa)
+        torch.cuda.synchronize()
+        ef, ea = rel(out.cpu().numpy(), u), rel(outa.cpu().numpy(), a)
+        print("  forward %.1e adjoint %.1e" % (ef, ea), flush=True)
+        assert ef <= 1e-13 and ea <= 1e-13
+    plan.close()
