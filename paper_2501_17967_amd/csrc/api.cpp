@@ -229,7 +229,13 @@ int schedule_all(volpot_plan_s* p, int nominal) {
         // chunks (edge stage of 345k leaves 899 us weighted as seven, 770 as two, 760 as one), four
         // where the output is read back to be added to.
         const bool wave_tile = s.cx_rel < 0 && s.NT == kWaveTile && s.KC == 16 && s.M < kNP;
-        const int cost = wave_tile ? (s.accumulate ? 4 : 2) : s.K / s.KC;
+        // 16-slot tiles: two (rows shared out over the waves, little to write; layer potential of 22.7k
+        // leaves, leaf stage 62 us weighted as five, 51 as two); 64-slot ones of k-chunk 16: three (corner
+        // stage of 16.7k leaves 38 us as seven, 35 as three).
+        const int per_seg = s.K / s.KC;
+        const int cost = wave_tile ? (s.accumulate ? 4 : 2)
+                         : s.NT == 16 ? std::min(per_seg, 2)
+                         : s.NT == 64 && s.KC == 16 && s.M < kNP ? std::min(per_seg, 3) : per_seg;
         build_schedule(s, blocks, p->split_min != 0 ? p->split_min : s.K / s.KC, cost);
       }
   } catch (const std::bad_alloc&) {
