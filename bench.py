@@ -47,7 +47,7 @@ def kernel_source_hash():
     (their ranks set the near field's segments) and the plan and scheduling code that cut the
     work into launches."""
     h = hashlib.sha256()
-    for f in ("kernels.hip", "device.hpp", "plan.cpp", "plan.hpp", "tables.cpp", "api.cpp"):
+    for f in ("kernels.hip", "leaf.hip", "device.hpp", "plan.cpp", "plan.hpp", "tables.cpp", "api.cpp"):
         with open(os.path.join(ROOT, "paper_2501_17967_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -341,8 +341,9 @@ def _near_roofline(plan, info, steps, f, ubar, u, fbar, traffic, timed_in):
                                         "frac": traffic / (avg_ms * 1e-3) / PEAK_HBM}
     return {"bound": "mfma", "achieved": achieved / 1e12, "peak": PEAK_FP64_MFMA / 1e12, "unit": "TFLOP/s",
             "frac": achieved / PEAK_FP64_MFMA, "traffic": traffic, "hbm": hbm,
-            "kernel": "grg_kernel, 256-row tiles of %d slots, k-chunk %d: %s (forward) and %s (adjoint)"
-                      % (near[0]["tile"], near[0]["kchunk"], near[0]["name"],
+            "kernel": "%s, 256-row tiles of %d slots, k-chunk %d: %s (forward) and %s (adjoint)"
+                      % ("leaf_out_kernel" if near[0]["inner"] > 64 and near[0]["name"] == "NEAR+LOCT" else "grg_kernel",
+                         near[0]["tile"], near[0]["kchunk"], near[0]["name"],
                          [s["name"] for s in plan.stages(True) if s["kind"] == "adj_near"][0]),
             "flops_per_launch": flops, "avg_launch_ms": avg_ms, "launches": n, "launches_per_step": per_step,
             "timed_in": timed_in}, 1e3 * t_pass / steps
@@ -516,7 +517,7 @@ def forest_leg(args, dev):
     print("bench: sequential single-tree applies", file=sys.stderr, flush=True)
     t0 = time.perf_counter()
     order = np.argsort(sizes, kind="stable")
-    cands = [{"tile_leaf": 32, "tile_box": 32, "split_min": 0, "overlap": 0, "tile_leaf_exp": 16, "kchunk_leaf": 32}]
+    cands = [{}, {"tile_leaf": 32, "tile_box": 32, "split_min": 0, "overlap": 0, "tile_leaf_exp": 16, "kchunk_leaf": 32}]
     for part in np.array_split(order, 8):
         med = trees[int(part[len(part) // 2])]
         sh, _ = autotune(med.centres, med.levels, eps=args.eps, dense_m2l=args.dense_m2l, dense_near=args.dense_near)

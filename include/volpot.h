@@ -63,13 +63,15 @@ typedef struct {
   int32_t use_graph;       /* 1: capture each apply once per (input, output) pointer pair into
                               a hipGraph and replay it. Default 0. */
   int32_t tile_leaf;       /* slots per tile of the near-field stages (256 rows): 32 or 64;
-                              0 = default (32). The 256-row stages with K = 80 take
-                              tile_leaf_exp. */
+                              0 = default (32; 16 in the low-rank form). The 256-row stages with
+                              K = 80 take tile_leaf_exp. Plans of 512 leaves and more have no
+                              such stage unless dense_near is set. */
   int32_t tile_box;        /* slots per tile of the expansion translation stages (M2M, L2L
-                              chains, M2L): 16, 32 or 64; 0 = default (32). The expansion
-                              stages whose other side is leaf data (S2M, S2L, their transposes,
-                              the low-rank near field's pair stages) take 64, and so does the
-                              factored M2L at expansion order 31 in place of 32. */
+                              chains, M2L): 16, 32 or 64; 0 = default (16 up to 8192 targets of
+                              the stage, 32 beyond). The stages whose other side is leaf data
+                              (S2M, S2L, their transposes, the near field's pair, edge and
+                              corner stages) take 16 up to 8192 targets, 64 beyond, and in plans
+                              of 512 leaves and more 32 (one wave's) from 65536 on. */
   const char* table_cache; /* directory for the host table cache; NULL = keep tables in memory */
   int32_t split_min;       /* each stage is cut into as many equal shares of its k-chunks as the
                               device runs blocks at once; a share has at least this many chunks
@@ -124,8 +126,13 @@ typedef struct {
                               corner and coarser neighbours): stages NEARC / NEARC48 form V_r f
                               for every such pair (64 values a pair in plan memory), the near
                               field then applies U_r to those and the self table to the leaf's
-                              own data, about half the dense matrix-core work. 1: the dense
-                              tables. The two agree to rounding (the tests compare them). */
+                              own data, about half the dense matrix-core work. Plans of 512
+                              leaves and more take the compressed form instead: 112 outgoing
+                              values a leaf, what it receives as 96 values across each edge and
+                              48 across each corner, every table on a leaf's own values in four
+                              blocks by its symmetries; the same stage names, a quarter of the
+                              dense work. 1: the dense tables. All agree to rounding (the tests
+                              compare them). */
 } volpot_options;
 
 /* Algorithmic work of one apply, from the plan's exact pair counts. Flops are 2 x the
@@ -142,8 +149,10 @@ typedef struct {
                                M2T^T, M2M^T chain), 6 adjoint near field, 7 S2M^T + S2L^T,
                                8 adjoint row sums (plans with leaves above level 2 only),
                                9 the low-rank near field's first stage (V_r f per pair), 10 its
-                               transpose's (U_r^T ubar per pair). The low-rank near field folds
-                               kinds 3 and 7 into kinds 2 and 6 (stages NEAR+LOCT, ANEAR+ALOCT). */
+                               transpose's (U_r^T ubar per pair); in the compressed form what the
+                               leaves receive across edges and corners, and its transpose. Both
+                               forms fold kinds 3 and 7 into kinds 2 and 6 (stages NEAR+LOCT,
+                               ANEAR+ALOCT). */
   int64_t launches_kind[11]; /* kernel launches per apply of each stage kind */
   double bytes_min;         /* mandatory HBM traffic: 16 B per unknown (f in, u out) */
   int64_t device_bytes;     /* device memory the plan holds (tables shared per device) */
@@ -346,7 +355,7 @@ int volpot_plan_table(volpot_plan_t plan, int32_t kind, int32_t index, double* o
 /* Autotuner (for callers that apply one tree shape many times, e.g. batched forests): searches
  * the launch shapes tile_box 16|32|64, tile_leaf 32|64, kchunk_leaf 32|16 and tile_leaf_exp
  * 16|32|64 (these two with dense_near only), split_min 0|1|-1 and overlap 0|16|24|32|48 one knob
- * at a time from the defaults (the other fields, eps among them, are taken from base,
+ * at a time from 32, 32, 32, 16, 0 and 0 (the other fields, eps among them, are taken from base,
  * nullable), building a plan for each candidate (the defaults' and the current choice's are
  * kept for timing again) and timing one forward plus one adjoint apply on internal device
  * buffers after a warm-up (HIP events, private stream, best of 5); writes the fastest options

@@ -1,6 +1,6 @@
 // HIP kernels of the box code for gfx950 (CDNA4), FP64 throughout.
 //
-// One kernel template serves every stage: a grouped-relation GEMM. A workgroup owns a tile of
+// One kernel template serves every stage but the leaf kernels (leaf.hip): a grouped-relation GEMM. A workgroup owns a tile of
 // NT output vectors ("slots") of M rows each and walks the relation segments present in the
 // tile (sorted by relation id). For relation r it accumulates
 //     C[:, slot] += A_r[:, k-chunk] * B[k-chunk, slot]

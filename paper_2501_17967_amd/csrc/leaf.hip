@@ -77,9 +77,12 @@ constexpr int kThreads = 256;
 // A tile's 256 x 32 parity sums sit in LDS (row stride 65: conflict-free operand reads). The
 // forward form has 48 rows per part: wave p keeps part p's 48 x 64 table in registers for the
 // whole launch and the next tile's values are loaded while this one is multiplied; it is bound by
-// the 2 KB read and 1.4 KB written per leaf. The adjoint form has 160 or 176 rows per part: the
-// waves share out the groups of 16 rows, each group with all four parts (whose sums its results
-// need), and stream the table's fragments from the L2.
+// the 2 KB read and 1.4 KB written per leaf (345k leaves: 266 us, 4.4 TB/s; it takes the place of a
+// 256-column S2M stage and a prescale pass of 225 us). The adjoint form has 160 or 176 rows per part:
+// the waves share out the groups of 16 rows, each group with all four parts (whose sums its results
+// need), and stream the table's fragments from the L2 two k-steps ahead. 7 KB a leaf and the
+// products each take about half of its time (345k leaves: 745 us, 3.2 TB/s, matrix cores busy half the
+// time; four waves that shared out whole tiles 977, six waves 874, 16-leaf tiles 789).
 constexpr int kLdIn = 65;
 
 __device__ __forceinline__ void in_load(const LeafParams& p, int tile, int tid, Raw (&r)[4], double (&sc)[4]) {
@@ -262,7 +265,9 @@ __global__ void __launch_bounds__(kAdjThreads, 4) leaf_in_adj_kernel(const LeafP
 // are between its own accumulators. No two waves read the same table fragment, so those go from the
 // L2 straight to registers, each refilled for the next chunk as soon as it has been multiplied; only
 // the 4 x 16 values of 32 leaves go through LDS, in two buffers, one barrier per chunk. (Staged
-// through LDS as well, the fragments took LDS to 56% of the matrix cores' time.) Every kind of column
+// through LDS as well, the fragments took LDS to 56% of the matrix cores' time.) 9 KB a leaf and the
+// products each take about half of its time: 345k leaves 1000 us forward (3.1 TB/s, matrix cores busy
+// 51%), 545 adjoint (with 256-column tables over leaves and pair rows 3370 either way, 356k leaves). Every kind of column
 // is four raw pairs per thread and sums of them: mirrored nodes, the two edges or four corners that
 // the parts add or subtract, or an expansion's reals.
 constexpr int kLdOut = 17;

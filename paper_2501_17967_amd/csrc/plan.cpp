@@ -424,6 +424,8 @@ static void make_tiles_ordered(Stage& st, const std::vector<int32_t>& targets,
 // field, which does not depend on the far field. The low-rank near field, folded with the leaf
 // stage into one stage that needs the far field, puts its pair stages there instead:
 //   S2M, M2M chain (helper), NEARC, FARV (join), FARX, L2L chain (helper), NEARC48, NEAR+LOCT (join)
+// The compressed near field has the same order; its NEARC (ANEARC) reads multipoles (cotangents of
+// locals), so the join comes before it.
 // Without overlap everything runs in this order on one stream, which is also a valid order. A
 // layer plan has P2M in S2M's place, P2L in FARX's, and its direct sum P2P, which adds onto
 // LOCT's output, last.

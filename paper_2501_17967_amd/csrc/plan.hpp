@@ -21,9 +21,24 @@
 //             ANEAR    fbar = s^2 sum_U T_r^T ubar                         (main, concurrent)
 //             ALOCT    fbar += s^2 [S2M^T abar + sum_X S2L_r^T lbar]       (main, after join)
 //
-// All relations of one stage share the inner dimension K (80 for expansions, 256 for leaf
-// values), which the k-chunk KC of the stage's kernel divides, so the kernel's chunks are
-// always full. Rank-one log-scale terms (ln s_l times a box mass) are folded into the
+// Volume plans apply the tables between different leaves through factors. Low-rank form (less than
+// kLeafFormMin leaves): NEARC and NEARC48 form V_r f for every adjacent pair, and one launch NEAR+LOCT
+// adds the self table, U_r of the pair rows and the leaf stage. Compressed form (leaf.hip):
+//
+//   forward   S2M        e, mp = the leaf's 112 outgoing values and its multipole
+//             NEARC      h  = sum C_r e + sum_W C_r mp   the 96 values received across each edge
+//             FARX       loc += sum_X X_r e
+//             NEARC48    h  = sum C_r e + sum_W C_r mp   the 48 across each corner
+//             NEAR+LOCT  u  = T_0 f + H h + L2T loc      all leaves
+//   adjoint   AL2T       hbar, lbar = H^T ubar, L2T^T ubar
+//             ANEARC     ebar = sum C_r^T hbar + sum_X X_r^T lbar   (edges)
+//             AFARW      abar += sum_W C_r^T hbar
+//             ANEARC48   ebar += sum C_r^T hbar                     (corners)
+//             ANEAR+ALOCT fbar = s^2 [T_0^T ubar + E^T ebar + S2M^T abar]
+//
+// Relations of one stage have inner dimensions K (an expansion's reals, 256 leaf values, 112
+// outgoing, 96 or 48 received) that the k-chunk KC of the stage's kernel divides, so the kernel's
+// chunks are always full. Rank-one log-scale terms (ln s_l times a box mass) are folded into the
 // epilogues of FARV, LOCT and AFARV. Stages run in this order on the caller's stream; with the
 // overlap option, the stages marked (helper) run on a plan-owned helper stream instead,
 // concurrently with the near field, which depends on nothing but f, and LOCT waits for both.
@@ -167,7 +182,11 @@ struct FamDesc { int8_t arr; int32_t stride; int8_t unused; };
 enum Custom : int8_t { C_NONE = 0, C_P2M, C_P2L, C_P2P, C_LIN, C_LOUT };
 constexpr int kWaveTile = 32;  // slots of a tile of one wave
 constexpr int kLeafTile = 32;  // leaves per tile of the leaf kernels
-// Volume plans of at least this many leaves take the compressed near field.
+// Volume plans of at least this many leaves take the compressed near field. The larger the tree the more
+// it saves (1501 leaves forward 364 -> 276 us, 345k leaves forward and adjoint 14.9 -> 10.1 ms, with the
+// kernels of the time); below, both forms take as long as their launches' dependent steps (forward and
+// adjoint, 256 leaves: 236 us compressed, 239 low-rank; 442: 354, 408; 1024: 289, 297), and the low-rank
+// form stays, in which every adjacent pair keeps a row of its own.
 constexpr int64_t kLeafFormMin = 512;
 
 // One piece of a stage's work as run by one block: n_chunks consecutive k-chunks of one tile,
