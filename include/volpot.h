@@ -153,7 +153,8 @@ typedef struct {
                                leaves receive across edges and corners, and its transpose. Both
                                forms fold kinds 3 and 7 into kinds 2 and 6 (stages NEAR+LOCT,
                                ANEAR+ALOCT). */
-  int64_t launches_kind[11]; /* kernel launches per apply of each stage kind */
+  int64_t launches_kind[11]; /* kernel launches per apply of each stage kind (small stages that
+                               share a launch count one each; they run apart while timed) */
   double bytes_min;         /* mandatory HBM traffic: 16 B per unknown (f in, u out) */
   int64_t device_bytes;     /* device memory the plan holds (tables shared per device) */
   double flops_issued_kind[11]; /* matrix-core work the kernels issue per stage kind: every tile

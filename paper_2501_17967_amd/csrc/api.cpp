@@ -236,7 +236,7 @@ int schedule_all(volpot_plan_s* p, int nominal) {
         const int cost = wave_tile ? (s.accumulate ? 4 : 2)
                          : s.NT == 16 ? std::min(per_seg, 2)
                          : s.NT == 64 && s.KC == 16 && s.M < kNP ? std::min(per_seg, 3) : per_seg;
-        build_schedule(s, blocks, p->split_min != 0 ? p->split_min : s.K / s.KC, cost);
+        build_schedule(s, blocks, p->split_min != 0 ? p->split_min : per_seg, cost, per_seg);
       }
   } catch (const std::bad_alloc&) {
     return VOLPOT_ERR_OOM;
@@ -246,10 +246,52 @@ int schedule_all(volpot_plan_s* p, int nominal) {
   return VOLPOT_OK;
 }
 
+// Small stages that can share a launch: 16-slot tiles of one k-chunk on the caller's stream (no overlap),
+// where nothing from the first on writes what a later one reads or touches what it writes. In trees of
+// less than kLeafFormMin leaves S2M and the pair stages read the leaves alone (three launches of 12 to
+// 13 us each become one of 15 at 64 leaves); in the compressed form the edge and corner stages.
+void group_launches(std::vector<Stage>& v) {
+  auto reads = [](const Stage& s, int8_t arr) {
+    for (const FamDesc& f : s.fam) if (f.arr == arr) return true;
+    for (const FamDesc& f : s.r1fam) if (f.arr == arr) return true;
+    return s.accumulate && (s.acc_arr == arr || s.out_arr == arr);
+  };
+  auto apart = [](const Stage& a, const Stage& b) {  // no row of the output in both (the pair stages)
+    std::vector<int32_t> x;
+    for (int32_t t : a.tile_tgt) if (t >= 0) x.push_back(t);
+    std::sort(x.begin(), x.end());
+    return std::none_of(b.tile_tgt.begin(), b.tile_tgt.end(), [&](int32_t t) { return t >= 0 && std::binary_search(x.begin(), x.end(), t); });
+  };
+  auto small = [](const Stage& s) { return s.custom == C_NONE && s.cx_rel < 0 && s.NT == 16 && s.n_tiles > 0; };
+  for (size_t i = 0; i < v.size(); ++i) {
+    Stage& a = v[i];
+    if (!small(a) || a.follows) continue;
+    std::vector<int> with;
+    int M[3] = {a.M, 0, 0};
+    for (size_t j = i + 1; j < v.size() && with.size() < 2; ++j) {
+      const Stage& b = v[j];
+      if (v[j - 1].custom != C_NONE) break;
+      bool free = small(b) && b.KC == a.KC && !b.follows && b.with.empty();
+      for (size_t k = i; k < j && free; ++k)
+        if (reads(b, v[k].out_arr) || reads(v[k], b.out_arr) || (v[k].out_arr == b.out_arr && !apart(v[k], b))) free = false;
+      if (!free) continue;
+      M[1 + with.size()] = b.M;
+      with.push_back(int(j));
+    }
+    if (with.empty() || !grg_group(a.KC, M, 1 + int(with.size()))) continue;
+    a.with = with;
+    for (int j : with) v[size_t(j)].follows = true;
+  }
+}
+
 int upload(volpot_plan_s* p) {
   Plan& P = p->host;
   int rc = schedule_all(p, 0);
   if (rc != VOLPOT_OK) return rc;
+  if (p->overlap == 0) {
+    group_launches(P.fwd);
+    group_launches(P.adj);
+  }
   size_t total = 0;
   const size_t nb = (size_t(P.n_boxes) + 1) * P.ne * sizeof(double);  // the row after the last box stays zero
   struct Off { size_t tt, tsp, sd, ss, rp, ri, rf, rc, pc, bp, tc, ct, cp, ci; };
@@ -419,6 +461,7 @@ int upload(volpot_plan_s* p) {
   for (auto* v : {&P.fwd, &P.adj})
     for (const Stage& s : *v) {
       size_t need = size_t(s.n_slots) * s.M * s.NT * (s.cx_rel >= 0 ? 2 : 1) * sizeof(double);
+      for (int k : s.with) need += size_t((*v)[size_t(k)].n_slots) * (*v)[size_t(k)].M * (*v)[size_t(k)].NT * sizeof(double);
       part[s.helper ? 0 : 1] = std::max(part[s.helper ? 0 : 1], need);
     }
   for (int i = 0; i < 2; ++i)
@@ -509,6 +552,35 @@ void timed_end(volpot_plan_s* p, int kind, hipStream_t st, hipEvent_t ea, hipEve
   }
 }
 
+// The launch arguments of one grouped-product stage.
+GrgParams stage_params(volpot_plan_s* p, const DevStage& d, const double* in, double* out) {
+  const Stage& s = *d.st;
+  GrgParams g;
+  std::memset(&g, 0, sizeof(g));
+  g.tile_tgt = d.tile_tgt; g.tile_seg_ptr = d.tile_seg_ptr; g.segs = d.segs; g.seg_src = d.seg_src;
+  for (int f = 0; f < 4; ++f) {
+    g.fam_base[f] = arr_ptr(p, s.fam[f].arr, in, out);
+    g.fam_stride[f] = s.fam[f].stride;
+  }
+  g.leaf_s2 = p->d_leaf_s2;
+  g.r1_ptr = d.r1_ptr; g.r1_idx = d.r1_idx; g.r1_fam = d.r1_fam; g.r1_coef = d.r1_coef;
+  for (int f = 0; f < 3; ++f) {
+    g.r1_base[f] = arr_ptr(p, s.r1fam[f].arr, in, out);
+    g.r1_stride[f] = s.r1fam[f].stride;
+  }
+  g.out = const_cast<double*>(arr_ptr(p, s.out_arr, in, out));
+  g.out_stride = s.out_stride;
+  g.out_scaled = s.out_scaled;
+  g.r1_all_rows = s.r1_all_rows;
+  g.accumulate = s.accumulate;
+  g.acc_src = s.acc_arr == A_NONE ? nullptr : arr_ptr(p, s.acc_arr, in, out);
+  g.pieces = d.pieces; g.blk_ptr = d.blk_ptr; g.tile_count = d.tile_count;
+  g.partial = p->d_part[s.helper ? 0 : 1];  // helper-marked stages never share a buffer with the others
+  g.n_blocks = s.n_blocks;
+  g.cx_core = s.cx_rel >= 0 ? p->tables->rels[size_t(s.cx_rel)].A : nullptr;
+  return g;
+}
+
 // The whole apply: every stage in plan order on the caller's stream. With the overlap option,
 // a stage marked fork_before makes the plan's helper stream wait for the caller's stream, the
 // stages marked helper then run on it (the far-field chains) while the caller's stream goes on
@@ -574,29 +646,27 @@ int run(volpot_plan_s* p, bool adjoint, const double* in, const double* in2, dou
       if (e != hipSuccess) return VOLPOT_ERR_HIP;
       continue;
     }
-    GrgParams g;
-    std::memset(&g, 0, sizeof(g));
-    g.tile_tgt = d.tile_tgt; g.tile_seg_ptr = d.tile_seg_ptr; g.segs = d.segs; g.seg_src = d.seg_src;
-    for (int f = 0; f < 4; ++f) {
-      g.fam_base[f] = arr_ptr(p, s.fam[f].arr, in, out);
-      g.fam_stride[f] = s.fam[f].stride;
+    if (!timing && s.follows) continue;  // ran with an earlier stage
+    if (!timing && !s.with.empty()) {
+      GrgGroup gr;
+      std::memset(&gr, 0, sizeof(gr));
+      int M[3] = {s.M, 0, 0}, n = 1;
+      gr.p[0] = stage_params(p, d, in, out);
+      size_t at = size_t(s.n_slots) * s.M * s.NT;  // the partial sums of the stages lie behind one another
+      for (int k : s.with) {
+        const Stage& o = *stages[size_t(k)].st;
+        M[n] = o.M;
+        gr.p[n] = stage_params(p, stages[size_t(k)], in, out);
+        gr.p[n++].partial += at;
+        at += size_t(o.n_slots) * o.M * o.NT;
+      }
+      roctxRangePushA(s.name.c_str());
+      const hipError_t e = launch_grg_group(s.KC, M, n, gr, st);
+      roctxRangePop();
+      if (e != hipSuccess) return VOLPOT_ERR_HIP;
+      continue;
     }
-    g.leaf_s2 = p->d_leaf_s2;
-    g.r1_ptr = d.r1_ptr; g.r1_idx = d.r1_idx; g.r1_fam = d.r1_fam; g.r1_coef = d.r1_coef;
-    for (int f = 0; f < 3; ++f) {
-      g.r1_base[f] = arr_ptr(p, s.r1fam[f].arr, in, out);
-      g.r1_stride[f] = s.r1fam[f].stride;
-    }
-    g.out = const_cast<double*>(arr_ptr(p, s.out_arr, in, out));
-    g.out_stride = s.out_stride;
-    g.out_scaled = s.out_scaled;
-    g.r1_all_rows = s.r1_all_rows;
-    g.accumulate = s.accumulate;
-    g.acc_src = s.acc_arr == A_NONE ? nullptr : arr_ptr(p, s.acc_arr, in, out);
-    g.pieces = d.pieces; g.blk_ptr = d.blk_ptr; g.tile_count = d.tile_count;
-    g.partial = p->d_part[s.helper ? 0 : 1];  // helper-marked stages never share a buffer with the others
-    g.n_blocks = s.n_blocks;
-    g.cx_core = s.cx_rel >= 0 ? p->tables->rels[size_t(s.cx_rel)].A : nullptr;
+    const GrgParams g = stage_params(p, d, in, out);
     hipEvent_t ea, eb;
     timed_begin(p, timing, s.kind, st, &ea, &eb);
     roctxRangePushA(s.name.c_str());  // a host range per stage, named as in volpot_plan_stage

@@ -73,6 +73,9 @@ struct GrgParams {
   const double* cx_core;        // factored stages: the core table (fragment-major, M x K)
 };
 
+// Up to three stages of one launch (see launch_grg_group).
+struct GrgGroup { GrgParams p[3]; };
+
 // Blocks of the grouped-product kernel for (M, NT, KC, factored) that fit on the current device
 // at once (0 on error).
 int grg_resident_blocks(int M, int NT, int KC, bool factored = false);
@@ -81,6 +84,10 @@ int grg_resident_blocks(int M, int NT, int KC, bool factored = false);
 // complex diagonals): M = the padded core rows, KC = the complex terms q, 2 NT columns.
 // hipErrorInvalidValue for a shape without an instantiation.
 hipError_t launch_grg(int M, int NT, int KC, bool factored, const GrgParams& p, hipStream_t stream);
+// Two or three stages of 16-slot tiles that do not depend on one another, with rows M[i] and one
+// k-chunk, in one launch; grg_group tells whether there is an instantiation.
+bool grg_group(int KC, const int* M, int n);
+hipError_t launch_grg_group(int KC, const int* M, int n, const GrgGroup& g, hipStream_t stream);
 // out = s2[leaf] * x  (n_leaves x 256)
 hipError_t launch_prescale(const double* x, const double* s2, double* out, int64_t n_leaves, hipStream_t stream);
 // usum[a] = sum of the 256 values of leaf a

@@ -491,8 +491,7 @@ constexpr int waves_per_simd() { return CX ? (KC == 40 ? 2 : 3) : 1; }
 // empty slots took the 345k-leaf forest (order 31, 118k segments of 32 to 64 slots) from 861 to 719 us
 // forward and 906 to 809 adjoint, and the order-39 stage of 17k leaves from 133 to 116.
 template <int MT, int NTT, int WM, int WN, int KC, bool CX>
-__global__ void __launch_bounds__(64 * WM * WN, (min_blocks<MT, NTT, WM, WN, KC, CX>()))
-__attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const GrgParams p) {
+__device__ __forceinline__ void grg_block(const GrgParams& p, int blk) {
   constexpr int M = 16 * MT * WM;
   constexpr int NCOL = 16 * NTT * WN;
   constexpr int NT = CX ? NCOL / 2 : NCOL;  // slots
@@ -507,7 +506,6 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
   __shared__ int last_s;
 
   __builtin_amdgcn_s_setprio(2);
-  const int blk = xcd_tile(blockIdx.x, gridDim.x);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % WM, wn = wave / WM;
   const double* __restrict__ Aw = As + (wm * MT) * 64 + lane;
@@ -726,6 +724,34 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
   }
 }
 
+template <int MT, int NTT, int WM, int WN, int KC, bool CX>
+__global__ void __launch_bounds__(64 * WM * WN, (min_blocks<MT, NTT, WM, WN, KC, CX>()))
+__attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const GrgParams p) {
+  grg_block<MT, NTT, WM, WN, KC, CX>(p, xcd_tile(blockIdx.x, gridDim.x));
+}
+
+// Small stages that do not depend on one another in one launch (16-slot tiles, W waves of 16 rows
+// each; a block of a stage with fewer waves than the launch's ends the others at once). Such a launch
+// takes as long as its longest stage, where one after another they took the sum.
+template <int KC, int W0, int W1, int W2>
+__global__ void __launch_bounds__(64 * (W0 > W1 ? W0 : W1)) grg_group_kernel(const GrgGroup g) {
+  int b = blockIdx.x;
+  const int wave = threadIdx.x >> 6;
+  if (b < g.p[0].n_blocks) {
+    if (wave < W0) grg_block<1, 1, W0, 1, KC, false>(g.p[0], xcd_tile(b, g.p[0].n_blocks));
+    return;
+  }
+  b -= g.p[0].n_blocks;
+  if (b < g.p[1].n_blocks) {
+    if (wave < W1) grg_block<1, 1, W1, 1, KC, false>(g.p[1], xcd_tile(b, g.p[1].n_blocks));
+    return;
+  }
+  if constexpr (W2 > 0) {
+    b -= g.p[1].n_blocks;
+    if (wave < W2) grg_block<1, 1, W2, 1, KC, false>(g.p[2], xcd_tile(b, g.p[2].n_blocks));
+  }
+}
+
 // out[leaf][k] = s2[leaf] * x[leaf][k]  (the s^2 Jacobian of each source leaf, applied once)
 __global__ void prescale_kernel(const double* __restrict__ x, const double* __restrict__ s2, double* __restrict__ out,
                                 int64_t n_leaves) {
@@ -790,6 +816,29 @@ hipError_t launch_grg(int M, int NT, int KC, bool factored, const GrgParams& p, 
   }
   VP_CONFIGS_CX(VP_LAUNCH_CX)
 #undef VP_LAUNCH_CX
+  return hipErrorInvalidValue;
+}
+
+// Launch groups: KC, rows / 16 of each stage (0: two stages).
+#define VP_GROUPS(X) X(32, 5, 4, 3) X(32, 4, 4, 3) X(32, 3, 4, 3) X(32, 2, 4, 3) X(16, 6, 3, 0)
+
+bool grg_group(int KC, const int* M, int n) {
+#define VP_HAS(kc, a, b, c) \
+  if (KC == kc && n == 2 + (c > 0) && M[0] == 16 * a && M[1] == 16 * b && (c == 0 || M[2] == 16 * c)) return true;
+  VP_GROUPS(VP_HAS)
+#undef VP_HAS
+  return false;
+}
+
+hipError_t launch_grg_group(int KC, const int* M, int n, const GrgGroup& g, hipStream_t stream) {
+  const dim3 grid(unsigned(g.p[0].n_blocks + g.p[1].n_blocks + (n > 2 ? g.p[2].n_blocks : 0)));
+#define VP_LAUNCH_GROUP(kc, a, b, c)                                                                               \
+  if (KC == kc && n == 2 + (c > 0) && M[0] == 16 * a && M[1] == 16 * b && (c == 0 || M[2] == 16 * c)) {            \
+    hipLaunchKernelGGL((grg_group_kernel<kc, a, b, c>), grid, dim3(64 * (a > b ? a : b)), 0, stream, g);           \
+    return hipGetLastError();                                                                                      \
+  }
+  VP_GROUPS(VP_LAUNCH_GROUP)
+#undef VP_LAUNCH_GROUP
   return hipErrorInvalidValue;
 }
 

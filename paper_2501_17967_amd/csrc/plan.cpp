@@ -494,7 +494,7 @@ static void arrange_stages(std::vector<Stage>& v, bool adjoint) {
   for (Stage& s : last) v.push_back(std::move(s));
 }
 
-void build_schedule(Stage& st, int max_blocks, int min_units, int tile_cost) {
+void build_schedule(Stage& st, int max_blocks, int min_units, int tile_cost, int block_cost) {
   const int T = st.n_tiles;
   st.pieces.clear();
   st.blk_ptr.assign(1, 0);
@@ -516,7 +516,8 @@ void build_schedule(Stage& st, int max_blocks, int min_units, int tile_cost) {
   // min_units < 0: one block per tile, no tile cut
   const bool whole = min_units < 0;
   const int64_t mu = std::max(1, min_units);
-  const int64_t G = whole ? T : std::max<int64_t>(1, std::min<int64_t>(std::max(1, max_blocks), (U + mu - 1) / mu));
+  const int64_t Ub = U + int64_t(T) * (std::max(0, block_cost) - std::max(0, tile_cost));
+  const int64_t G = whole ? T : std::max<int64_t>(1, std::min<int64_t>(std::max(1, max_blocks), (Ub + mu - 1) / mu));
   // first unit of block b; a boundary inside a tile's fixed-cost units moves to the tile's end
   auto first = [&](int64_t b) {
     if (whole) return tu[b];

@@ -144,3 +144,24 @@ def test_compressed_form_matches_dense_tables(vp, name, eps):
         print("  forward %.1e adjoint %.1e" % (ef, ea), flush=True)
         assert ef <= 1e-13 and ea <= 1e-13
     plan.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("eps", [0.0, 1e-11, 1e-9, 1e-6])
+@pytest.mark.parametrize("n_splits", [0, 1, 20, 120, 200])
+def test_grouped_launches_match_separate_ones(vp, n_splits, eps):
+    # stages that share a launch run apart while they are timed: the same pieces in the same order, so
+    # the same bits
+    import torch
+    C, L, off = _plan_data([_random(n_splits, n_splits, 8)], 3)
+    print("case", n_splits, "splits, eps", eps, len(L), "leaves", flush=True)
+    f = torch.from_numpy(np.random.default_rng(n_splits).standard_normal((len(L), 256))).cuda()
+    plan = vp.Plan(C, L, eps=eps)
+    out = {}
+    for timed in (False, True, False):
+        plan.set_timing(timed)
+        got = (plan.apply(f).cpu().numpy(), plan.apply_adjoint(f).cpu().numpy())
+        if out:
+            assert np.array_equal(got[0], out[0]) and np.array_equal(got[1], out[1])
+        out = got
+    plan.close()
