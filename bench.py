@@ -497,7 +497,7 @@ def forest_leg(args, dev):
                       "leaves_min": int(sizes.min()), "leaves_max": int(sizes.max()), "max_level": int(info["max_level"]),
                       "p": 16, "far_field_eps": args.eps, "expansion_order": int(info["order"]),
                       "m2l": "dense" if args.dense_m2l else "factored",
-                      "near": "dense" if args.dense_near else "rank-64/48 factors of the non-self tables",
+                      "near": "dense" if args.dense_near else "compressed: 112 outgoing values a leaf, 96 / 48 received per edge / corner",
                       "step": "forward + adjoint, one hipGraph replay each",
                       "launch_shape": shape, "autotune_s": t_tune, "plan_s": t_plan, "gen_s": t_gen,
                       "plan_device_gb": info["device_bytes"] / 1e9},
