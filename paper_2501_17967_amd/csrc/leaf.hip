@@ -271,9 +271,14 @@ __global__ void __launch_bounds__(kAdjThreads, 4) leaf_in_adj_kernel(const LeafP
 // is four raw pairs per thread and sums of them: mirrored nodes, the two edges or four corners that
 // the parts add or subtract, or an expansion's reals.
 constexpr int kLdOut = 17;
+// Up to this many leaves a launch is one tile's chain of chunks, each as long as its loads take. There
+// tiles of 16 leaves (H = 1) leave the registers to keep two chunks in flight: 1501 leaves forward 34
+// -> 23 us, adjoint 20 -> 13. At 16.7k leaves both take 78 and 38; beyond, 32 leaves (H = 2) read the
+// fragments half as often.
+constexpr int kOutSmall = 8192;
 constexpr int kCorner0 = (64 + kEdge) / 16;  // first chunk of the corners' columns
 
-template <bool ADJ>
+template <bool ADJ, int SLOTS>
 struct OutLoader {
   Raw r;
   // the raw pairs of chunk c for leaf first + slot, term pair starting at o = 2 m
@@ -350,31 +355,34 @@ struct OutLoader {
     const int slot = tid >> 3, k = 2 * (tid & 7);
 #pragma unroll
     for (int pt = 0; pt < 4; ++pt) {
-      double* b = Bs + (pt * kSlots + slot) * kLdOut + k;
+      double* b = Bs + (pt * SLOTS + slot) * kLdOut + k;
       b[0] = r.v[pt].x;
       b[1] = r.v[pt].y;
     }
   }
 };
 
-template <bool ADJ>
+template <bool ADJ, int H>
 __global__ void __launch_bounds__(kThreads, 3) leaf_out_kernel(const LeafParams p) {
+  constexpr int kSlots = 16 * H;
   __shared__ double Bs[2][4 * kSlots * kLdOut];
   __shared__ double r1s_[2][kSlots];  // of even and of odd tiles: a fast wave forms the next tile's while this one's are read
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int blk = leaf_block(blockIdx.x, gridDim.x);
-  const int t0 = (int)((int64_t)blk * p.n_tiles / gridDim.x), t1 = (int)((int64_t)(blk + 1) * p.n_tiles / gridDim.x);
+  const int n_tiles = (p.n_leaves + kSlots - 1) / kSlots;
+  const int t0 = (int)((int64_t)blk * n_tiles / gridDim.x), t1 = (int)((int64_t)(blk + 1) * n_tiles / gridDim.x);
+  const bool stages = (tid >> 3) < kSlots;  // this thread stages values
   const int n_chunks = p.n_chunks;
   const int b_at = (lane & 15) * kLdOut + (lane >> 4);
   for (int tile = t0; tile < t1; ++tile) {
     const int first = tile * kSlots, last = p.n_leaves - 1 - first;
     double* r1s = r1s_[tile & 1];
-    const bool ok = (tid >> 3) <= last;            // this thread stages values of a leaf, not of an empty slot
-    const int slot = min(tid >> 3, last), leaf = first + slot;
+    const bool ok = stages && (tid >> 3) <= last;  // and of a leaf, not of an empty slot
+    const int slot = min(min(tid >> 3, kSlots - 1), last), leaf = first + slot;
     const int box = ok ? p.loc_box[leaf] : -1;
     const double scale = ok ? (p.s2_in ? p.leaf_s2[leaf] : 1.0) : 0.0;
-    OutLoader<ADJ> L;
-    L.load(p, 0, first, slot, box, tid);
+    OutLoader<ADJ, kSlots> L, M;  // M: with 16 leaves a second chunk in flight
+    if (stages) L.load(p, 0, first, slot, box, tid);
     if (!ADJ) {  // the leaf's log terms, summed by its eight threads in a fixed order
       double c = 0.0;
       if (ok)
@@ -383,13 +391,13 @@ __global__ void __launch_bounds__(kThreads, 3) leaf_out_kernel(const LeafParams 
       c += __shfl_xor(c, 1, 64);
       c += __shfl_xor(c, 2, 64);
       c += __shfl_xor(c, 4, 64);
-      if ((tid & 7) == 0) r1s[tid >> 3] = c;
+      if (stages && (tid & 7) == 0) r1s[tid >> 3] = c;
     }
-    d4 acc[4][2];
+    d4 acc[4][H];
 #pragma unroll
     for (int pt = 0; pt < 4; ++pt)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[pt][j] = d4{0.0, 0.0, 0.0, 0.0};
+      for (int j = 0; j < H; ++j) acc[pt][j] = d4{0.0, 0.0, 0.0, 0.0};
     double a[4][4];  // fragments [k-step][part] of the current chunk
     int a_off = wave * 64;  // of the current chunk's fragments
     const uint32_t a_at = 8 * lane;
@@ -397,11 +405,18 @@ __global__ void __launch_bounds__(kThreads, 3) leaf_out_kernel(const LeafParams 
     for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
       for (int pt = 0; pt < 4; ++pt) a[kk][pt] = value_at(p.table + a_off + (kk * 16 + pt * 4) * 64, a_at);
-    L.store(0, scale, tid, Bs[0]);
-    if (n_chunks > 1) L.load(p, 1, first, slot, box, tid);
+    if (stages) {
+      L.store(0, scale, tid, Bs[0]);
+      if (H == 2) {
+        if (n_chunks > 1) L.load(p, 1, first, slot, box, tid);
+      } else {
+        if (n_chunks > 1) M.load(p, 1, first, slot, box, tid);
+        if (n_chunks > 2) L.load(p, 2, first, slot, box, tid);
+      }
+    }
     __syncthreads();
-#pragma clang loop unroll(disable)
-    for (int c = 0; c < n_chunks; ++c) {
+    // chunk c: multiply it, stage the next one from X and load the one `ahead` into X
+    auto step = [&](int c, OutLoader<ADJ, kSlots>& X, int ahead) {
       const bool more = c + 1 < n_chunks;
       const double* __restrict__ Bw = Bs[c & 1] + b_at;
       a_off += more ? 256 * 16 : 0;  // the last chunk reloads its own fragments
@@ -413,22 +428,32 @@ __global__ void __launch_bounds__(kThreads, 3) leaf_out_kernel(const LeafParams 
 #pragma unroll
         for (int pt = 0; pt < 4; ++pt) {
           acc[pt][0] = mfma_16x16x4(a[kk][pt], Bw[pt * kSlots * kLdOut + 4 * kk], acc[pt][0]);
-          acc[pt][1] = mfma_16x16x4(a[kk][pt], Bw[(pt * kSlots + 16) * kLdOut + 4 * kk], acc[pt][1]);
+          if constexpr (H == 2) acc[pt][1] = mfma_16x16x4(a[kk][pt], Bw[(pt * kSlots + 16) * kLdOut + 4 * kk], acc[pt][1]);
         }
 #pragma unroll
         for (int pt = 0; pt < 4; ++pt) a[kk][pt] = value_at(A + (kk * 16 + pt * 4) * 64, a_at);
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (more) {
-        L.store(c + 1, scale, tid, Bs[(c + 1) & 1]);
-        if (c + 2 < n_chunks) L.load(p, c + 2, first, slot, box, tid);
+      if (more && stages) {
+        X.store(c + 1, scale, tid, Bs[(c + 1) & 1]);
+        if (c + ahead < n_chunks) X.load(p, c + ahead, first, slot, box, tid);
       }
       __syncthreads();  // the next chunk is visible, this one is read
+    };
+    if constexpr (H == 2) {
+#pragma clang loop unroll(disable)
+      for (int c = 0; c < n_chunks; ++c) step(c, L, 2);
+    } else {
+#pragma clang loop unroll(disable)
+      for (int c = 0; c < n_chunks; c += 2) {
+        step(c, M, 3);
+        if (c + 1 < n_chunks) step(c + 1, L, 3);
+      }
     }
     // row 16 w + l % 16 of each part: node row j = 2 w + l % 16 / 8, column i = l % 8
     const int j = 2 * wave + ((lane & 15) >> 3), i = lane & 7;
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < H; ++h)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int s = 16 * h + 4 * q + (lane >> 4), lf = tile * kSlots + s;
@@ -449,7 +474,7 @@ __global__ void __launch_bounds__(kThreads, 3) leaf_out_kernel(const LeafParams 
 static int leaf_threads(bool out, bool adjoint) { return !out && adjoint ? kAdjThreads : kThreads; }
 static const void* leaf_kernel(bool out, bool adjoint) {
   if (out)
-    return adjoint ? reinterpret_cast<const void*>(&leaf_out_kernel<true>) : reinterpret_cast<const void*>(&leaf_out_kernel<false>);
+    return adjoint ? reinterpret_cast<const void*>(&leaf_out_kernel<true, 2>) : reinterpret_cast<const void*>(&leaf_out_kernel<false, 2>);
   return adjoint ? reinterpret_cast<const void*>(&leaf_in_adj_kernel) : reinterpret_cast<const void*>(&leaf_in_kernel);
 }
 
@@ -472,9 +497,15 @@ hipError_t launch_leaf_in(const LeafParams& p, bool adjoint, int n_blocks, hipSt
 
 hipError_t launch_leaf_out(const LeafParams& p, bool adjoint, int n_blocks, hipStream_t stream) {
   if (p.n_tiles <= 0) return hipSuccess;
+  if (p.n_leaves <= kOutSmall) {
+    const int tiles16 = (p.n_leaves + 15) / 16;
+    if (adjoint) hipLaunchKernelGGL((leaf_out_kernel<true, 1>), dim3(unsigned(tiles16)), dim3(kThreads), 0, stream, p);
+    else hipLaunchKernelGGL((leaf_out_kernel<false, 1>), dim3(unsigned(tiles16)), dim3(kThreads), 0, stream, p);
+    return hipGetLastError();
+  }
   const dim3 grid(unsigned(n_blocks < p.n_tiles ? n_blocks : p.n_tiles));
-  if (adjoint) hipLaunchKernelGGL(leaf_out_kernel<true>, grid, dim3(kThreads), 0, stream, p);
-  else hipLaunchKernelGGL(leaf_out_kernel<false>, grid, dim3(kThreads), 0, stream, p);
+  if (adjoint) hipLaunchKernelGGL((leaf_out_kernel<true, 2>), grid, dim3(kThreads), 0, stream, p);
+  else hipLaunchKernelGGL((leaf_out_kernel<false, 2>), grid, dim3(kThreads), 0, stream, p);
   return hipGetLastError();
 }
 
