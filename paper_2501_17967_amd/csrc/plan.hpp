@@ -126,9 +126,9 @@ const std::vector<Offset>& v_offsets();     // 40, in half-widths (rho 1)
 const std::vector<Offset>& w_offsets();     // 20 (rho 1/2)
 const std::vector<Offset>& x_offsets();     // 20 (rho 2)
 int find_offset(const std::vector<Offset>& v, double dx, double dy, double rho);
-// Where a source box at (dx, dy) of half-width rho (target half-widths) lies from the reference
-// target: across its right, left, upper, lower edge (0..3) or its upper right, upper left, lower
-// right, lower left corner (4..7); -1 when it overlaps the target.
+// Where the compressed near field receives a source box at (dx, dy) of half-width rho (target
+// half-widths): across the target's right, left, upper, lower edge (0..3) or its upper right, upper left,
+// lower right, lower left corner (4..7; boxes on a diagonal only); -1 when the box overlaps the target.
 int near_dir(double dx, double dy, double rho);
 
 // ---------------------------------------------------------------- matrices

@@ -850,15 +850,14 @@ static std::vector<double> s2m_table(int Q) {
   return R;
 }
 
+// Boxes on a diagonal are a corner's; the others are the edge's of their larger coordinate, also where they
+// lie wholly to the side of it (W boxes at (1.5, 2.5) and its images).
 int near_dir(double dx, double dy, double rho) {
-  // the edge of the reference target that the source touches or faces: its near face lies at or
-  // beyond that edge
-  const int x = dx - rho >= 1.0 - 1e-9 ? 1 : dx + rho <= -1.0 + 1e-9 ? -1 : 0;
-  const int y = dy - rho >= 1.0 - 1e-9 ? 1 : dy + rho <= -1.0 + 1e-9 ? -1 : 0;
-  if (x && y) return 4 + (x < 0) + 2 * (y < 0);
-  if (x) return x > 0 ? 0 : 1;
-  if (y) return y > 0 ? 2 : 3;
-  return -1;
+  const double ax = std::fabs(dx), ay = std::fabs(dy);
+  if (std::max(ax, ay) < 1.0 + rho - 1e-9) return -1;  // overlaps the target
+  if (std::fabs(ax - ay) < 1e-9) return 4 + (dx < 0) + 2 * (dy < 0);
+  if (ax > ay) return dx > 0 ? 0 : 1;
+  return dy > 0 ? 2 : 3;
 }
 
 // The bases of what a leaf receives through each of its four edges and four corners, and the
@@ -868,8 +867,13 @@ int near_dir(double dx, double dy, double rho) {
 //   (on the parts py = 0) and 48 odd ones. The other edges are its images: W mirrors x (the sign
 //   of the parts px = 1), N swaps x and y, S mirrors N.
 //   H_NE (256 x 48): the same across the upper right corner; NW, SE, SW mirror it.
-// For data of magnitude one the part of the result outside its basis is at most 3e-15 with 48
-// vectors, the size of the tables' own quadrature error (4e-14 with 44, 1e-12 with 40).
+// The bases are fitted to the adjacent leaves' tables alone, on data of unit length. What they leave of
+// those (Frobenius norm, in that of the self table) is 1.2e-15 to 1.7e-15 across edges and 4e-15 to 6e-15
+// across corners; the rank-64/48 factors of the same tables leave 1.7e-15 to 8e-15. W-list boxes need no
+// vectors of their own: a coarser neighbour fills the same region, and of the field of a point charge
+// anywhere in one (a W box may be refined further, so its multipoles are not those of a leaf's
+// polynomial) they leave 1.7e-15 at most, at every expansion order. That holds for the edge that near_dir
+// names: H_NE leaves 4e-14 of a charge in the box at (1.5, 2.5), where H_N leaves 1.7e-15.
 struct LeafForm {
   std::vector<double> E;               // 4 x 28 x 64
   std::vector<double> H[8];            // E, W, N, S (256 x 96), NE, NW, SE, SW (256 x 48)
@@ -894,7 +898,6 @@ static const LeafForm& leaf_form() {
     outgoing_basis(f->E);
     const auto& T = near_tables();
     const auto& NO = near_offsets();
-    const auto& WO = w_offsets();
     std::vector<std::vector<double>> TE(33);  // parity basis, times E^T: 256 x 112
     {
       std::vector<std::thread> th;
@@ -902,53 +905,20 @@ static const LeafForm& leaf_form() {
         th.emplace_back([&, r]() { TE[size_t(r)] = times_et(parity_rows(parity_cols(T[size_t(r)], kNP), kNP), kNP, f->E); });
       for (auto& t : th) t.join();
     }
-    // a W-list box's field is what the multipoles of a leaf there make of its outgoing values
-    const std::vector<double> SE = times_et(parity_rows(s2m_table(kTerms), kNE), kNE, f->E);
-    // outgoing values of the 256 products T_a(x) T_b(y) of Chebyshev polynomials: the data that the
-    // bases are fitted to (constants and low degrees as closely as the rest; fitted to unit vectors
-    // of the outgoing values instead, 48 vectors would leave 1e-13 of a constant)
-    std::vector<double> cheb(size_t(kNP) * kNP), D(size_t(kOutAll) * kNP, 0.0);
-    const Basis& B = basis();
-    for (int b = 0; b < kP; ++b)
-      for (int a = 0; a < kP; ++a)
-        for (int j = 0; j < kP; ++j)
-          for (int i = 0; i < kP; ++i)
-            cheb[size_t(b * kP + a) * kNP + j * kP + i] = std::cos(a * std::acos(B.t[i])) * std::cos(b * std::acos(B.t[j]));
-    {
-      const std::vector<double> ce = times_et(parity_rows(cheb, kNP), kNP, f->E);  // 256 polynomials x 112
-      for (int f2 = 0; f2 < kNP; ++f2)
-        for (int c = 0; c < kOutAll; ++c) D[size_t(c) * kNP + f2] = ce[size_t(f2) * kOutAll + c];
-    }
     std::vector<std::vector<double>> even, odd, corner;
-    auto take = [&](const std::vector<double>& A, int dir) {  // columns of A (256 x 112) times D
-      std::vector<double> AD(size_t(kNP) * kNP, 0.0);
-      for (int i = 0; i < kNP; ++i)
-        for (int c = 0; c < kOutAll; ++c)
-          for (int k = 0; k < kNP; ++k) AD[size_t(i) * kNP + k] += A[size_t(i) * kOutAll + c] * D[size_t(c) * kNP + k];
-      for (int c = 0; c < kNP; ++c) {
+    for (int r = 1; r <= 32; ++r) {
+      const int d = near_dir(NO[size_t(r)].dx, NO[size_t(r)].dy, NO[size_t(r)].rho);
+      if (d != 0 && d != 4) continue;
+      for (int c = 0; c < kOutAll; ++c) {
         std::vector<double> v(kNP);
-        for (int i = 0; i < kNP; ++i) v[size_t(i)] = AD[size_t(i) * kNP + c];
-        if (dir == 4) {
+        for (int i = 0; i < kNP; ++i) v[size_t(i)] = TE[size_t(r)][size_t(i) * kOutAll + c];
+        if (d == 4) {
           corner.push_back(v);
         } else {
           even.emplace_back(v.begin(), v.begin() + 128);
           odd.emplace_back(v.begin() + 128, v.end());
         }
       }
-    };
-    for (int r = 1; r <= 32; ++r) {
-      const int d = near_dir(NO[size_t(r)].dx, NO[size_t(r)].dy, NO[size_t(r)].rho);
-      if (d == 0 || d == 4) take(TE[size_t(r)], d);
-    }
-    for (size_t r = 0; r < WO.size(); ++r) {
-      const int d = near_dir(WO[r].dx, WO[r].dy, WO[r].rho);
-      if (d != 0 && d != 4) continue;
-      const std::vector<double> M = parity_cols(m2t_table(int(r), kTerms), kNE);
-      std::vector<double> A(size_t(kNP) * kOutAll, 0.0);
-      for (int i = 0; i < kNP; ++i)
-        for (int k = 0; k < kNE; ++k)
-          for (int c = 0; c < kOutAll; ++c) A[size_t(i) * kOutAll + c] += M[size_t(i) * kNE + k] * SE[size_t(k) * kOutAll + c];
-      take(A, d);
     }
     std::vector<double> He, Ho, Hc;
     {
