@@ -63,7 +63,7 @@ typedef struct {
   int32_t use_graph;       /* 1: capture each apply once per (input, output) pointer pair into
                               a hipGraph and replay it. Default 0. */
   int32_t tile_leaf;       /* slots per tile of the near-field stages (256 rows): 32 or 64;
-                              0 = default (32; 16 in the low-rank form). The 256-row stages with
+                              0 = default (32; 16 in the low-rank form, where 16 asks for it too). The 256-row stages with
                               K = 80 take tile_leaf_exp. Plans of 512 leaves and more have no
                               such stage unless dense_near is set. */
   int32_t tile_box;        /* slots per tile of the expansion translation stages (M2M, L2L
@@ -354,15 +354,17 @@ int volpot_stage_times(volpot_plan_t plan, double* ms, int64_t* launches, int32_
 int volpot_plan_table(volpot_plan_t plan, int32_t kind, int32_t index, double* out, int64_t n);
 
 /* Autotuner (for callers that apply one tree shape many times, e.g. batched forests): searches
- * the launch shapes tile_box 16|32|64, tile_leaf 32|64, kchunk_leaf 32|16 and tile_leaf_exp
- * 16|32|64 (these two with dense_near only), split_min 0|1|-1 and overlap 0|16|24|32|48 one knob
- * at a time from 32, 32, 32, 16, 0 and 0 (the other fields, eps among them, are taken from base,
- * nullable), building a plan for each candidate (the defaults' and the current choice's are
+ * the launch shapes tile_box 16|32|64, tile_leaf 32|64 (plans of less than 512 leaves or with dense_near),
+ * kchunk_leaf 32|16 and tile_leaf_exp 16|32|64 (these two with dense_near only), split_min 0|1|-1 and
+ * overlap 0|16|24|32|48 one knob at a time from the library's defaults (the other fields, eps among them,
+ * are taken from base, nullable), building a plan for each candidate (the defaults' and the current choice's are
  * kept for timing again) and timing one forward plus one adjoint apply on internal device
  * buffers after a warm-up (HIP events, private stream, best of 5); writes the fastest options
  * to *best and their time in milliseconds to *best_ms (nullable). A candidate must beat the
  * current choice by more than 1.5%, and the result must beat the defaults by as much when both
- * are timed again, so that differences within timing noise keep the defaults. With cache_path
+ * are timed again, so that differences within timing noise keep the defaults, which are written as
+ * tile_box 16 (0 where the default differs from stage to stage), tile_leaf 16 in the low-rank form and 32
+ * otherwise, kchunk_leaf 32, tile_leaf_exp 16, split_min 0 and overlap 0. With cache_path
  * (nullable) the result is looked up in, and appended to, that text file, keyed by a signature
  * of the trees' level histogram and sizes, of the expansion order that base's eps selects, of
  * base's dense_m2l and dense_near and of the device, so that a shape is timed once.

@@ -884,7 +884,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   // and 24 (35). Beyond, 32 slots read the tables half as often: M2L of 22k boxes 116 us (130 at 16
   // slots), of the 345k-leaf forest 719 (850), its chains 448 (560).
   const int tile_box_opt = (tile_box == 16 || tile_box == 32 || tile_box == 64) ? tile_box : 0;
-  auto box_tile = [&](size_t targets) { return tile_box_opt ? tile_box_opt : targets <= 8192 ? 16 : 32; };
+  auto box_tile = [&](size_t targets) { return tile_box_opt ? tile_box_opt : targets <= kBoxTileSmall ? 16 : 32; };
   // the expansion-row stages that read or write leaf data (K or M = 256: S2M, S2L and their
   // transposes, and the pair stages of the low-rank near field) take kLeafDataTile slots
   // Up to 8192 targets they take 16-slot tiles too (64 leaves: S2M 13 us where 64 slots took 21, pair
@@ -893,7 +893,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   // (65536 targets): below, such tiles are cut along their segments to fill the chip, and 64 slots
   // shared by four waves need fewer cuts. Edge stage of 345k leaves (1.4M targets) 877 -> 770 us, its
   // adjoint (345k) 910 -> 770; 16.7k leaves (67k / 16.7k targets) 60 -> 61 and 66 -> 76.
-  auto data_tile = [&](size_t targets) { return targets <= 8192 ? 16 : lf && targets >= 65536 ? kWaveTile : kLeafDataTile; };
+  auto data_tile = [&](size_t targets) { return targets <= kBoxTileSmall ? 16 : lf && targets >= 65536 ? kWaveTile : kLeafDataTile; };
   // The leaf stages with K = 80 (L2T, M2T and their transposes' counterparts S2M^T, S2L^T) do
   // little work per tile: on small trees 16-slot tiles give more independent workgroups to hide
   // the latency of their few dependent k-chunks; on large trees and forests wider tiles read

@@ -180,6 +180,7 @@ struct FamDesc { int8_t arr; int32_t stride; int8_t unused; };
 // expansions and direct sums over the curve's quadrature nodes, and the leaf kernels of the
 // compressed near field.
 enum Custom : int8_t { C_NONE = 0, C_P2M, C_P2L, C_P2P, C_LIN, C_LOUT };
+constexpr int kBoxTileSmall = 8192;  // expansion stages of up to this many targets take 16-slot tiles (plan.cpp)
 constexpr int kWaveTile = 32;  // slots of a tile of one wave
 constexpr int kLeafTile = 32;  // leaves per tile of the leaf kernels
 // Volume plans of at least this many leaves take the compressed near field. The larger the tree the more

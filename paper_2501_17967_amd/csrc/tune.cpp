@@ -1,7 +1,7 @@
 // Autotuner of the launch shapes: for one tree or forest, time candidate combinations of
 // leaf-stage tiles, expansion-stage tile and split policy on the current device (one forward
 // and one adjoint apply after a warm-up, HIP events on a private stream), one knob at a time
-// (coordinate descent from the defaults: expansion tile, leaf tile, split policy, streams),
+// (coordinate descent from the library's defaults: expansion tile, leaf tile, split policy, streams),
 // and report the fastest. Optionally remembers the answer in a text file keyed by a signature of the
 // workload's shape and of the device, so that later plans of the same shape skip the timing.
 #include <hip/hip_runtime.h>
@@ -46,7 +46,9 @@ uint64_t signature(int32_t n_trees, const int64_t* off, const int32_t* levels, i
       h *= 1099511628211ull;
     }
   };
-  mix(3);  // the cache line format: key, tile_leaf, tile_box, split_min, overlap, tile_leaf_exp, kchunk_leaf, ms
+  // raised with the line format (key, tile_leaf, tile_box, split_min, overlap, tile_leaf_exp, kchunk_leaf, ms) and
+  // with kernels or defaults that make the shapes timed before them the wrong ones
+  mix(4);
   mix(uint64_t(n_trees));
   std::vector<int64_t> hist(32, 0);
   for (int64_t i = 0; i < off[n_trees]; ++i) hist[size_t(std::min(std::max(levels[i], 0), 31))]++;
@@ -79,7 +81,7 @@ bool cache_lookup(const char* path, uint64_t key, volpot_options* best, double* 
     std::string rest;
     if (!(ss >> std::hex >> k >> std::dec >> tl >> tb >> sm >> one >> te >> kc >> t) || (ss >> rest)) continue;
     // a line that does not hold a valid shape is ignored (the shape is then timed again)
-    if (k != key || !(tl == 32 || tl == 64) || !(tb == 16 || tb == 32 || tb == 64) || sm < -1 || one < 0 ||
+    if (k != key || !(tl == 16 || tl == 32 || tl == 64) || !(tb == 0 || tb == 16 || tb == 32 || tb == 64) || sm < -1 || one < 0 ||
         !(te == 16 || te == 32 || te == 64) || !(kc == 16 || kc == 32) || !(t > 0.0))
       continue;
     best->tile_leaf = tl;
@@ -140,7 +142,11 @@ extern "C" int volpot_autotune(int32_t n_trees, const int64_t* tree_offsets, con
                           hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess ||
                           hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess))
     rc = VOLPOT_ERR_HIP;
-  const Candidate def{32, 32, 0, 0, 16, 32};
+  // The defaults. tile_leaf: 16 slots in the low-rank form, 32 otherwise (the compressed form has no stage
+  // that takes it). tile_box: 0, each stage by its number of targets; the same as 16 where the stage of the
+  // most targets, the M2L of the boxes from level 2 on, has no more than kBoxTileSmall.
+  const bool low_rank = !o.dense_near && tree_offsets[n_trees] < vp::kLeafFormMin;
+  Candidate def{low_rank ? 16 : 32, 0, 0, 0, 16, 32};
   // Plans kept for timing again: slot 0 the defaults' (timed first and last), slot 1 the current
   // choice's, and `last` the candidate just timed (kept as the choice if it wins).
   volpot_plan_t kept[2] = {nullptr, nullptr}, last = nullptr;
@@ -225,8 +231,14 @@ extern "C" int volpot_autotune(int32_t n_trees, const int64_t* tree_offsets, con
   }
   if (rc == VOLPOT_OK) rc = time_it(cur, &best_t);  // the defaults are the first incumbent
   if (rc == VOLPOT_OK) {
+    volpot_info info;
+    rc = volpot_plan_info(kept[0], &info);
+    if (rc == VOLPOT_OK && info.n_boxes <= vp::kBoxTileSmall) def.tile_box = cur.tile_box = kept_c[0].tile_box = 16;
+  }
+  if (rc == VOLPOT_OK) {
     try_axis(0, {16, 32, 64});
-    try_axis(1, {32, 64});
+    if (low_rank) try_axis(1, {16, 32, 64});
+    if (o.dense_near) try_axis(1, {32, 64});
     if (o.dense_near) try_axis(5, {32, 16});  // the low-rank near field always takes k-chunk 16
     if (o.dense_near) try_axis(4, {16, 32, 64});  // the low-rank near field folds the K = 80 leaf stage
     if (!o.deterministic) try_axis(2, {0, 1, -1});  // deterministic plans never cut tiles
