@@ -736,7 +736,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<KC, CX>()))) grg_kernel(const 
 template <int KC, int W0, int W1, int W2>
 __global__ void __launch_bounds__(64 * (W0 > W1 ? W0 : W1)) grg_group_kernel(const GrgGroup g) {
   int b = blockIdx.x;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // scalar: whole waves leave before the stage's barriers
   if (b < g.p[0].n_blocks) {
     if (wave < W0) grg_block<1, 1, W0, 1, KC, false>(g.p[0], xcd_tile(b, g.p[0].n_blocks));
     return;
