@@ -78,10 +78,13 @@ typedef struct {
                               (0 = default: one relation's worth, K / chunk; -1 = no cut:
                               one block per tile) */
   int32_t overlap;         /* 0 (default): every stage on the caller's stream, in plan order.
-                              n > 0: the near field runs as two launches that leave n compute
-                              units' share of blocks free, each beside one latency-bound chain
-                              of the far field (upward, downward) on a plan-owned helper
-                              stream forked from and joined back into the caller's stream */
+                              n > 0: near-field launches leave n compute units' share of
+                              blocks free for a latency-bound chain of the far field beside
+                              them, on a plan-owned helper stream forked from and joined back
+                              into the caller's stream: with dense_near one half of the near
+                              field beside each chain (upward, downward), in the low-rank form
+                              one pair stage beside each, in the compressed form (512 leaves
+                              and more) the corner stage beside the downward chain */
   double root_centre[2];   /* centre (x, y) of the root box in the caller's coordinates
                               (default 0, 0) */
   double root_halfwidth;   /* half-width h > 0 of the root box; 0 = default 1. The root box

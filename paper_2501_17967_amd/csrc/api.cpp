@@ -217,11 +217,11 @@ int schedule_all(volpot_plan_s* p, int nominal) {
           it = resident.emplace(key, nominal > 0 ? nominal : grg_resident_blocks(s.M, s.NT, s.KC, s.cx_rel >= 0)).first;
         if (it->second <= 0) return VOLPOT_ERR_HIP;
         // a stage that runs beside the helper stream leaves `overlap` compute units' share free
-        // (helper-stream stages get that share only)
+        // (helper-stream stages get that share only); stages that run alone take the whole device
         int blocks = it->second;
         const int per_cu = blocks / std::max(cus, 1);
-        if (p->overlap > 0 && s.concurrent) blocks = std::max(1, blocks - per_cu * p->overlap);
-        if (p->overlap > 0 && s.helper) blocks = std::max(1, std::min(blocks, per_cu * p->overlap));
+        if (p->overlap > 0 && s.concurrent)
+          blocks = std::max(1, s.helper ? std::min(blocks, per_cu * p->overlap) : blocks - per_cu * p->overlap);
         // default: a block gets at least one whole segment (K / KC chunks). A tile's fixed cost
         // (index loads, rank-one terms, the output pass) is weighted as one segment: without it,
         // blocks whose share is many one-segment tiles ran about twice as long as the others

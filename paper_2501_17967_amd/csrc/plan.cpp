@@ -425,7 +425,8 @@ static void make_tiles_ordered(Stage& st, const std::vector<int32_t>& targets,
 // stage into one stage that needs the far field, puts its pair stages there instead:
 //   S2M, M2M chain (helper), NEARC, FARV (join), FARX, L2L chain (helper), NEARC48, NEAR+LOCT (join)
 // The compressed near field has the same order; its NEARC (ANEARC) reads multipoles (cotangents of
-// locals), so the join comes before it.
+// locals), so the join comes before it: the upward chain and NEARC run alone, with all compute units, and
+// only NEARC48 beside a chain.
 // Without overlap everything runs in this order on one stream, which is also a valid order. A
 // layer plan has P2M in S2M's place, P2L in FARX's, and its direct sum P2P, which adds onto
 // LOCT's output, last.
@@ -449,6 +450,7 @@ static void arrange_stages(std::vector<Stage>& v, bool adjoint) {
   auto chain = [&](std::vector<Stage>& c) {
     for (size_t i = 0; i < c.size(); ++i) {
       c[i].helper = 1;
+      c[i].concurrent = 1;
       c[i].fork_before = i == 0;
       v.push_back(std::move(c[i]));
     }
@@ -1605,10 +1607,14 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   }
   arrange_stages(P.fwd, false);
   arrange_stages(P.adj, true);
-  if (lf)  // these read multipoles (locals' cotangents) of the upward chain
+  if (lf)  // the pair stages read multipoles (locals' cotangents) of the upward chain
     for (auto* v : {&P.fwd, &P.adj})
-      for (Stage& st : *v)
+      for (Stage& st : *v) {
+        const bool up = st.helper && (st.kind == K_UP || st.kind == K_AUP);
+        if (!up && !st.pre_near) continue;
+        st.concurrent = 0;
         if (st.pre_near) { st.join_before = 1; break; }
+      }
   return VOLPOT_OK;
 }
 

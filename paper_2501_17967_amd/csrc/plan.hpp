@@ -227,7 +227,7 @@ struct Stage {
   int8_t helper = 0;       // runs on the helper stream (far-field chain)
   int8_t join_before = 0;  // waits for the helper stream's work before launching
   int8_t fork_before = 0;  // the helper stream waits for the caller's stream before this stage
-  int8_t concurrent = 0;   // runs while helper-stream stages may run: leaves compute units free
+  int8_t concurrent = 0;   // runs beside the other stream's stages: the two share the compute units
   int8_t custom = C_NONE;  // not a grouped product: c_tgt / c_ptr / c_idx (layer stages), table (leaf kernels)
   int leaf_rel = -1;       // leaf kernels: relation id of the table
   std::string name;        // stage name for reports, e.g. NEAR or M2M[5]
