@@ -388,14 +388,16 @@ int volpot_autotune(int32_t n_trees, const int64_t* tree_offsets, const double* 
  * 256 blocks doubles, caller-owned). VOLPOT_ERR_ARG for blocks or iters <= 0 or a null out_dev. */
 int volpot_peak_mfma(int32_t blocks, int32_t iters, double* out_dev, void* hip_stream);
 
-/* One stage (one kernel launch) of an apply, for inspection and tuning. */
+/* One stage of an apply, for inspection and tuning: one kernel launch (small stages that do not
+ * depend on one another share one while no timing is on). */
 typedef struct {
   char name[24];           /* e.g. "NEAR", "M2M[5]", "AFARV" */
   int32_t kind;            /* stage kind, numbered as in volpot_info.flops_kind */
   int32_t rows, tile, kchunk; /* output rows per slot (2q or 256; the padded core's rows when
                               factored), slots per tile, k-chunk */
   int32_t helper;          /* 1: runs on the plan's helper stream */
-  int64_t n_tiles, n_segments, n_blocks, n_split_tiles;
+  int64_t n_tiles, n_segments, n_blocks, n_split_tiles; /* the compressed form's leaf kernels cut no
+                              tile: they launch n_blocks or n_tiles blocks, whichever is less */
   double flops, flops_issued;
   int32_t inner;           /* inner dimension K of the stage's products (reals; complex terms
                               when factored); the largest one where segments differ (the

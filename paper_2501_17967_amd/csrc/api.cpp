@@ -202,7 +202,7 @@ int schedule_all(volpot_plan_s* p, int nominal) {
       for (Stage& s : *v) {
         if (s.custom == C_LIN || s.custom == C_LOUT) {
           // whole tiles, each block an equal run of them: a tile counts its chunks and as much again
-          // for its fixed cost, as below
+          // for its fixed cost; a launch has no more blocks than tiles
           const bool out = s.custom == C_LOUT, adj = v == &p->host.adj;
           const int res = nominal > 0 ? nominal : leaf_resident_blocks(out, adj);
           if (res <= 0) return VOLPOT_ERR_HIP;
@@ -513,6 +513,7 @@ hipError_t launch_leaf(volpot_plan_s* p, const DevStage& d, bool adjoint, const 
   // forward locals and their cotangents belong to leaves at level >= 2, multipoles to every leaf
   g.loc_box = lout == adjoint ? p->d_leaf_box : p->d_loc_box;
   g.n_leaves = int32_t(p->host.n_leaves);
+  g.tile = s.NT;
   g.n_tiles = s.n_tiles;
   g.n_chunks = s.K / s.KC;
   g.n_groups = s.M / 64;

@@ -101,7 +101,7 @@ struct LeafParams {
   const double* leaf_s2;
   const int32_t* leaf_box;    // box of each leaf
   const int32_t* loc_box;     // box whose expansion a leaf reads or writes, -1: none
-  int32_t n_leaves, n_tiles;  // tiles of kLeafTile leaves
+  int32_t n_leaves, tile, n_tiles;  // tiles of `tile` leaves
   int32_t n_chunks;           // leaf_out: chunks of 16 columns per part
   int32_t n_groups;           // adjoint leaf_in: groups of 16 rows per part
   int32_t ne;                 // reals per expansion

@@ -70,7 +70,7 @@ struct Raw {
   }
 };
 
-constexpr int kSlots = 32;    // leaves per tile
+constexpr int kSlots = kLeafTile;  // leaves per tile
 constexpr int kThreads = 256;
 
 // ---------------------------------------------------------------- leaf_in
@@ -271,11 +271,10 @@ __global__ void __launch_bounds__(kAdjThreads, 4) leaf_in_adj_kernel(const LeafP
 // is four raw pairs per thread and sums of them: mirrored nodes, the two edges or four corners that
 // the parts add or subtract, or an expansion's reals.
 constexpr int kLdOut = 17;
-// Up to this many leaves a launch is one tile's chain of chunks, each as long as its loads take. There
+// Up to kLeafOutSmall leaves a launch is one tile's chain of chunks, each as long as its loads take. There
 // tiles of 16 leaves (H = 1) leave the registers to keep two chunks in flight: 1501 leaves forward 34
 // -> 23 us, adjoint 20 -> 13. At 16.7k leaves both take 78 and 38; beyond, 32 leaves (H = 2) read the
 // fragments half as often.
-constexpr int kOutSmall = 8192;
 constexpr int kCorner0 = (64 + kEdge) / 16;  // first chunk of the corners' columns
 
 template <bool ADJ, int SLOTS>
@@ -365,12 +364,12 @@ struct OutLoader {
 template <bool ADJ, int H>
 __global__ void __launch_bounds__(kThreads, 3) leaf_out_kernel(const LeafParams p) {
   constexpr int kSlots = 16 * H;
+  static_assert(kLeafOutTileSmall == 16 && kLeafTile == 32, "H = 1 and H = 2");
   __shared__ double Bs[2][4 * kSlots * kLdOut];
   __shared__ double r1s_[2][kSlots];  // of even and of odd tiles: a fast wave forms the next tile's while this one's are read
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int blk = leaf_block(blockIdx.x, gridDim.x);
-  const int n_tiles = (p.n_leaves + kSlots - 1) / kSlots;
-  const int t0 = (int)((int64_t)blk * n_tiles / gridDim.x), t1 = (int)((int64_t)(blk + 1) * n_tiles / gridDim.x);
+  const int t0 = (int)((int64_t)blk * p.n_tiles / gridDim.x), t1 = (int)((int64_t)(blk + 1) * p.n_tiles / gridDim.x);
   const bool stages = (tid >> 3) < kSlots;  // this thread stages values
   const int n_chunks = p.n_chunks;
   const int b_at = (lane & 15) * kLdOut + (lane >> 4);
@@ -497,13 +496,12 @@ hipError_t launch_leaf_in(const LeafParams& p, bool adjoint, int n_blocks, hipSt
 
 hipError_t launch_leaf_out(const LeafParams& p, bool adjoint, int n_blocks, hipStream_t stream) {
   if (p.n_tiles <= 0) return hipSuccess;
-  if (p.n_leaves <= kOutSmall) {
-    const int tiles16 = (p.n_leaves + 15) / 16;
-    if (adjoint) hipLaunchKernelGGL((leaf_out_kernel<true, 1>), dim3(unsigned(tiles16)), dim3(kThreads), 0, stream, p);
-    else hipLaunchKernelGGL((leaf_out_kernel<false, 1>), dim3(unsigned(tiles16)), dim3(kThreads), 0, stream, p);
+  const dim3 grid(unsigned(n_blocks < p.n_tiles ? n_blocks : p.n_tiles));
+  if (p.tile == kLeafOutTileSmall) {
+    if (adjoint) hipLaunchKernelGGL((leaf_out_kernel<true, 1>), grid, dim3(kThreads), 0, stream, p);
+    else hipLaunchKernelGGL((leaf_out_kernel<false, 1>), grid, dim3(kThreads), 0, stream, p);
     return hipGetLastError();
   }
-  const dim3 grid(unsigned(n_blocks < p.n_tiles ? n_blocks : p.n_tiles));
   if (adjoint) hipLaunchKernelGGL((leaf_out_kernel<true, 2>), grid, dim3(kThreads), 0, stream, p);
   else hipLaunchKernelGGL((leaf_out_kernel<false, 2>), grid, dim3(kThreads), 0, stream, p);
   return hipGetLastError();

@@ -935,16 +935,17 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   };
   // one launch of a leaf kernel over all leaves: reported as n_tiles segments of the kernel's table
   auto leaf_stage = [&](int kind, const char* name, int8_t custom, int rel, int K, int KC) {
+    const int NT = custom == C_LOUT && P.n_leaves <= kLeafOutSmall ? kLeafOutTileSmall : kLeafTile;
     Stage st;
-    init_stage(st, kind, name, -1, mats.M[size_t(rel)], K, kLeafTile, A_NONE, 0);
+    init_stage(st, kind, name, -1, mats.M[size_t(rel)], K, NT, A_NONE, 0);
     st.KC = KC;
     st.custom = custom;
     st.leaf_rel = rel;
-    st.n_tiles = int((P.n_leaves + kLeafTile - 1) / kLeafTile);
+    st.n_tiles = int((P.n_leaves + NT - 1) / NT);
     st.seg_rel.assign(size_t(st.n_tiles), rel);
     st.seg_k.assign(size_t(st.n_tiles), K);
     st.flops = 2.0 * mats.nnz[size_t(rel)] * double(P.n_leaves);
-    st.flops_issued = 2.0 * st.M * K * kLeafTile * double(st.n_tiles);
+    st.flops_issued = 2.0 * st.M * K * NT * double(st.n_tiles);
     return st;
   };
   // boxes at levels >= 2 ordered by (level, quadrant, tree, morton): targets of one tile then

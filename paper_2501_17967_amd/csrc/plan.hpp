@@ -183,6 +183,8 @@ enum Custom : int8_t { C_NONE = 0, C_P2M, C_P2L, C_P2P, C_LIN, C_LOUT };
 constexpr int kBoxTileSmall = 8192;  // expansion stages of up to this many targets take 16-slot tiles (plan.cpp)
 constexpr int kWaveTile = 32;  // slots of a tile of one wave
 constexpr int kLeafTile = 32;  // leaves per tile of the leaf kernels
+constexpr int kLeafOutTileSmall = 16;  // of leaf_out in plans of up to kLeafOutSmall leaves (leaf.hip)
+constexpr int kLeafOutSmall = 8192;
 // Volume plans of at least this many leaves take the compressed near field. The larger the tree the more
 // it saves (1501 leaves forward 364 -> 276 us, 345k leaves forward and adjoint 14.9 -> 10.1 ms, with the
 // kernels of the time); below, both forms take as long as their launches' dependent steps (forward and

@@ -34,3 +34,15 @@ def test_overlap_reserves_units_only_beside_a_chain(vp):
             else:                                         # alone: the whole device
                 assert s["n_blocks"] == base, s
         assert limited > 0
+
+
+@pytest.mark.parametrize("trees,tile", [([_uniform(5)], 16), ([_random(3, 260, 9)], 16), ([_uniform(7)], 32)])
+def test_leaf_output_reports_the_tiles_it_launches(vp, trees, tile):
+    n = sum(len(t) for t in trees)
+    assert (n <= 8192) == (tile == 16)
+    for split_min in (0, 1, -1):
+        for st, name in zip(_stages(vp, trees, split_min=split_min), ("NEAR+LOCT", "ANEAR+ALOCT")):
+            s = st[name]
+            assert s["tile"] == tile and s["n_tiles"] == -(-n // tile), s
+            assert s["flops_issued"] == 2.0 * 256 * s["inner"] * tile * s["n_tiles"]
+            assert split_min >= 0 or s["n_blocks"] == s["n_tiles"], s
