@@ -4,6 +4,7 @@
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstring>
 #include <map>
@@ -24,6 +25,7 @@ namespace {
 // ---------------------------------------------------------------- shared device tables
 struct DeviceTables {
   int device = -1, q = kTerms;  // device and expansion terms
+  bool leaf_form = false;       // the compressed near field's tables
   double* buf = nullptr;
   RelDesc* d_rels = nullptr;
   std::vector<RelDesc> rels;  // host copy (device pointers)
@@ -31,33 +33,36 @@ struct DeviceTables {
   int refs = 0;
 };
 std::mutex g_mu;
-std::map<std::pair<int, int>, DeviceTables*> g_tables;  // per (device, expansion terms)
+std::map<std::array<int, 3>, DeviceTables*> g_tables;  // per device, expansion terms, and whether the compressed form's
 
-int acquire_tables(int device, int q, DeviceTables** out) {
+// The tables of all plans on the device, or (leaf_form) those of the compressed near field.
+int acquire_tables(int device, int q, bool leaf_form, DeviceTables** out) {
   std::lock_guard<std::mutex> lk(g_mu);
-  auto it = g_tables.find({device, q});
+  auto it = g_tables.find({device, q, leaf_form});
   if (it != g_tables.end()) {
     it->second->refs++;
     *out = it->second;
     return VOLPOT_OK;
   }
-  const Matrices& M = matrices(q);
+  const Matrices& M = leaf_form ? leaf_matrices(q) : matrices(q);
   std::vector<size_t> off(kNumRel), woff(kNumRel);
   size_t total = 0;
   for (int r = 0; r < kNumRel; ++r) {
     off[r] = total;
-    total += size_t(M.M[r]) * M.K[r];
+    total += M.a[r].size();
   }
   for (int r = 0; r < kNumRel; ++r) {  // the factored relations' diagonals after the tables
     woff[r] = total;
-    total += M.w_in[r].size() + M.w_out[r].size();
+    if (!M.a[r].empty()) total += M.w_in[r].size() + M.w_out[r].size();
   }
   std::vector<double> host(total);
   for (int r = 0; r < kNumRel; ++r) {
+    if (M.a[r].empty()) continue;
     std::copy(M.w_in[r].begin(), M.w_in[r].end(), host.begin() + std::ptrdiff_t(woff[r]));
     std::copy(M.w_out[r].begin(), M.w_out[r].end(), host.begin() + std::ptrdiff_t(woff[r] + M.w_in[r].size()));
   }
   for (int r = 0; r < kNumRel; ++r) {
+    if (M.a[r].empty()) continue;
     const int rows = M.M[r], cols = M.K[r], nt = rows / 16;
     const double* a = M.a[r].data();
     double* f = host.data() + off[r];
@@ -69,11 +74,13 @@ int acquire_tables(int device, int q, DeviceTables** out) {
   if (!T) return VOLPOT_ERR_OOM;
   T->device = device;
   T->q = q;
+  T->leaf_form = leaf_form;
   T->bytes = total * sizeof(double) + kNumRel * sizeof(RelDesc);
   if (hipMalloc(&T->buf, total * sizeof(double)) != hipSuccess) { delete T; return VOLPOT_ERR_OOM; }
   if (hipMalloc(&T->d_rels, kNumRel * sizeof(RelDesc)) != hipSuccess) { (void)hipFree(T->buf); delete T; return VOLPOT_ERR_OOM; }
   std::vector<RelDesc> rd(kNumRel);
   for (int r = 0; r < kNumRel; ++r) {
+    if (M.a[r].empty()) continue;
     const bool w = !M.w_in[r].empty();
     rd[r] = {T->buf + off[r], M.M[r], M.K[r], w ? T->buf + woff[r] : nullptr,
              w ? T->buf + woff[r] + M.w_in[r].size() : nullptr, M.koff[r]};
@@ -85,7 +92,7 @@ int acquire_tables(int device, int q, DeviceTables** out) {
     return VOLPOT_ERR_HIP;
   }
   T->refs = 1;
-  g_tables[{device, q}] = T;
+  g_tables[{device, q, leaf_form}] = T;
   *out = T;
   return VOLPOT_OK;
 }
@@ -100,7 +107,7 @@ void release_tables(DeviceTables* T) {
     (void)hipFree(T->buf);
     (void)hipFree(T->d_rels);
     (void)hipSetDevice(prev);
-    g_tables.erase({T->device, T->q});
+    g_tables.erase({T->device, T->q, T->leaf_form});
     delete T;
   }
 }
@@ -134,7 +141,10 @@ struct volpot_plan_s {
   bool host_only = false;
   bool use_graph = false;
   int device = -1;
-  DeviceTables* tables = nullptr;
+  DeviceTables *tables = nullptr, *leaf_tables = nullptr;  // leaf_tables: the compressed near field's
+  const RelDesc& rel(int id) const {
+    return (id % kNumFwd < kRelLeafForm ? tables : leaf_tables)->rels[size_t(id)];
+  }
   char* d_block = nullptr;
   double *d_mp = nullptr, *d_loc = nullptr, *d_lb = nullptr, *d_ab = nullptr, *d_usum = nullptr, *d_leaf_s2 = nullptr;
   double *d_far = nullptr, *d_afar = nullptr;  // far-field parts before the downward chains
@@ -301,8 +311,8 @@ int upload(volpot_plan_s* p) {
     Off o;
     segd.emplace_back(s.seg_fam.size());  // none for the leaf kernels
     for (size_t i = 0; i < s.seg_fam.size(); ++i) {
-      const RelDesc& rd = p->tables->rels[size_t(s.seg_rel[i])];
-      const RelDesc& ra = s.cx_rel >= 0 ? p->tables->rels[size_t(s.cx_rel)] : rd;  // factored: the core
+      const RelDesc& rd = p->rel(s.seg_rel[i]);
+      const RelDesc& ra = s.cx_rel >= 0 ? p->rel(s.cx_rel) : rd;  // factored: the core
       segd.back()[i] = {ra.A, ra.K, int32_t(s.seg_fam[i]), rd.w_in, rd.w_out, rd.koff};
     }
     o.tt = add_bytes(total, s.tile_tgt); o.tsp = add_bytes(total, s.tile_seg_ptr); o.sd = add_bytes(total, segd.back());
@@ -507,7 +517,7 @@ hipError_t launch_leaf(volpot_plan_s* p, const DevStage& d, bool adjoint, const 
   LeafParams g;
   std::memset(&g, 0, sizeof(g));
   g.x = in;
-  g.table = p->tables->rels[size_t(s.leaf_rel)].A;
+  g.table = p->rel(s.leaf_rel).A;
   g.leaf_s2 = p->d_leaf_s2;
   g.leaf_box = p->d_leaf_box;
   // forward locals and their cotangents belong to leaves at level >= 2, multipoles to every leaf
@@ -578,7 +588,7 @@ GrgParams stage_params(volpot_plan_s* p, const DevStage& d, const double* in, do
   g.pieces = d.pieces; g.blk_ptr = d.blk_ptr; g.tile_count = d.tile_count;
   g.partial = p->d_part[s.helper ? 0 : 1];  // helper-marked stages never share a buffer with the others
   g.n_blocks = s.n_blocks;
-  g.cx_core = s.cx_rel >= 0 ? p->tables->rels[size_t(s.cx_rel)].A : nullptr;
+  g.cx_core = s.cx_rel >= 0 ? p->rel(s.cx_rel).A : nullptr;
   return g;
 }
 
@@ -716,6 +726,7 @@ void free_plan(volpot_plan_s* p) {
     for (double* d : p->d_part)
       if (d) (void)hipFree(d);
     release_tables(p->tables);
+    release_tables(p->leaf_tables);
   }
   delete p;
 }
@@ -785,8 +796,15 @@ int make_plan(int32_t n_trees, const int64_t* offsets, const double* centres, co
     if (rc != VOLPOT_OK) { delete plan; return rc; }
   } else {
     if (hipGetDevice(&plan->device) != hipSuccess) { delete plan; return VOLPOT_ERR_HIP; }
-    rc = acquire_tables(plan->device, plan->host.ne / 2, &plan->tables);
-    if (rc == VOLPOT_OK) rc = upload(plan);
+    try {
+      rc = acquire_tables(plan->device, plan->host.ne / 2, false, &plan->tables);
+      if (rc == VOLPOT_OK && plan->host.leaf_form) rc = acquire_tables(plan->device, plan->host.ne / 2, true, &plan->leaf_tables);
+      if (rc == VOLPOT_OK) rc = upload(plan);
+    } catch (const std::bad_alloc&) {
+      rc = VOLPOT_ERR_OOM;
+    } catch (...) {
+      rc = VOLPOT_ERR_HIP;
+    }
     if (rc != VOLPOT_OK) { free_plan(plan); return rc; }
   }
   *out = plan;
@@ -944,7 +962,9 @@ int volpot_plan_info(volpot_plan_t plan, volpot_info* out) {
   out->n_points = P.n_pts;
   out->pairs_points = int64_t(P.pt_near_leaf.size());
   out->pairs_lowrank = P.pairs_lr;
-  out->device_bytes = plan->device_bytes + (plan->tables ? int64_t(plan->tables->bytes) : 0);
+  out->device_bytes = plan->device_bytes;
+  for (const DeviceTables* t : {plan->tables, plan->leaf_tables})
+    if (t) out->device_bytes += int64_t(t->bytes);
   return VOLPOT_OK;
 }
 

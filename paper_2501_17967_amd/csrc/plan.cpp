@@ -868,7 +868,6 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   }
 
   // ---------------------------------------------------------------- stages
-  const Matrices& mats = matrices(ne / 2);
   const int NTL = (tile_leaf == 32 || tile_leaf == 64) ? tile_leaf : 32;
   // the low-rank form's leaf stage serves trees of less than kLeafFormMin leaves: 16 slots, eight waves of
   // 32 rows (64 leaves: 18 us, 28 with 32 slots and four waves of 64 rows)
@@ -879,6 +878,7 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   // sends (A_E) and what it receives across each edge and corner
   const bool lf = lr && P.n_leaves >= kLeafFormMin;
   P.leaf_form = lf;
+  const Matrices& mats = lf ? leaf_matrices(ne / 2) : matrices(ne / 2);
   const int KCL = (lr || kchunk_leaf == 16) ? 16 : 32;
   // Slots per tile of the expansion stages (M2L and the chains). Up to 8192 targets a launch is a few
   // dependent steps long, and tiles of 16 slots whose rows are shared out over the waves take the

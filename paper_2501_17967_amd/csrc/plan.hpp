@@ -103,6 +103,7 @@ constexpr int kOut = 28;
 constexpr int kOutAll = 4 * kOut;
 constexpr int kEdge = 96;
 constexpr int kCorner = 48;
+constexpr int kRelLeafForm = 228;  // the compressed form's ids, to kNumFwd
 constexpr int kRelC = 228;    // +32: near relation r (1..32) from outgoing to received values
 constexpr int kRelCW = 260;   // +20: W offset, from multipoles to received values
 constexpr int kRelXE = 280;   // +20: X offset, from outgoing values to locals
@@ -151,6 +152,9 @@ constexpr int pad16(int n) { return (n + 15) / 16 * 16; }
 // The relation matrices for expansions of q complex terms (order q - 1; q = 16, 24, 32 or 40),
 // built once per process and q; the near tables (polar quadrature) are the same for every q.
 const Matrices& matrices(int q = kTerms);
+// The compressed near field's tables (ids from kRelLeafForm, and their adjoints), built when the first
+// plan takes that form; the other tables' shapes, counts and diagonals are here too, not their values.
+const Matrices& leaf_matrices(int q);
 // The quadrature rules of the point-moment kernel (moments.hip): leaf nodes and barycentric
 // weights, the 24-point tensor rule, the 12-point edge rule and the 16-point log-product rule.
 struct MomentRules;

@@ -968,8 +968,8 @@ static const LeafForm& leaf_form() {
   return *F;
 }
 
-// The relation tables of the compressed form for expansions of Q complex terms.
-static void leaf_form_tables(Matrices& M, int Q) {
+// The relation tables of the compressed form for expansions of Q complex terms, from the others (B).
+static void leaf_form_tables(Matrices& M, const Matrices& B, int Q) {
   const LeafForm& F = leaf_form();
   const int ne = 2 * Q, qh = Q / 2, qp = pad16(qh);
   auto set = [&](int id, int rows, int cols, std::vector<double>&& a) {
@@ -982,14 +982,14 @@ static void leaf_form_tables(Matrices& M, int Q) {
   for (int r = 0; r < 20; ++r) {
     const Offset& w = w_offsets()[size_t(r)];
     const int d = near_dir(w.dx, w.dy, w.rho), k = d < 4 ? kEdge : kCorner;
-    set(kRelCW + r, k, ne, ht_times(F.H[d], k, parity_cols(M.a[kRelM2T + r], ne), ne));
-    set(kRelXE + r, ne, kOutAll, times_et(parity_rows(M.a[kRelS2L + r], ne), ne, F.E));
+    set(kRelCW + r, k, ne, ht_times(F.H[d], k, parity_cols(B.a[kRelM2T + r], ne), ne));
+    set(kRelXE + r, ne, kOutAll, times_et(parity_rows(B.a[kRelS2L + r], ne), ne, F.E));
   }
   // real i of part p in an expansion of interleaved reals: the series' terms z^n have Re even in y
   // and Im odd in y, their parity in x that of n (Re) or n - 1 (Im)
   auto real_of = [](int p, int i) { return 4 * i + (p == 0 ? 0 : p == 1 ? 2 : p == 2 ? 3 : 1); };
-  const std::vector<double> S = parity_rows(M.a[kRelS2M], ne), L = parity_cols(M.a[kRelL2T], ne);
-  const std::vector<double> T0 = parity_rows(parity_cols(M.a[kRelNear], kNP), kNP);
+  const std::vector<double> S = parity_rows(B.a[kRelS2M], ne), L = parity_cols(B.a[kRelL2T], ne);
+  const std::vector<double> T0 = parity_rows(parity_cols(B.a[kRelNear], kNP), kNP);
   const int groups = kLinGroups + qp / 16;
   std::vector<double> li(size_t(kLinRows) * 64, 0.0), lia(size_t(groups) * 64 * 64, 0.0);
   std::vector<double> lo(size_t(kNP) * (kLoutCols + qp), 0.0), loa(size_t(kNP) * (kLoutAdjCols + qp), 0.0);
@@ -1028,6 +1028,25 @@ static void leaf_form_tables(Matrices& M, int Q) {
   set(kRelLO, kNP, kLoutCols + qp, std::move(lo));
   set(kRelLI + kNumFwd, groups * 64, 64, std::move(lia));
   set(kRelLO + kNumFwd, kNP, kLoutAdjCols + qp, std::move(loa));
+}
+
+// Transposes of the tables of forward ids [id0, id1); non-zeros of every table present.
+static void transpose_tables(Matrices& M, int id0, int id1) {
+  for (int id = id0; id < id1; ++id) {
+    const int r = M.M[id], c = M.K[id];
+    std::vector<double> T(size_t(r) * c);
+    for (int i = 0; i < r; ++i)
+      for (int j = 0; j < c; ++j) T[size_t(j) * r + i] = M.a[id][size_t(i) * c + j];
+    M.M[id + kNumFwd] = c; M.K[id + kNumFwd] = r; M.a[id + kNumFwd] = std::move(T);
+  }
+}
+static void count_tables(Matrices& M) {
+  for (int id = 0; id < kNumRel; ++id) {
+    if (M.a[id].empty()) continue;
+    double n = 0;
+    for (double v : M.a[id]) n += (v != 0.0);
+    M.nnz[id] = n;
+  }
 }
 
 static Matrices build_matrices(const int Q) {
@@ -1173,16 +1192,7 @@ static Matrices build_matrices(const int Q) {
     real_from_realout(Lt, kNP, Q, R);
     set(kRelL2T, kNP, kNE, std::move(R));
   }
-  leaf_form_tables(M, Q);
-  // transposes (the leaf kernels' adjoint tables have their own layout and are set already)
-  for (int id = 0; id < kNumFwd; ++id) {
-    if (id == kRelLI || id == kRelLO) continue;
-    int r = M.M[id], c = M.K[id];
-    std::vector<double> T(size_t(r) * c);
-    for (int i = 0; i < r; ++i)
-      for (int j = 0; j < c; ++j) T[size_t(j) * r + i] = M.a[id][size_t(i) * c + j];
-    set(id + kNumFwd, c, r, std::move(T));
-  }
+  transpose_tables(M, 0, kRelLeafForm);
   {  // the core's transpose keeps the padded shape: rows k (padded), columns l
     const int QP = pad16(Q);
     const std::vector<double>& H = M.a[kRelH];
@@ -1191,21 +1201,37 @@ static Matrices build_matrices(const int Q) {
       for (int k = 0; k < Q; ++k) T[size_t(k) * Q + l] = H[size_t(l) * Q + k];
     set(kRelH + kNumFwd, QP, Q, std::move(T));
   }
-  for (int id = 0; id < kNumRel; ++id) {
-    double n = 0;
-    for (double v : M.a[id]) n += (v != 0.0);
-    M.nnz[id] = n;
-  }
+  count_tables(M);
   return M;
 }
 
+static Matrices build_leaf_matrices(const int Q) {
+  const Matrices& B = matrices(Q);
+  Matrices M;
+  M.M = B.M; M.K = B.K; M.nnz = B.nnz; M.w_in = B.w_in; M.w_out = B.w_out; M.lnd = B.lnd; M.koff = B.koff;
+  M.a.assign(kNumRel, {});
+  leaf_form_tables(M, B, Q);
+  // the leaf kernels' adjoint tables have their own layout and are set already
+  transpose_tables(M, kRelLeafForm, kRelLI);
+  count_tables(M);
+  return M;
+}
+
+static const Matrices& build_once(int q, Matrices (*build)(int), std::mutex& mu, std::map<int, const Matrices*>& built) {
+  std::lock_guard<std::mutex> lk(mu);
+  auto it = built.find(q);
+  if (it == built.end()) it = built.emplace(q, new Matrices(build(q))).first;
+  return *it->second;
+}
 const Matrices& matrices(int q) {
   static std::mutex mu;
   static std::map<int, const Matrices*> built;
-  std::lock_guard<std::mutex> lk(mu);
-  auto it = built.find(q);
-  if (it == built.end()) it = built.emplace(q, new Matrices(build_matrices(q))).first;
-  return *it->second;
+  return build_once(q, build_matrices, mu, built);
+}
+const Matrices& leaf_matrices(int q) {
+  static std::mutex mu;
+  static std::map<int, const Matrices*> built;
+  return build_once(q, build_leaf_matrices, mu, built);
 }
 
 }  // namespace vp
