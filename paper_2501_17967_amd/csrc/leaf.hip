@@ -64,6 +64,11 @@ struct Raw {
     const d2 a = v[0], b = v[1], c = v[2], d = v[3];
     v[0] = a + c; v[1] = b + d; v[2] = a - c; v[3] = b - d;
   }
+  // before the sums, which would pass the type's range for values that s^2 brings back into it
+  __device__ __forceinline__ void scale(double s) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] *= s;
+  }
   __device__ __forceinline__ void zero() {
 #pragma unroll
     for (int q = 0; q < 4; ++q) v[q] = d2{0.0, 0.0};
@@ -100,14 +105,15 @@ __device__ __forceinline__ void in_store(int tid, Raw (&r)[4], const double (&sc
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int idx = tid + q * kThreads, slot = idx >> 5, k = 8 * ((idx & 31) >> 2) + 2 * (idx & 3);
+    r[q].scale(sc[q]);
     r[q].unmirror();
     r[q].sum_x();
     r[q].sum_y();
 #pragma unroll
     for (int pt = 0; pt < 4; ++pt) {
       double* b = Bs + (pt * kSlots + slot) * kLdIn + k;
-      b[0] = r[q].v[pt].x * sc[q];
-      b[1] = r[q].v[pt].y * sc[q];
+      b[0] = r[q].v[pt].x;
+      b[1] = r[q].v[pt].y;
     }
   }
 }
@@ -332,11 +338,10 @@ struct OutLoader {
   }
   __device__ __forceinline__ void store(int c, double scale, int tid, double* Bs) {
     if (c < 4) {
+      r.scale(scale);
       r.unmirror();
       r.sum_x();
       r.sum_y();
-#pragma unroll
-      for (int q = 0; q < 4; ++q) r.v[q] *= scale;
     } else if (!ADJ && c < 7) {
       r.sum_x();
     } else if (!ADJ && c < 10) {

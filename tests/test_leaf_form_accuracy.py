@@ -90,3 +90,19 @@ def test_fields_of_w_boxes_keep_their_digits():
         assert max(e) <= TOL, (n, e)
     for p in plans:
         p.close()
+
+
+@pytest.mark.gpu
+def test_values_near_the_largest_number():
+    # s^2 f lies far inside the type's range, and at this level so does what the translations make of it;
+    # powers of two change no digit
+    import torch
+    from paper_2501_17967_amd import volpot as vp
+    C, L, off = _plan_data([_uniform(7)], 5)
+    print("case large values,", len(L), "leaves", flush=True)
+    g = np.random.default_rng(5).uniform(-1.0, 1.0, (len(L), 256))   # of both signs: the total charge stays in range too
+    f = torch.from_numpy(g).cuda() * 2.0 ** 1023
+    plan = vp.Plan(C, L)
+    u, small = plan.apply(f), plan.apply(f * 2.0 ** -60)
+    assert bool(torch.isfinite(u).all()) and torch.equal(u, small * 2.0 ** 60)
+    plan.close()
