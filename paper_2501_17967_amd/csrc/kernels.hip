@@ -776,20 +776,20 @@ __global__ void rowsum_kernel(const double* __restrict__ x, double* __restrict__
 // to fill the chip, whose time is the dependent steps of one tile: their rows are shared out over the
 // waves (16 rows each; 32 of the leaf stages' 256), which divides a chunk's products, 50 to 80 in a
 // row, and the sum over a split tile's pieces by the number of waves.
-#define VP_CONFIGS(X)                                                                            \
+#define VP_CONFIGS(X)                                                                             \
   X(256, 32, 32, 4, 2, 4, 1, 256) X(256, 64, 32, 4, 2, 4, 2, 512) X(256, 16, 16, 2, 1, 8, 1, 512) \
   X(256, 32, 16, 4, 2, 4, 1, 256) X(256, 64, 16, 4, 2, 4, 2, 512)                                 \
   X(112, 64, 16, 7, 1, 1, 4, 256) X(96, 64, 16, 3, 2, 2, 2, 256) X(80, 64, 16, 5, 1, 1, 4, 256)   \
   X(112, 32, 16, 7, 2, 1, 1, 64) X(96, 32, 16, 6, 2, 1, 1, 64) X(80, 32, 16, 5, 2, 1, 1, 64)      \
   X(112, 16, 16, 1, 1, 7, 1, 448) X(96, 16, 16, 1, 1, 6, 1, 384) X(80, 16, 16, 1, 1, 5, 1, 320)   \
-  X(80, 64, 40, 5, 1, 1, 4, 256) X(80, 32, 40, 5, 1, 1, 2, 128) X(80, 16, 40, 1, 1, 5, 1, 320)     \
-  X(80, 64, 32, 5, 1, 1, 4, 256) X(80, 32, 32, 5, 1, 1, 2, 128) X(80, 16, 32, 1, 1, 5, 1, 320)     \
+  X(80, 64, 40, 5, 1, 1, 4, 256) X(80, 32, 40, 5, 1, 1, 2, 128) X(80, 16, 40, 1, 1, 5, 1, 320)    \
+  X(80, 64, 32, 5, 1, 1, 4, 256) X(80, 16, 32, 1, 1, 5, 1, 320)                                   \
   X(64, 64, 16, 4, 1, 1, 4, 256) X(64, 32, 16, 4, 2, 1, 1, 64) X(64, 16, 16, 1, 1, 4, 1, 256)     \
-  X(64, 64, 32, 4, 1, 1, 4, 256) X(64, 32, 32, 4, 1, 1, 2, 128) X(64, 16, 32, 1, 1, 4, 1, 256)     \
+  X(64, 64, 32, 4, 1, 1, 4, 256) X(64, 16, 32, 1, 1, 4, 1, 256)                                   \
   X(48, 64, 16, 3, 1, 1, 4, 256) X(48, 32, 16, 3, 2, 1, 1, 64) X(48, 16, 16, 1, 1, 3, 1, 192)     \
-  X(48, 64, 32, 3, 1, 1, 4, 256) X(48, 32, 32, 3, 1, 1, 2, 128) X(48, 16, 32, 1, 1, 3, 1, 192)     \
+  X(48, 64, 32, 3, 1, 1, 4, 256) X(48, 16, 32, 1, 1, 3, 1, 192)                                   \
   X(32, 64, 16, 2, 1, 1, 4, 256) X(32, 32, 16, 2, 2, 1, 1, 64) X(32, 16, 16, 1, 1, 2, 1, 128)     \
-  X(32, 64, 32, 2, 1, 1, 4, 256) X(32, 32, 32, 2, 1, 1, 2, 128) X(32, 16, 32, 1, 1, 2, 1, 128)
+  X(32, 64, 32, 2, 1, 1, 4, 256) X(32, 16, 32, 1, 1, 2, 1, 128)
 
 // Factored M2L instantiations: padded core rows, slots, complex terms q (= k-chunk); MT, NTT, WM,
 // WN, threads. A wave has all rows and both parts of 16 slots, so tiles of more slots only share the core.
