@@ -190,10 +190,12 @@ constexpr int kLeafTile = 32;  // leaves per tile of the leaf kernels
 constexpr int kLeafOutTileSmall = 16;  // of leaf_out in plans of up to kLeafOutSmall leaves (leaf.hip)
 constexpr int kLeafOutSmall = 8192;
 // Volume plans of at least this many leaves take the compressed near field. The larger the tree the more
-// it saves (1501 leaves forward 364 -> 276 us, 345k leaves forward and adjoint 14.9 -> 10.1 ms, with the
-// kernels of the time); below, both forms take as long as their launches' dependent steps (forward and
-// adjoint, 256 leaves: 236 us compressed, 239 low-rank; 442: 354, 408; 1024: 289, 297), and the low-rank
-// form stays, in which every adjacent pair keeps a row of its own.
+// it saves (345k leaves forward and adjoint 14.9 -> 10.1 ms when it came). Below, both forms take as long as
+// their launches' dependent steps, and which has fewer depends on the tree. Forward and adjoint at order 39,
+// compressed / low-rank: uniform trees of 64 leaves 170 / 138 us, 256: 186 / 171, 1024: 260 / 266; graded ones
+// of 88: 247 / 263, 187: 305 / 316, 460: 326 / 348, 721: 345 / 372; order 15 alike. The line stands where no tree
+// loses by the compressed form; below it uniform trees would lose up to a fifth and graded ones gain a
+// twentieth.
 constexpr int64_t kLeafFormMin = 512;
 
 // One piece of a stage's work as run by one block: n_chunks consecutive k-chunks of one tile,
