@@ -378,8 +378,9 @@ int volpot_autotune(int32_t n_trees, const int64_t* tree_offsets, const double* 
                     const int32_t* levels, int32_t p, const volpot_options* base,
                     const char* cache_path, volpot_options* best, double* best_ms);
 
-/* Measurement: the FP64 matrix-core rate this device sustains, the measured companion of the
- * published 78.6 TFLOP/s in roofline reports. Launches `blocks` workgroups of 256 threads on the
+/* Measurement: the rate of a stream of FP64 matrix instructions on register operands (49.5 TFLOP/s
+ * of the published 78.6). Not the device's ceiling: a large library matrix product sustains 72.5.
+ * Launches `blocks` workgroups of 256 threads on the
  * stream; every wave runs `iters` rounds of 8 independent v_mfma_f64_16x16x4f64 (2,048 flops
  * each) on register operands, so one launch does blocks * 4 * iters * 8 * 2048 flops; time it
  * with events on the same stream. Thread t of block k writes out_dev[256 k + t], the sum of its
