@@ -1498,13 +1498,14 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   };
   if (lf) {
     // ANEARC: cotangents of each leaf's outgoing values, from those of what the adjacent leaves
-    // receive across their edges and of the locals that its X boxes take; ANEARC48 adds the corners'
+    // receive across their edges and of the locals that its X boxes take; ANEARC48 adds the corners'.
+    // A leaf with a corner neighbour has one across an edge too, so ANEARC has written its row; a leaf that
+    // is a whole tree has neither, and its row is zero from the plan's creation on.
     for (int c = 0; c < 2; ++c) {
       std::vector<int32_t> tg;
       for (int32_t b : leaf_order) {
-        bool any = c == 0;
-        if (c)
-          for (auto& e : Uinv[size_t(b)]) any = any || (e.first != 0 && dir_near(e.first) >= 4);
+        bool any = !c && !Xinv[size_t(b)].empty();
+        for (auto& e : Uinv[size_t(b)]) any = any || (e.first != 0 && dir_near(e.first) / 4 == c);
         if (any) tg.push_back(b);
       }
       if (tg.empty()) continue;

@@ -46,3 +46,15 @@ def test_leaf_output_reports_the_tiles_it_launches(vp, trees, tile):
             assert s["tile"] == tile and s["n_tiles"] == -(-n // tile), s
             assert s["flops_issued"] == 2.0 * 256 * s["inner"] * tile * s["n_tiles"]
             assert split_min >= 0 or s["n_blocks"] == s["n_tiles"], s
+
+
+def test_leaves_without_neighbours_are_no_targets(vp):
+    # trees of one leaf receive and send nothing; beside others they add nothing to the edge and corner stages
+    fwd, adj = _stages(vp, [_uniform(0)] * 600)
+    assert [n for n in fwd if fwd[n]["n_tiles"]] == ["S2M", "NEAR+LOCT"]
+    assert "ANEARC" not in adj and "ANEARC48" not in adj
+    trees = [_random(3, 260, 9)]
+    for alone, beside in zip(_stages(vp, trees), _stages(vp, [_uniform(0)] * 40 + trees)):
+        for n in alone:
+            if n in ("NEARC", "NEARC48", "ANEARC", "ANEARC48"):
+                assert beside[n]["n_tiles"] == alone[n]["n_tiles"], n
