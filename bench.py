@@ -406,12 +406,12 @@ def measured_peaks(dev):
         bw = max(bw, 5 * 2 * 8 * n / (e0.elapsed_time(e1) * 1e-3))
     del a, b, c, out
     return {"fp64_gemm_tflops": gemm / 1e12, "fp64_mfma_tflops": best / 1e12, "hbm_copy_gbs": bw / 1e9,
-            "how": "torch.mm of 8192 x 8192 FP64 matrices, best of 3 x 5; FP64 MFMA only on register operands (2048 x 256 threads, 8 chains per wave), best of 3; "
-                   "torch copy_ of 2 GiB (read + write bytes), best of 3 x 5 copies"}
+            "how": "torch.mm of 8192 x 8192 FP64 matrices, best of 3 x 5; FP64 MFMA only on register operands "
+                   "(2048 x 256 threads, 8 chains per wave), best of 3; torch copy_ of 2 GiB (read + write bytes), best of 3 x 5 copies"}
 
 
 def _shape_given(args):
-    return bool(args.tile_leaf and args.tile_box and args.split_min is not None and args.overlap is not None)
+    return bool(args.tile_leaf and args.tile_box is not None and args.split_min is not None and args.overlap is not None)
 
 
 def _shape_from_args(args):
@@ -758,7 +758,7 @@ def main():
     ap.add_argument("--tile-leaf", type=int, default=0,
                     help="launch shape of the forest (and of --single-only): with tile-box, split-min and overlap "
                          "all given, no autotuning")
-    ap.add_argument("--tile-box", type=int, default=0)
+    ap.add_argument("--tile-box", type=int, default=None)
     ap.add_argument("--split-min", type=int, default=None)
     ap.add_argument("--overlap", type=int, default=None)
     ap.add_argument("--tile-leaf-exp", type=int, default=0)
@@ -771,7 +771,7 @@ def main():
     ap.add_argument("--dense-near", action="store_true",
                     help="dense 256 x 256 adjacent-leaf tables instead of their low-rank factors (for comparison)")
     ap.add_argument("--peaks-only", action="store_true",
-                    help="only measure this device's FP64 matrix-core and HBM copy rates, print them and exit")
+                    help="only measure this device's FP64 matrix and HBM copy rates, print them and exit")
     ap.add_argument("--calibrate-copy-mib", type=int, default=0,
                     help="only run 5 device-to-device copies of this many MiB (counter calibration) and exit")
     args = ap.parse_args()

@@ -1,8 +1,8 @@
 // HIP kernels of the box code for gfx950 (CDNA4), FP64 throughout.
 //
-// One kernel template serves every stage but the leaf kernels (leaf.hip): a grouped-relation GEMM. A workgroup owns a tile of
-// NT output vectors ("slots") of M rows each and walks the relation segments present in the
-// tile (sorted by relation id). For relation r it accumulates
+// One kernel template serves every stage but the leaf kernels (leaf.hip): a grouped-relation GEMM.
+// A workgroup owns a tile of NT output vectors ("slots") of M rows each and walks the relation
+// segments present in the tile (sorted by relation id). For relation r it accumulates
 //     C[:, slot] += A_r[:, k-chunk] * B[k-chunk, slot]
 // with v_mfma_f64_16x16x4f64, where B gathers the NT source vectors by index. Both operands are
 // staged through LDS in k-chunks of KC; the global loads of chunk c+1 are issued into registers
@@ -11,8 +11,10 @@
 // copy) and every LDS fragment read a contiguous 512-byte wave access. A segment's metadata
 // (table pointer, source family, this thread's source indices) is fetched once per segment.
 //
-// Each output vector has exactly one owner and a fixed relation order: no atomics, bitwise
-// deterministic, identical whether a tree is applied alone or inside a forest.
+// Each output vector is written by one block, its terms summed in a fixed order: results are
+// bitwise repeatable. A tile cut between blocks is finished by the block that arrives last, found
+// by an atomic counter, which adds the pieces in their order. A plan's size decides its near-field
+// form, its tiles and its cuts, so a tree applied alone and inside a forest agrees to rounding.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
