@@ -224,7 +224,8 @@ __device__ __forceinline__ void wave_lds_fence() {
 // l % 8 of each 16-term chunk of the sources l / 8 + 8 q. Bound by the matrix cores (0.72 of their
 // time at 112 rows) and, where a tile has one segment, by its stores: 345k-leaf forest, edge stage
 // 877 -> 770 us (1.4M targets, 96 rows, mostly one segment of K = 112), adjoint 910 -> 770 (345k targets,
-// 112 rows, 3.4 segments), corners 477 -> 423 and 317 -> 295, far-field pair stages 280 -> 256, 192 -> 182.
+// 112 rows, 3.4 segments), corners 477 -> 423 and 317 -> 295, far-field pair stages 280 -> 256, 192 -> 182
+// (since the edge stages took the W boxes off the diagonals: 838, 766, 381, 297, 256, 221).
 __device__ const double kZeroRow[512] = {};  // what a slot without a source reads
 
 struct LoaderW {

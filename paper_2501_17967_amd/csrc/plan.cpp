@@ -894,7 +894,8 @@ int build_plan(int32_t n_trees, const int64_t* offsets, const double* centres, c
   // In the compressed near field they take tiles of one wave once there are two for every SIMD
   // (65536 targets): below, such tiles are cut along their segments to fill the chip, and 64 slots
   // shared by four waves need fewer cuts. Edge stage of 345k leaves (1.4M targets) 877 -> 770 us, its
-  // adjoint (345k) 910 -> 770; 16.7k leaves (67k / 16.7k targets) 60 -> 61 and 66 -> 76.
+  // adjoint (345k) 910 -> 770 (838 and 766 with the W boxes off the diagonals, which it has taken from the
+  // corner stage since); 16.7k leaves (67k / 16.7k targets) 60 -> 61 and 66 -> 76.
   auto data_tile = [&](size_t targets) { return targets <= kBoxTileSmall ? 16 : lf && targets >= 65536 ? kWaveTile : kLeafDataTile; };
   // The leaf stages with K = 80 (L2T, M2T and their transposes' counterparts S2M^T, S2L^T) do
   // little work per tile: on small trees 16-slot tiles give more independent workgroups to hide
