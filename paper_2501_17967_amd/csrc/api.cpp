@@ -357,8 +357,13 @@ int upload(volpot_plan_s* p) {
   const size_t per_leaf = size_t(P.n_leaves) * sizeof(double), nlf = lf ? per_leaf : 0;
   const size_t o_mp = work(nb), o_loc = work(nb), o_lb = work(vol ? nb : 0), o_ab = work(vol ? nb : 0), o_far = work(nb);
   const size_t o_afar = work(vol ? nb : 0), o_nw = work(nlr), o_nwa = work(vol ? nlr : 0);
-  const size_t o_e = work(nlf * kOutAll), o_ea = work(nlf * kOutAll), o_hs = work(nlf * 4 * kEdge), o_hsa = work(nlf * 4 * kEdge);
+  const size_t o_ea = work(nlf * kOutAll), o_hs = work(nlf * 4 * kEdge), o_hsa = work(nlf * 4 * kEdge);
   const size_t o_hc = work(nlf * 4 * kCorner), o_hca = work(nlf * 4 * kCorner);
+  // The outgoing values share the corner cotangents' memory: one belongs to the forward apply and one to the
+  // adjoint, a plan runs one at a time, and each is written whole by the first stage of its apply. The other
+  // arrays hold rows that no stage writes and that stay zero.
+  static_assert(kOutAll <= 4 * kCorner, "outgoing values within the corner cotangents");
+  const size_t o_e = o_hca;
   const size_t o_us = work(vol ? per_leaf : 0), o_fs = work(vol && !lf ? per_leaf * kNP : 0);
   const size_t o_pmom = work(n_pairs * 3 * kNP * sizeof(double));
   const size_t o_sq = work(std::max<size_t>(size_t(P.n_src), 1) * sizeof(double));

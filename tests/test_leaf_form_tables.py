@@ -1,4 +1,5 @@
-"""Plans that do not take the compressed near field neither build nor hold its tables."""
+"""Device memory of the near-field forms: plans that do not take the compressed form neither build nor hold
+its tables, and one that does holds no more than the low-rank form's pair rows took."""
 import numpy as np
 import pytest
 
@@ -19,3 +20,16 @@ def test_small_plan_holds_no_compressed_tables(eps, ne):
     print("  %d bytes, at most %d" % (held, 16 * doubles + (1 << 20)), flush=True)
     assert held <= 16 * doubles + (1 << 20)
     plan.close()
+
+
+def test_compressed_plan_holds_no_more_than_pair_rows():
+    from test_leaf_form import _plan_data, _uniform
+    from paper_2501_17967_amd import volpot as vp
+    C, L, _ = _plan_data([_uniform(9)], 1)
+    print("case memory,", len(L), "leaves", flush=True)
+    plan = vp.Plan(C, L)
+    held = plan.info()["device_bytes"]
+    plan.close()
+    bound = 4752.9e6   # with two rows of 64 doubles a pair, the scaled input and their schedules
+    print("  %d bytes, at most %d" % (held, bound), flush=True)
+    assert held <= bound
