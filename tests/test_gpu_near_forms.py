@@ -150,3 +150,29 @@ def test_small_stages_share_launches(vp, name, trees, saved, eps):
     print("  stages", stages, "launches", got, flush=True)
     assert (stages[0] - got[0], stages[1] - got[1]) == saved
     plan.close()
+
+
+@pytest.mark.parametrize("name,trees", [
+    ("low-rank", [_random(9, 30, 8), _uniform(2), _uniform(0), _random(4, 25, 7)]),
+    ("compressed", [_random(3, 60, 7), _uniform(4), _uniform(0), _random(5, 40, 9)]),
+    ("compressed", [_uniform(7), _random(5, 400, 10), _uniform(1)]),
+])
+def test_nan_stays_in_its_tree_and_its_apply(vp, name, trees):
+    # a NaN in one tree of a forest reaches no other tree, and nothing of it is left in the plan's memory
+    import torch
+    C, L, off = _plan_data(trees, 8)
+    print("case NaN", name, len(L), "leaves", flush=True)
+    plan = vp.Plan(C, L, tree_offsets=off)
+    assert _form(plan) == name
+    x, = _values(len(L), 8, 1)
+    for fn in (plan.apply, plan.apply_adjoint):
+        clean = fn(x).clone()
+        for t in range(len(trees)):
+            bad = x.clone()
+            bad[off[t] + (off[t + 1] - off[t]) // 2, 77] = float("nan")
+            got = fn(bad)
+            other = torch.ones(len(L), dtype=torch.bool, device="cuda")
+            other[off[t]:off[t + 1]] = False
+            assert torch.equal(got[other], clean[other]) and bool(torch.isnan(got[~other]).all())
+            assert torch.equal(fn(x), clean)
+    plan.close()
