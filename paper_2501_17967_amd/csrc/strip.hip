@@ -12,7 +12,8 @@
 // The blocks of E are most of the bytes (Bi^2 per element, 50 MB at 56 elements of 24 x 16 nodes) and wait
 // for nothing but b, so their product (14 us) runs beside the sweep, a chain in one workgroup (24 us);
 // only the 2m columns that meet z* and t* are left for the last launch: 4 + 28 + 6 us where the
-// launches took 5 + 24 + 14.
+// launches took 5 + 24 + 14. Small elements (below kSplitQ, kSplitM) keep those: strip_sweep_kernel alone, then
+// strip_solution_full_kernel.
 // In the sweep, wave 0 runs the recurrence with lane a holding component a of the vector (each
 // step writes the vector to a wave-private LDS slot and reads it back as a broadcast), reading
 // its m x m matrices from LDS, while waves 1-3 stage the next chunk of matrices (double buffer,
@@ -29,7 +30,15 @@ namespace vp {
 namespace {
 
 constexpr int kStripThreads = 256;
+constexpr int kSolThreads = 512;  // full solution kernel: 8 waves split the columns of a 64-row tile
 constexpr int kMaxM = 30;  // n_r <= 32
+// Elements of at least kSplitQ nodes along and kSplitM + 2 across take the product of E_k with b_k beside the
+// sweep. Elsewhere the sweep runs alone and strip_solution_full_kernel forms x_k in one product: of the m q
+// columns of E only those of the q - 2 inner nodes can run ahead, and beside their stream (and in the kernel
+// they share) the sweep takes 2 to 6 us longer. Apply with the product beside the sweep / after it, 56 elements:
+// 8 x 24 nodes 54.5 / 49.5 us, 12 x 20 44.6 / 42.3, 14 x 20 47.2 / 46.7, 16 x 24 62.8 / 66.3, 24 x 16 37.9 / 43.4;
+// 160 elements of 16 x 4 nodes 42.5 / 40.9.
+constexpr int kSplitQ = 14, kSplitM = 4;
 
 __device__ __forceinline__ double lane_value(double v, int lane) {
   // the value held by `lane` (wave-uniform) of this wavefront
@@ -233,6 +242,12 @@ __device__ __forceinline__ void strip_sweep(const StripDevice& d, double* sm) {
 }
 
 template <int m>
+__global__ void __launch_bounds__(kStripThreads) strip_sweep_kernel(StripDevice d) {
+  extern __shared__ double sm[];
+  strip_sweep<m>(d, sm);
+}
+
+template <int m>
 __global__ void __launch_bounds__(kStripThreads)
     strip_middle_kernel(StripDevice d, const double* __restrict__ f, double* __restrict__ x) {
   extern __shared__ double sm[];  // the sweep's buffers; r (Bi) and partial sums (kStripThreads)
@@ -313,6 +328,54 @@ __global__ void __launch_bounds__(kStripThreads) strip_solution_kernel(StripDevi
   }
 }
 
+// The whole of x_k = E_k (b_k + P' z*_k - P t*_{k+1}), after a sweep that ran alone.
+__global__ void __launch_bounds__(kSolThreads)
+    strip_solution_full_kernel(StripDevice d, const double* __restrict__ f, double* __restrict__ x) {
+  extern __shared__ double sm[];  // r (Bi), z* (m), t* (m), partial sums (kSolThreads)
+  const int k = blockIdx.x, tile = blockIdx.y, q = d.q, Bi = d.Bi, m = d.m, B = d.B;
+  double* r = sm;
+  double* zs = r + Bi;
+  double* ts = zs + m;
+  double* red = ts + m;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  if (tid < m) {
+    const double* P = d.Pz + size_t(k) * m * m + size_t(tid) * m;
+    double v = d.z[size_t(k) * m + tid];
+    for (int b = 0; b < m; ++b) v = fma(P[b], d.h[b], v);
+    zs[tid] = v;
+  } else if (tid >= 64 && tid < 64 + m) {
+    const int a = tid - 64, m2 = 2 * m;
+    const double* P = d.Pt + size_t(k + 1) * m * m2 + size_t(a) * m2;
+    double v = d.t[size_t(k + 1) * m + a];
+    for (int j = 0; j < m2; ++j) v = fma(P[j], d.h[j], v);
+    ts[a] = v;
+  }
+  __syncthreads();
+  const size_t base = size_t(k) * B + q;
+  for (int c = tid; c < Bi; c += kSolThreads) {
+    const int j = c % q, a = c / q;
+    r[c] = j == 0 ? zs[a] : (j == q - 1 ? -ts[a] : f[base + c] * d.rs[base + c]);
+  }
+  __syncthreads();
+  constexpr int kWaves = kSolThreads / 64;
+  const int p = tile * 64 + lane, per = (Bi + kWaves - 1) / kWaves, c0 = wave * per, c1 = min(Bi, c0 + per);
+  double acc = 0.0;
+  if (p < Bi) {
+    const double* E = d.EiT + size_t(k) * Bi * Bi + p;
+#pragma unroll 8
+    for (int c = c0; c < c1; ++c) acc = fma(E[size_t(c) * Bi], r[c], acc);
+  }
+  red[tid] = acc;
+  __syncthreads();
+  if (wave == 0 && p < Bi) {
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) v += red[w * 64 + lane];
+    x[base + p] = v;
+  }
+  if (tile == 0 && tid < 2 * q) x[size_t(k) * B + (tid < q ? tid : B - 2 * q + tid)] = 0.0;
+}
+
 // Work vectors of the apply (s, w, z, t, h) for callers that cannot allocate: one static array
 // per device, held until the process ends. Host code reaches it only through the address
 // hipGetSymbolAddress returns on each device (strip_scratch); the array's name is not a device
@@ -344,16 +407,21 @@ hipError_t launch_strip_solve(const StripDevice& d, const double* f, double* v, 
   const size_t sweep = size_t(2) * d.chunk * (d.m * d.m + d.m) + 32, product = size_t(d.Bi) + kStripThreads;
   hipLaunchKernelGGL(strip_rhs_kernel, dim3(unsigned(d.n), unsigned((2 * d.m + 3) / 4)), dim3(kStripThreads),
                      size_t(d.Bi) * sizeof(double), stream, d, f);
+  using Sweep = void (*)(StripDevice);
   using Middle = void (*)(StripDevice, const double*, double*);
-  static const Middle middle[kMaxM + 1] = {
-      nullptr, nullptr, strip_middle_kernel<2>, strip_middle_kernel<3>, strip_middle_kernel<4>, strip_middle_kernel<5>,
-      strip_middle_kernel<6>, strip_middle_kernel<7>, strip_middle_kernel<8>, strip_middle_kernel<9>, strip_middle_kernel<10>,
-      strip_middle_kernel<11>, strip_middle_kernel<12>, strip_middle_kernel<13>, strip_middle_kernel<14>,
-      strip_middle_kernel<15>, strip_middle_kernel<16>, strip_middle_kernel<17>, strip_middle_kernel<18>,
-      strip_middle_kernel<19>, strip_middle_kernel<20>, strip_middle_kernel<21>, strip_middle_kernel<22>,
-      strip_middle_kernel<23>, strip_middle_kernel<24>, strip_middle_kernel<25>, strip_middle_kernel<26>,
-      strip_middle_kernel<27>, strip_middle_kernel<28>, strip_middle_kernel<29>, strip_middle_kernel<30>};
+#define VP_STRIP_M(K)                                                                                          \
+  nullptr, nullptr, K<2>, K<3>, K<4>, K<5>, K<6>, K<7>, K<8>, K<9>, K<10>, K<11>, K<12>, K<13>, K<14>, K<15>, \
+      K<16>, K<17>, K<18>, K<19>, K<20>, K<21>, K<22>, K<23>, K<24>, K<25>, K<26>, K<27>, K<28>, K<29>, K<30>
+  static const Sweep sweeps[kMaxM + 1] = {VP_STRIP_M(strip_sweep_kernel)};
+  static const Middle middle[kMaxM + 1] = {VP_STRIP_M(strip_middle_kernel)};
+#undef VP_STRIP_M
   const unsigned tiles = unsigned((d.Bi + 63) / 64);
+  if (d.q < kSplitQ || d.m < kSplitM) {
+    hipLaunchKernelGGL(sweeps[d.m], dim3(1), dim3(kStripThreads), sweep * sizeof(double), stream, d);
+    hipLaunchKernelGGL(strip_solution_full_kernel, dim3(unsigned(d.n), tiles), dim3(kSolThreads),
+                       size_t(d.Bi + 2 * d.m + kSolThreads) * sizeof(double), stream, d, f, v);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(middle[d.m], dim3(1 + unsigned(d.n) * tiles), dim3(kStripThreads),
                      (sweep > product ? sweep : product) * sizeof(double), stream, d, f, v);
   hipLaunchKernelGGL(strip_solution_kernel, dim3(unsigned(d.n), tiles), dim3(kStripThreads), 0, stream, d, v);
